@@ -24,7 +24,6 @@
 // features of one token for the epilogue.  Tiles go out in an XCD-aware
 // order (consecutive ids on one XCD share an activation tile in its L2).
 #include <algorithm>
-#include <cstdlib>
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -34,12 +33,26 @@ namespace glds {
 
 typedef __attribute__((address_space(3))) void lds_void;
 
-// XOR swizzle of the 16-byte chunks of an LDS row of BKB bytes: 128-byte rows
-// by (row >> 1) & 7, 64-byte rows by (row >> 2) & 3, so the 16 rows that one
-// fragment read touches fall in distinct banks.
-template <int BKB>
+// EPI_RESID and EPI_RESID_LN on states in separate buffers whose token count
+// is not a multiple of 64: the 64 rows of a wave may lie in several states.
+constexpr int EPI_RESID_SPLIT = 6, EPI_RESID_LN_SPLIT = 7;
+constexpr bool epi_resid(int e) { return e == EPI_RESID || e == EPI_RESID_SPLIT; }
+constexpr bool epi_resid_ln(int e) { return e == EPI_RESID_LN || e == EPI_RESID_LN_SPLIT; }
+inline bool splits(const EpiArgs &ep) { return ep.resid_ptrs && ep.T % 64 != 0; }
+
+// XOR swizzle of the 16-byte chunks of a 128-byte LDS row, so that a fragment
+// read (ds_read_b128) has no bank conflict.  Its 64 lanes (row r16 = l % 16,
+// chunk by g = l / 16) go through LDS 16 at a time: in the lower half of the
+// wave rows 0-3 and 12-15 of g = 0 with rows 4-11 of g = 1, then the others;
+// the upper half alike with g = 2, 3.  bf16 lanes of neighbouring g read
+// neighbouring chunks (4 o + g): (row >> 1) & 7.  e4m3 lanes read chunks 2 g
+// and 2 g + 1, two apart: with t = (row >> 1) & 7 rows 0-3 and 12-15 get the
+// even and rows 4-11 the odd values (with the bf16 swizzle half of the LDS
+// cycles of the e4m3 GEMM were conflicts).
+template <bool FP8>
 __device__ __forceinline__ int swz(int row) {
-    return BKB == 128 ? (row >> 1) & 7 : (row >> 2) & 3;
+    const int t = (row >> 1) & 7;
+    return FP8 ? (t & 4) | ((t & 1) << 1) | (((t >> 1) ^ (t >> 2)) & 1) : t;
 }
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, unsigned bytes) {
@@ -50,117 +63,40 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, unsig
                                              0x00020000);
 }
 
-__device__ __forceinline__ void store4(float *p, f32x4 v) {
-    *(float4 *)p = make_float4(v[0], v[1], v[2], v[3]);
-}
-__device__ __forceinline__ void store4(bf16 *p, f32x4 v) {
-    uint2 u;
-    u.x = pack_bf16x2(v[0], v[1]);
-    u.y = pack_bf16x2(v[2], v[3]);
-    *(uint2 *)p = u;
-}
+// Epilogue stores (and residual loads) go through buffer resources whose base
+// is the wave's first row, so that a lane's 32-bit offsets are the same for
+// every tile and rows past M fail the range check: a store there is dropped,
+// a load reads zero.
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-// Epilogue on four consecutive output features n..n+3 of token m.  For the
-// QKV scatter, `qkv_base` is the element offset of (part, head 0, token 0)
-// of the tile's part, `hc` the channel within the part and `qs` the factor
-// of the part (the Q scale or 1, times out_mul[part] when e4m3 codes are
-// stored): all but hc are uniform over the tile.
-template <int EPI>
-__device__ __forceinline__ float epilogue4(const EpiArgs &ep, int N, long m, int n, f32x4 v,
-                                           size_t qkv_base, int hc, float qs, float dq, float4 b, float4 rr) {
-    // explicit FMAs: the rounding of every element must not depend on how
-    // the compiler contracts each unrolled copy (a token's result must not
-    // depend on its position in the tile, i.e. on the batch)
-    v[0] = fmaf(v[0], dq, b.x); v[1] = fmaf(v[1], dq, b.y); v[2] = fmaf(v[2], dq, b.z); v[3] = fmaf(v[3], dq, b.w);
-    if constexpr (epi_qkv(EPI)) {
-        if (EPI == EPI_QKV_ROPE && n < 2 * ep.C) {
-            float r[4] = {v[0], v[1], v[2], v[3]};
-            rope_rotate(r, 4, hc & 31, m, ep);
-            v[0] = r[0]; v[1] = r[1]; v[2] = r[2]; v[3] = r[3];
-        }
-        v[0] *= qs; v[1] *= qs; v[2] *= qs; v[3] *= qs;
-        const size_t o = qkv_base + ((size_t)(hc >> 5) * ep.Mtot + m) * 32 + (hc & 31);
-        if (ep.out8) *(unsigned *)((unsigned char *)ep.out + o) = e4m3x4(v[0], v[1], v[2], v[3]);
-        else store4((bf16 *)ep.out + o, v);
-    } else if constexpr (EPI == EPI_GELU) {
-        v[0] = gelu_as4(v[0]); v[1] = gelu_as4(v[1]); v[2] = gelu_as4(v[2]); v[3] = gelu_as4(v[3]);
-        if (ep.out8) {
-            const float om = ep.out_mul[0];
-            *(unsigned *)((unsigned char *)ep.out + (size_t)m * N + n) = e4m3x4(v[0] * om, v[1] * om, v[2] * om, v[3] * om);
-        } else {
-            store4((bf16 *)ep.out + (size_t)m * N + n, v);
-        }
-    } else if constexpr (EPI == EPI_RESID) {
-        // rr: the residual values at (m, n..n+3), loaded by the caller
-        *(float4 *)(state_row(ep.resid, ep.resid_ptrs, (unsigned)ep.T, ep.dT, (unsigned)m, N) + n) =
-            make_float4(rr.x + v[0], rr.y + v[1], rr.z + v[2], rr.w + v[3]);
-    } else {
-        store4((bf16 *)ep.out + (size_t)m * N + n, v);
+// An offset that fails every range check.
+constexpr unsigned DROP = 0xfffff000u;
+
+// A wave's rows of an output: `bytes` from `p` on; at(n): the same n bytes on.
+// Constant byte offsets of stores go into the resource's base and not into the
+// instruction's scalar offset: after a 16-byte store with a scalar offset
+// register the compiler may overwrite the data registers in the very next
+// instruction, and such stores then wrote some of the new values (single rows
+// of MLP1's output at N = 1024); without that register it keeps the two
+// instructions between that the hardware needs.
+struct RowSpan {
+    unsigned long long p;
+    unsigned bytes;
+    __device__ __forceinline__ RowSpan(const void *q, unsigned n) {
+        const unsigned long long v = (unsigned long long)q;
+        p = ((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(v >> 32)) << 32) |
+            (unsigned)__builtin_amdgcn_readfirstlane((unsigned)v);
+        bytes = __builtin_amdgcn_readfirstlane(n);
     }
-    if (!ep.out_amax) return 0.f;           // amax only feeds FP8 requantization
-    return fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
-}
-
-__device__ __forceinline__ void store8(bf16 *p, const float *v) {
-    uint4 u;
-    u.x = pack_bf16x2(v[0], v[1]);
-    u.y = pack_bf16x2(v[2], v[3]);
-    u.z = pack_bf16x2(v[4], v[5]);
-    u.w = pack_bf16x2(v[6], v[7]);
-    *(uint4 *)p = u;
-}
-
-// Epilogue on eight consecutive output features n..n+7 of (global) token
-// mg, from two MFMA tiles of permuted W rows (16-byte stores; 32 bytes for
-// the float32 residual).  Same conventions as epilogue4.
-template <int EPI>
-__device__ __forceinline__ float epilogue8(const EpiArgs &ep, int N, long mg, int n, f32x4 a, f32x4 c,
-                                           size_t qkv_base, int hc, float qs, float dq, const float2 *rc,
-                                           float4 b0, float4 b1) {
-    float v[8] = {a[0], a[1], a[2], a[3], c[0], c[1], c[2], c[3]};
-    const float bb[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = fmaf(v[i], dq, bb[i]);    // explicit FMA, as in epilogue4
-    if constexpr (epi_qkv(EPI)) {
-        if (EPI == EPI_QKV_ROPE && n < 2 * ep.C) {
-            // rc: (cos, sin) of this row's 4 channel pairs (hc & 31) / 2 ..
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float a0 = v[2 * i], a1 = v[2 * i + 1];
-                v[2 * i] = fmaf(a0, rc[i].x, -(a1 * rc[i].y));
-                v[2 * i + 1] = fmaf(a0, rc[i].y, a1 * rc[i].x);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] *= qs;
-        const size_t o = qkv_base + ((size_t)(hc >> 5) * ep.Mtot + mg) * 32 + (hc & 31);
-        if (ep.out8) *(uint2 *)((unsigned char *)ep.out + o) = make_uint2(e4m3x4(v[0], v[1], v[2], v[3]), e4m3x4(v[4], v[5], v[6], v[7]));
-        else store8((bf16 *)ep.out + o, v);
-    } else if constexpr (EPI == EPI_GELU) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = gelu_as4(v[i]);
-        if (ep.out8) {
-            const float om = ep.out_mul[0];
-            *(uint2 *)((unsigned char *)ep.out + (size_t)mg * N + n) =
-                make_uint2(e4m3x4(v[0] * om, v[1] * om, v[2] * om, v[3] * om), e4m3x4(v[4] * om, v[5] * om, v[6] * om, v[7] * om));
-        } else {
-            store8((bf16 *)ep.out + (size_t)mg * N + n, v);
-        }
-    } else if constexpr (EPI == EPI_RESID) {
-        float4 *r = (float4 *)(state_row(ep.resid, ep.resid_ptrs, (unsigned)ep.T, ep.dT, (unsigned)mg, N) + n);
-        float4 x0 = r[0], x1 = r[1];
-        x0.x += v[0]; x0.y += v[1]; x0.z += v[2]; x0.w += v[3];
-        x1.x += v[4]; x1.y += v[5]; x1.z += v[6]; x1.w += v[7];
-        r[0] = x0;
-        r[1] = x1;
-    } else {
-        store8((bf16 *)ep.out + (size_t)mg * N + n, v);
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t at(unsigned n) const {
+        return __builtin_amdgcn_make_buffer_rsrc((void *)(p + n), 0, bytes > n ? bytes - n : 0u, 0x00020000);
     }
-    if (!ep.out_amax) return 0.f;
-    float m = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(v[i]));
-    return m;
+};
+
+__device__ __forceinline__ u32x2 pack4_bf16(const float *v) { return u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])}; }
+__device__ __forceinline__ u32x4 pack8_bf16(const float *v) {
+    return u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
 }
 
 // Wait until at most min(later, D - 2) stages of PER load instructions each
@@ -244,80 +180,86 @@ __device__ __forceinline__ void mma_stage(const unsigned char *sa, const unsigne
 // value * out_mul[2] after the dequantization acc * a_dequant * w_dequant.
 // Rows whose four tokens leave a lat row (X or the state size not a
 // multiple of 4) are stored one by one.
-template <int TM, int TN, bool FP8>
+template <int TM, int TN, bool FP8, typename F>
 __device__ __forceinline__ void vt_epilogue(const EpiArgs &ep, const float *bias, int M, int r0, int f0,
-                                            const f32x4 (&acc)[TN][TM], int g, int r16) {
+                                            const f32x4 (&acc)[TN][TM], int g, int r16, F pre_store) {
+    constexpr unsigned ES = FP8 ? 1 : 2;
     float bv[TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) bv[j] = bias[f0 + 16 * j + r16];
     const float dq = FP8 ? ep.a_dequant * ep.w_dequant : 1.0f;
     const float om = FP8 ? ep.out_mul[2] : 1.0f;
     const int X = ep.vX, xp = ep.vxp, YX = ep.vY * ep.vX;
-    const bool quad = (X & 3) == 0 && (ep.T & 3) == 0;
+    pre_store();
+    // element 0 of (head f0 / 32, state of the wave's first row); a head's plane, and a state's in it
+    const unsigned b0 = udiv((unsigned)__builtin_amdgcn_readfirstlane(min(r0, M - 1) + ep.row0), ep.dT);
+    const size_t state = (size_t)ep.vZ * ep.vY * xp * 32 * ES, plane = state * ep.vB;
+    const unsigned char *vbase = (const unsigned char *)ep.vt + (size_t)__builtin_amdgcn_readfirstlane(f0 >> 5) * plane + b0 * state;
+    // byte offset from vbase of position i of token row mg's (state, level, lat) row, channel r16
+    auto row_off = [&](unsigned mg, int &x) -> unsigned {
+        const unsigned b = udiv(mg, ep.dT), tt = mg - b * (unsigned)ep.T;
+        const unsigned z = udiv(tt, ep.dYX), rr = tt - z * (unsigned)YX;
+        const unsigned y = udiv(rr, ep.dX);
+        x = (int)(rr - y * (unsigned)X);
+        return (((b - b0) * (unsigned)ep.vZ + z) * (unsigned)ep.vY + y) * (unsigned)xp * (32 * ES) + (unsigned)r16 * 4 * ES;
+    };
+    if ((X & 3) == 0 && (ep.T & 3) == 0) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const int m4 = r0 + 16 * i + 4 * g;
-        if (m4 >= M) continue;
-        if (quad) {
-            const unsigned mg = (unsigned)(m4 + ep.row0);
-            const unsigned b = udiv(mg, ep.dT), tt = mg - b * (unsigned)ep.T;
-            const unsigned z = udiv(tt, ep.dYX), rr = tt - z * (unsigned)YX;
-            const unsigned y = udiv(rr, ep.dX), x = rr - y * (unsigned)X;
+        for (int i = 0; i < TM; ++i) {
+            const int m4 = r0 + 16 * i + 4 * g;
+            int x;
+            const unsigned row = row_off((unsigned)(min(m4, M - 1) + ep.row0), x);
+            const int i0 = x + 4;
+            const bool in = m4 < M;
+            const unsigned o0 = in ? row + (unsigned)(i0 >> 2) * 128 * ES : DROP;
+            const unsigned o1 = in && i0 >= X ? row + (unsigned)((i0 - X) >> 2) * 128 * ES
+                                              : (in && i0 + X < xp ? row + (unsigned)((i0 + X) >> 2) * 128 * ES : DROP);
+            const unsigned o2 = in && i0 >= X && i0 + X < xp ? row + (unsigned)((i0 + X) >> 2) * 128 * ES : DROP;
+            const bool wrap = __builtin_amdgcn_ballot_w64(o1 != DROP) != 0;
+            const bool wrap2 = __builtin_amdgcn_ballot_w64(o2 != DROP) != 0;
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                const int f = f0 + 16 * j + r16;
-                const size_t row = v_blocked_offset(ep.vB, ep.vZ, ep.vY, xp, f >> 5, (int)b, (int)z, (int)y, 0, f & 31);
-                const int i0 = (int)x + 4;
+                const RowSpan head(vbase + (j >> 1) * plane, DROP);
+                const __amdgpu_buffer_rsrc_t rs = head.at((j & 1) * 64 * ES);      // from channel 16 (j & 1) of the head
                 float e[4];
 #pragma unroll
                 for (int k = 0; k < 4; ++k) e[k] = fmaf(acc[j][i][k], dq, bv[j]);
                 if constexpr (FP8) {
-                    unsigned char *vt = (unsigned char *)ep.vt + row;
                     const unsigned u = e4m3x4(e[0] * om, e[1] * om, e[2] * om, e[3] * om);
-                    *(unsigned *)(vt + (size_t)(i0 >> 2) * 128) = u;
-                    if (i0 - X >= 0) *(unsigned *)(vt + (size_t)((i0 - X) >> 2) * 128) = u;
-                    if (i0 + X < xp) *(unsigned *)(vt + (size_t)((i0 + X) >> 2) * 128) = u;
+                    __builtin_amdgcn_raw_buffer_store_b32(u, rs, o0, 0, 0);
+                    if (wrap) __builtin_amdgcn_raw_buffer_store_b32(u, rs, o1, 0, 0);
+                    if (wrap2) __builtin_amdgcn_raw_buffer_store_b32(u, rs, o2, 0, 0);
                 } else {
-                    bf16 *vt = (bf16 *)ep.vt + row;
-                    uint2 u;
-                    u.x = pack_bf16x2(e[0], e[1]);
-                    u.y = pack_bf16x2(e[2], e[3]);
-                    *(uint2 *)(vt + (size_t)(i0 >> 2) * 128) = u;
-                    if (i0 - X >= 0) *(uint2 *)(vt + (size_t)((i0 - X) >> 2) * 128) = u;
-                    if (i0 + X < xp) *(uint2 *)(vt + (size_t)((i0 + X) >> 2) * 128) = u;
+                    const u32x2 u = pack4_bf16(e);
+                    __builtin_amdgcn_raw_buffer_store_b64(u, rs, o0, 0, 0);
+                    if (wrap) __builtin_amdgcn_raw_buffer_store_b64(u, rs, o1, 0, 0);
+                    if (wrap2) __builtin_amdgcn_raw_buffer_store_b64(u, rs, o2, 0, 0);
                 }
             }
-        } else {
+        }
+        return;
+    }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (m4 + e >= M) break;
-                const unsigned mg = (unsigned)(m4 + e + ep.row0);
-                const unsigned b = udiv(mg, ep.dT), tt = mg - b * (unsigned)ep.T;
-                const unsigned z = udiv(tt, ep.dYX), rr = tt - z * (unsigned)YX;
-                const unsigned y = udiv(rr, ep.dX), x = rr - y * (unsigned)X;
-                const int i0 = (int)x + 4;
+    for (int i = 0; i < TM; ++i) {
+        const int m4 = r0 + 16 * i + 4 * g;
 #pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    const int f = f0 + 16 * j + r16;
-                    const float val = fmaf(acc[j][i][e], dq, bv[j]);
-                    const size_t row = v_blocked_offset(ep.vB, ep.vZ, ep.vY, xp, f >> 5, (int)b, (int)z, (int)y, 0, f & 31);
-                    const size_t o0 = (size_t)(i0 >> 2) * 128 + (i0 & 3);
-                    const size_t o1 = (size_t)((i0 - X) >> 2) * 128 + ((i0 - X) & 3);
-                    const size_t o2 = (size_t)((i0 + X) >> 2) * 128 + ((i0 + X) & 3);
-                    if constexpr (FP8) {
-                        unsigned char *vt = (unsigned char *)ep.vt + row;
-                        const unsigned char c = (unsigned char)(e4m3x4(val * om, 0.f, 0.f, 0.f) & 0xffu);
-                        vt[o0] = c;
-                        if (i0 - X >= 0) vt[o1] = c;
-                        if (i0 + X < xp) vt[o2] = c;
-                    } else {
-                        bf16 *vt = (bf16 *)ep.vt + row;
-                        const bf16 c = (bf16)val;
-                        vt[o0] = c;
-                        if (i0 - X >= 0) vt[o1] = c;
-                        if (i0 + X < xp) vt[o2] = c;
-                    }
-                }
+        for (int e = 0; e < 4; ++e) {
+            if (m4 + e >= M) break;
+            int x;
+            const unsigned row = row_off((unsigned)(m4 + e + ep.row0), x);
+            const int i0 = x + 4;
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const float val = fmaf(acc[j][i][e], dq, bv[j]);
+                unsigned char *vt = const_cast<unsigned char *>(vbase) + (j >> 1) * plane + row + (j & 1) * 64 * ES;
+                auto put = [&](int p) {
+                    const size_t o = ((size_t)(p >> 2) * 128 + (p & 3)) * ES;
+                    if constexpr (FP8) vt[o] = (unsigned char)(e4m3x4(val * om, 0.f, 0.f, 0.f) & 0xffu);
+                    else *(bf16 *)(vt + o) = (bf16)val;
+                };
+                put(i0);
+                if (i0 - X >= 0) put(i0 - X);
+                if (i0 + X < xp) put(i0 + X);
             }
         }
     }
@@ -329,6 +271,65 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Residual update of a wave's tiles: rows r0 + 16 i + r16, features
+// n + 16 j + 4 g .. +3 of the float32 rows += acc * dq + bias; use(j, i, v)
+// receives the updated values.  Two feature tiles at a time; with AHEAD the
+// next pair's rows and bias are loaded before this pair's stores (a wait for a
+// load also waits for the stores issued before it).  The wave's rows lie in
+// one buffer, or in one state's; SPLIT: they may straddle states.
+template <int TM, int TN, bool AHEAD, bool SPLIT, typename F>
+__device__ __forceinline__ void resid_update(const EpiArgs &ep, int M, int N, int r0, int n, int g, int r16, float dq,
+                                             const f32x4 (&acc)[TN][TM], F use) {
+    const int rows = min(max(M - r0, 0), 16 * TM);
+    RowSpan span(nullptr, 0);
+    unsigned off[TM];
+    float *xr[TM];
+    if constexpr (SPLIT) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+            xr[i] = state_row(ep.resid, ep.resid_ptrs, (unsigned)ep.T, ep.dT, (unsigned)(min(r0 + 16 * i + r16, M - 1) + ep.row0), N) +
+                    n + 4 * g;
+    } else {
+        const unsigned mg = (unsigned)__builtin_amdgcn_readfirstlane(min(r0, M - 1) + ep.row0);
+        span = RowSpan(state_row(ep.resid, ep.resid_ptrs, (unsigned)ep.T, ep.dT, mg, N) + n, rows ? (unsigned)(rows * N - n) * 4u : 0u);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) off[i] = (unsigned)((16 * i + r16) * N + 4 * g) * 4u;
+    }
+    f32x4 rz[1 + AHEAD][TM][2], bz[1 + AHEAD][2];
+    auto load = [&](int j) {
+        const int s = AHEAD ? (j >> 1) & 1 : 0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            bz[s][h] = *(const f32x4 *)(ep.bias + n + 16 * (j + h) + 4 * g);
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                if constexpr (SPLIT) rz[s][i][h] = *(const f32x4 *)(xr[i] + 16 * (j + h));
+                else rz[s][i][h] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(span.at(64 * (j + h)), off[i], 0, 0));
+            }
+        }
+    };
+    if (AHEAD) load(0);
+#pragma unroll
+    for (int j = 0; j < TN; j += 2) {
+        if (!AHEAD) load(j);
+        else if (j + 2 < TN) load(j + 2);
+        const int s = AHEAD ? (j >> 1) & 1 : 0;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                f32x4 v;
+                // explicit FMAs: the rounding of every element must not
+                // depend on how the compiler contracts each unrolled copy
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c] = rz[s][i][h][c] + fmaf(acc[j + h][i][c], dq, bz[s][h][c]);
+                if constexpr (!SPLIT) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), span.at(64 * (j + h)), off[i], 0, 0);
+                else if (r0 + 16 * i + r16 < M) *(f32x4 *)(xr[i] + 16 * (j + h)) = v;
+                use(j + h, i, v);
+            }
+    }
 }
 
 // Epilogue of EPI_RESID_LN (LayerNorm fused into the residual update, WM3
@@ -348,7 +349,7 @@ __device__ __forceinline__ void lds_barrier() {
 // stored a pair of feature tiles at a time, as in the EPI_RESID epilogue:
 // holding them to the end spills registers).
 // `red` (LDS, 2 WGN BM + 2 N floats): row sums, then ln_g and ln_b.
-template <int TM, int TN, int WGN, int BM, bool FP8>
+template <int TM, int TN, int WGN, int BM, bool FP8, bool SPLIT>
 __device__ __forceinline__ void resid_ln_epilogue(const EpiArgs &ep, int M, int N, int mt, int row0w, int wn, int ncol,
                                                   int g, int r16, int tid, int nth, f32x4 (&acc)[TN][TM], float *red) {
     const float dq = FP8 ? ep.a_dequant * ep.w_dequant : 1.0f;
@@ -360,41 +361,13 @@ __device__ __forceinline__ void resid_ln_epilogue(const EpiArgs &ep, int M, int 
         lg[u] = c < N ? ep.ln_g[c] : 0.f;
         lb[u] = c < N ? ep.ln_b[c] : 0.f;
     }
-    float *xr[TM];
     float s[TM];
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const int m = min(mt + row0w + 16 * i + r16, M - 1);
-        xr[i] = state_row(ep.resid, ep.resid_ptrs, (unsigned)ep.T, ep.dT, (unsigned)(m + ep.row0), N);
-        s[i] = 0.f;
-    }
-    // residual update, a pair of feature tiles at a time
-#pragma unroll
-    for (int j = 0; j < TN; j += 2) {
-        const int n = ncol + 16 * j + 4 * g;
-        const float4 b0 = *(const float4 *)(ep.bias + n), b1 = *(const float4 *)(ep.bias + n + 16);
-        float4 rz[TM][2];
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            rz[i][0] = *(const float4 *)(xr[i] + n);
-            rz[i][1] = *(const float4 *)(xr[i] + n + 16);
-        }
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const float4 b = h ? b1 : b0, r = rz[i][h];
-                f32x4 &a = acc[j + h][i];
-                // explicit FMAs, as in epilogue4
-                a[0] = r.x + fmaf(a[0], dq, b.x);
-                a[1] = r.y + fmaf(a[1], dq, b.y);
-                a[2] = r.z + fmaf(a[2], dq, b.z);
-                a[3] = r.w + fmaf(a[3], dq, b.w);
-                if (mt + row0w + 16 * i + r16 < M) *(float4 *)(xr[i] + n + 16 * h) = make_float4(a[0], a[1], a[2], a[3]);
-                s[i] += (a[0] + a[1]) + (a[2] + a[3]);
-            }
-        }
-    }
+    for (int i = 0; i < TM; ++i) s[i] = 0.f;
+    resid_update<TM, TN, !SPLIT, SPLIT>(ep, M, N, mt + row0w, ncol, g, r16, dq, acc, [&](int j, int i, f32x4 v) {
+        acc[j][i] = v;
+        s[i] += (v[0] + v[1]) + (v[2] + v[3]);
+    });
     // row sums across the lanes g and the waves: red[w][row], then
     // red[WGN + w][row]; ln_g and ln_b at red + 2 WGN BM
     const float invN = 1.0f / (float)N;
@@ -442,30 +415,145 @@ __device__ __forceinline__ void resid_ln_epilogue(const EpiArgs &ep, int M, int 
     }
     // normalized rows: bf16, or e4m3 codes at the static scale *ln_amax / 448
     const float inv = FP8 ? (*ep.ln_amax > 0.f ? 448.0f / *ep.ln_amax : 1.0f) : 1.0f;
+    constexpr unsigned ES = FP8 ? 1 : 2;
+    const int r0 = mt + row0w, rows = min(max(M - r0, 0), 16 * TM);
+    const RowSpan span((const unsigned char *)ep.ln_out + ((size_t)(r0 + ep.row0) * N + ncol) * ES,
+                       rows ? (unsigned)(rows * N - ncol) * ES : 0u);
+    unsigned off[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) off[i] = (unsigned)((16 * i + r16) * N + 4 * g) * ES;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
         const int n = ncol + 16 * j + 4 * g;
         const float4 gm = *(const float4 *)(lgb + n), bt = *(const float4 *)(lgb + N + n);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            const int m = mt + row0w + 16 * i + r16;
-            if (m >= M) continue;
             const f32x4 a = acc[j][i];
             // explicit FMAs, as in the LayerNorm kernel
-            const float y0 = fmaf((a[0] - mean[i]) * rstd[i], gm.x, bt.x) * inv;
-            const float y1 = fmaf((a[1] - mean[i]) * rstd[i], gm.y, bt.y) * inv;
-            const float y2 = fmaf((a[2] - mean[i]) * rstd[i], gm.z, bt.z) * inv;
-            const float y3 = fmaf((a[3] - mean[i]) * rstd[i], gm.w, bt.w) * inv;
-            const size_t o = (size_t)(m + ep.row0) * N + n;
-            if constexpr (FP8) {
-                *(unsigned *)((unsigned char *)ep.ln_out + o) = e4m3x4(y0, y1, y2, y3);
-            } else {
-                uint2 u;
-                u.x = pack_bf16x2(y0, y1);
-                u.y = pack_bf16x2(y2, y3);
-                *(uint2 *)((bf16 *)ep.ln_out + o) = u;
+            float y[4];
+            y[0] = fmaf((a[0] - mean[i]) * rstd[i], gm.x, bt.x) * inv;
+            y[1] = fmaf((a[1] - mean[i]) * rstd[i], gm.y, bt.y) * inv;
+            y[2] = fmaf((a[2] - mean[i]) * rstd[i], gm.z, bt.z) * inv;
+            y[3] = fmaf((a[3] - mean[i]) * rstd[i], gm.w, bt.w) * inv;
+            if constexpr (FP8) __builtin_amdgcn_raw_buffer_store_b32(e4m3x4(y[0], y[1], y[2], y[3]), span.at(16 * j * ES), off[i], 0, 0);
+            else __builtin_amdgcn_raw_buffer_store_b64(pack4_bf16(y), span.at(16 * j * ES), off[i], 0, 0);
+        }
+    }
+}
+
+// Epilogue of a wave's TM x TN tiles of every kind but EPI_RESID_LN and the
+// swapped V tiles: rows r0 + 16 i + r16 (of the chunk), features
+// n0 + ncol + 16 j + .. (n0: first feature of the workgroup's tile).  PERM
+// (permuted W rows, EpiArgs.perm): the pair of tiles j, j + 1 covers features
+// 16 j + 8 g .. +7 of each lane, stored at once (16 bytes of bf16, or 8 e4m3
+// codes in the FP8 kernels, whose permuted outputs are codes); else tile j
+// covers 16 j + 4 g .. +3.  The bias is loaded before the first store (on
+// gfx9 a wait for a load also waits for every store issued before it).
+// `pre_store` runs once before the first store.  All arithmetic is explicit
+// FMAs: the rounding of an element must not depend on how the compiler
+// contracts each unrolled copy (a token's result must not depend on its
+// position in the tile, i.e. on the batch).
+template <int EPI, bool FP8, bool PERM, int TM, int TN, typename F>
+__device__ __forceinline__ void tile_epilogue(const EpiArgs &ep, int M, int N, int r0, int n0, int ncol, int g, int r16,
+                                              const f32x4 (&acc)[TN][TM], F pre_store) {
+    const float dq = FP8 ? ep.a_dequant * ep.w_dequant : 1.0f;
+    if constexpr (epi_resid(EPI)) {
+        pre_store();
+        resid_update<TM, TN, EPI == EPI_RESID, EPI == EPI_RESID_SPLIT>(ep, M, N, r0, n0 + ncol, g, r16, dq, acc, [](int, int, f32x4) {});
+        return;
+    } else {
+    constexpr bool OUT8 = FP8 && PERM;
+    constexpr unsigned ES = OUT8 ? 1 : 2;
+    constexpr int NP = PERM ? 8 : 4;          // consecutive features per lane
+    // a feature tile never straddles Q/K/V (C is a multiple of BN)
+    const int part = epi_qkv(EPI) ? ep.part0 + n0 / ep.C : 0;
+    const int rows = min(max(M - r0, 0), 16 * TM);
+    const int rs_len = epi_qkv(EPI) ? 32 : N;              // elements per row of the output
+    float om = 1.0f;
+    if constexpr (epi_qkv(EPI)) om = (part == 0 ? ep.qscale : 1.0f) * (OUT8 ? ep.out_mul[part] : 1.0f);
+    else if constexpr (OUT8) om = ep.out_mul[0];
+    // the wave's first row, and (QKV) its first head's plane in [3][H][M][32]
+    const unsigned char *base = (const unsigned char *)ep.out;
+    size_t pair = 32 * ES;                                 // bytes from a pair of feature tiles to the next
+    unsigned bytes;
+    if constexpr (epi_qkv(EPI)) {
+        const int hc = n0 + ncol - (part - ep.part0) * ep.C;
+        base += (((size_t)part * ep.H + (hc >> 5)) * ep.Mtot + r0 + ep.row0) * 32 * ES;
+        pair = (size_t)ep.Mtot * 32 * ES;
+        bytes = (unsigned)(rows * 32) * ES;
+    } else {
+        base += ((size_t)(r0 + ep.row0) * N + n0 + ncol) * ES;
+        bytes = rows ? (unsigned)(rows * N - n0 - ncol) * ES : 0u;
+    }
+    unsigned off[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) off[i] = (unsigned)((16 * i + r16) * rs_len + NP * g) * ES;
+    // rotary (cos, sin) of each row's channel pairs 4g .. 4g+3 (the same
+    // pairs in every head this lane stores), loaded once per tile
+    float2 rc[TM][4];
+    if constexpr (EPI == EPI_QKV_ROPE) {
+        if (part < 2) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                const long mg = (long)min(r0 + 16 * i + r16, M - 1) + ep.row0;
+                const unsigned tt = (unsigned)(mg % ep.T);
+                const unsigned yx = (unsigned)(ep.rY * ep.rX);
+                const int z = (int)(tt / yx), y = (int)((tt / (unsigned)ep.rX) % (unsigned)ep.rY),
+                          x = (int)(tt % (unsigned)ep.rX);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int pr = 4 * g + q;
+                    const int row = pr < 4 ? z : (pr < 10 ? ep.rZ + y : ep.rZ + ep.rY + x);
+                    rc[i][q] = *(const float2 *)(ep.rope + 2 * (row * 16 + pr));
+                }
             }
         }
+    }
+    f32x4 bz[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+        bz[j] = *(const f32x4 *)(ep.bias + n0 + ncol + 16 * (j & ~1) + (PERM ? 8 * g + 4 * (j & 1) : 4 * g + 16 * (j & 1)));
+    pre_store();
+#pragma unroll
+    for (int j = 0; j < TN; j += 2) {
+        const RowSpan span(base + (epi_qkv(EPI) ? (j >> 1) * pair : 0), bytes);
+        const __amdgpu_buffer_rsrc_t rs = span.at(epi_qkv(EPI) ? 0 : 16 * j * ES);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            float v[8];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                v[c] = fmaf(acc[j][i][c], dq, bz[j][c]);
+                v[4 + c] = fmaf(acc[j + 1][i][c], dq, bz[j + 1][c]);
+            }
+            if constexpr (EPI == EPI_QKV_ROPE) {
+                if (part < 2) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float a0 = v[2 * q], a1 = v[2 * q + 1];
+                        v[2 * q] = fmaf(a0, rc[i][q].x, -(a1 * rc[i][q].y));
+                        v[2 * q + 1] = fmaf(a0, rc[i][q].y, a1 * rc[i][q].x);
+                    }
+                }
+            }
+            if constexpr (EPI == EPI_GELU) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c) v[c] = gelu_as4(v[c]);
+            }
+            if constexpr (epi_qkv(EPI) || OUT8) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c) v[c] *= om;
+            }
+            if constexpr (OUT8)
+                __builtin_amdgcn_raw_buffer_store_b64(u32x2{e4m3x4(v[0], v[1], v[2], v[3]), e4m3x4(v[4], v[5], v[6], v[7])}, rs, off[i], 0, 0);
+            else if constexpr (PERM)
+                __builtin_amdgcn_raw_buffer_store_b128(pack8_bf16(v), rs, off[i], 0, 0);
+            else {
+                __builtin_amdgcn_raw_buffer_store_b64(pack4_bf16(v), rs, off[i], 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b64(pack4_bf16(v + 4), span.at((epi_qkv(EPI) ? 0 : 16 * j * ES) + 32), off[i], 0, 0);
+            }
+        }
+    }
     }
 }
 
@@ -474,7 +562,7 @@ __device__ __forceinline__ void resid_ln_epilogue(const EpiArgs &ep, int M, int 
 // WGM x WGN waves tile the BM x BN output; OCC workgroups share a CU.
 // The activation and weight tiles of each K stage stream through two rings
 // of D slots each, D - 1 stages ahead of the MFMAs.
-template <int BM, int BN, int BKB, int D, int WGM, int WGN, int OCC, int EPI, bool FP8>
+template <int BM, int BN, int BKB, int D, int WGM, int WGN, int OCC, int EPI, bool FP8, bool PERM>
 __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const void *__restrict__ A, const void *__restrict__ W,
                                                          int M, int N, int K, EpiArgs ep, int tpw, int rw) {
 #if defined(__HIP_DEVICE_COMPILE__)   // LDS-address-space builtins exist only in the device pass
@@ -486,7 +574,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
     constexpr int RPI = 64 / CPR;                  // rows one load instruction fills
     constexpr int LPA = BM / RPI / NW;             // activation load instructions per wave per stage
     constexpr int LPB = BN / RPI / NW;             // weight load instructions per wave per stage
-    static_assert(BKB == 128 || BKB == 64, "stage row bytes");
+    static_assert(BKB == 128, "stage row bytes");
     static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "rows per stage must split over the waves");
     static_assert(WM % 16 == 0 && WN % 16 == 0, "wave tile");
     static_assert(D >= 2 && D <= 5, "ring depth");
@@ -511,7 +599,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
     const unsigned astep = rw ? (unsigned)BM * (unsigned)K * (FP8 ? 1u : 2u) : 0u;
     const unsigned wstep = rw ? 0u : (unsigned)BN * (unsigned)K * (FP8 ? 1u : 2u);
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WGM, wn = wave / WGM;
     const int g = lane >> 4, r16 = lane & 15;
     const unsigned Kb = (unsigned)K * (FP8 ? 1 : 2);
@@ -524,12 +613,12 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
 #pragma unroll
     for (int i = 0; i < LPA; ++i) {
         const int row = RPI * (wave + NW * i) + lane / CPR;
-        voa[i] = (unsigned)(m0 + row) * Kb + (((lane % CPR) ^ swz<BKB>(row)) << 4);
+        voa[i] = (unsigned)(m0 + row) * Kb + (((lane % CPR) ^ swz<FP8>(row)) << 4);
     }
 #pragma unroll
     for (int i = 0; i < LPB; ++i) {
         const int row = RPI * (wave + NW * i) + lane / CPR;
-        vob[i] = (unsigned)(tn0 * BN + row) * Kb + (((lane % CPR) ^ swz<BKB>(row)) << 4);
+        vob[i] = (unsigned)(tn0 * BN + row) * Kb + (((lane % CPR) ^ swz<FP8>(row)) << 4);
     }
     const int nk = K / (FP8 ? BKB : BKB / 2);
     // stage s of the stream = k-stage (s % nk) of tile (s / nk)
@@ -554,7 +643,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
                                                      vob[i], wsoff, 0, 0);
     };
 
-    constexpr bool ZSTART = !FP8 && EPI != EPI_QKV_ROPE && EPI != EPI_RESID_LN;
+    constexpr bool ZSTART = !FP8 && EPI != EPI_QKV_ROPE;
 
     // lane-constant fragment offsets inside a stage (swizzle depends on r16
     // only): bf16 k-step ks reads 16 bytes at k = 32ks + 8g; fp8 k-step ks
@@ -567,8 +656,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
     int aoff[NOFF], woff[NOFF];
 #pragma unroll
     for (int o = 0; o < NOFF; ++o) {
-        const int pc = FP8 ? (((8 * (o >> 1) + 2 * g + (o & 1)) ^ swz<BKB>(r16)) << 4)
-                           : (((4 * o + g) ^ swz<BKB>(r16)) << 4);
+        const int pc = FP8 ? (((8 * (o >> 1) + 2 * g + (o & 1)) ^ swz<FP8>(r16)) << 4)
+                           : (((4 * o + g) ^ swz<FP8>(r16)) << 4);
         aoff[o] = (wm * WM + r16) * BKB + pc;
         woff[o] = (wn * WN + r16) * BKB + pc;
     }
@@ -612,30 +701,15 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
             const unsigned char *sbA = aring + (st % D) * ABYTES, *sbW = wring + (st % D) * WBYTES;
             // ZSTART: a tile's first k-step starts its accumulators from an
             // inline zero operand instead of registers cleared in the previous
-            // epilogue (not for the FP8, rotary and LayerNorm variants, whose
+            // epilogue (not for the FP8 and rotary variants, whose
             // extra registers would spill with a second copy of the stage code)
             if (ZSTART && kt == 0) mma_stage<ZSTART, FP8, TM, TN, KSTEPS, BKB, SWAP>(sbA, sbW, aoff, woff, acc);
             else mma_stage<false, FP8, TM, TN, KSTEPS, BKB, SWAP>(sbA, sbW, aoff, woff, acc);
         }
         const int n0 = (rw ? tn0 : tn0 + t) * BN;
         const int mt = rw ? m0 + t * BM : m0;    // first row of this tile
-        if constexpr (EPI == EPI_RESID_LN) {
-            // the launcher checks N == BN; the partial sums go to the
-            // activation slot of the tile's last stage, which no load is
-            // filling (the next tile's first stage went to the other slot)
-            static_assert((2 * WGN * BM + 2 * BN) * 4 <= ABYTES && BN <= 2 * NW * 64, "row sums and ln_g, ln_b fit a stage slot");
-            resid_ln_epilogue<TM, TN, WGN, BM, FP8>(ep, M, N, mt, wm * WM, wn, wn * WN, g, r16, tid, NW * 64, acc,
-                                                    (float *)(aring + (((t + 1) * nk - 1) % D) * ABYTES));
-            if constexpr (!ZSTART) {
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-#pragma unroll
-                    for (int i = 0; i < TM; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-            continue;
-        }
         if constexpr (SWAP) {
-            vt_epilogue<TM, TN, FP8>(ep, ep.bias + 2 * ep.C, M, mt + wm * WM, n0 - 2 * ep.C + wn * WN, acc, g, r16);
+            vt_epilogue<TM, TN, FP8>(ep, ep.bias + 2 * ep.C, M, mt + wm * WM, n0 - 2 * ep.C + wn * WN, acc, g, r16, [] {});
             if constexpr (!ZSTART) {
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
@@ -644,126 +718,257 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
             }
             continue;
         }
-        // a feature tile never straddles Q/K/V (C is a multiple of BN)
-        const int part = epi_qkv(EPI) ? ep.part0 + n0 / ep.C : 0;
-        const size_t qkv_base = (size_t)part * ep.H * ep.Mtot * 32;
-        const float qs = (part == 0 ? ep.qscale : 1.0f) * (epi_qkv(EPI) && ep.out8 ? ep.out_mul[part] : 1.0f);
-        // per-row dequantization (fp8) and per-state amax of the outputs
-        float dq[TM];
-        int srow[TM];
+        tile_epilogue<EPI, FP8, PERM, TM, TN>(ep, M, N, mt + wm * WM, n0, wn * WN, g, r16, acc, [] {});
+        if constexpr (!ZSTART) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const long mg = (long)min(mt + wm * WM + 16 * i + r16, M - 1) + ep.row0;
-            srow[i] = FP8 || ep.out_amax ? (int)(mg / ep.T) : 0;
-            dq[i] = FP8 ? (ep.a_amax ? ep.a_amax[srow[i]] * (1.0f / 448.0f) : ep.a_dequant) * ep.w_dequant : 1.0f;
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int i = 0; i < TM; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
-        const int s_lo = ep.out_amax ? (int)(((long)min(mt, M - 1) + ep.row0) / ep.T) : 0;
-        // rotary (cos, sin) of each row's channel pairs 4g .. 4g+3 (the same
-        // pairs in every head this lane stores), loaded once per tile
-        float2 rc[TM][4];
-        if constexpr (EPI == EPI_QKV_ROPE) {
-            if (ep.perm && part < 2) {
+    }
+    };
+    if constexpr (epi_qkv(EPI)) {
+        if (ep.vt && tn0 * BN >= 2 * ep.C) {
+            body(std::true_type{});
+            return;
+        }
+    }
+    body(std::false_type{});
+#endif
+}
+
+// ---------------------------------------------------------------------------
+// Ping-pong kernel: the main loop of the wide tiles.  8 waves, wave tile
+// 64 x 128 (TM = 4, TN = 8), two per SIMD: waves 0-3 (group 0) and 4-7
+// (group 1).  A K stage (128 bytes per row) is two phases; in each a wave
+// first reads fragments from LDS and issues loads (memory part), then runs
+// 32 bf16 (or 16 f8f6f4) MFMAs on registers (matrix part), with a workgroup
+// barrier after each part.  Group 1 runs one part behind group 0, so on every
+// SIMD one wave's MFMAs cover the other wave's LDS reads.
+//
+// An LDS slot holds one stage in three sub-tiles that are read, and refilled,
+// one after the other: A, W03 and W47 (feature tiles 0..3 and 4..7 of every
+// wave).  Stage st:
+//   phase 0: reads A(st), W03(st)   A x W03   loads W47(st + 1)
+//   phase 1: reads W47(st)          A x W47   loads A(st + 2), W03(st + 2)
+// so the sub-tiles read in one phase are free (both groups are past it) in
+// the next, where the loads that refill them are issued: those have five to
+// six parts (about 2800 MFMA cycles) to land.  A wave waits, one barrier ahead
+// of group 0's read, until at most the loads issued after those it needs are
+// outstanding (loads return in order).
+// Every accumulator sees its k-steps in the order of gemm_lds_kernel, so the
+// two kernels agree bit for bit.
+template <int BM, int BN, int EPI, bool FP8, bool PERM>
+__global__ __launch_bounds__(512, 1) void gemm_pp_kernel(const void *__restrict__ A, const void *__restrict__ W,
+                                                         int M, int N, int K, EpiArgs ep, int tpw, int rw) {
+#if defined(__HIP_DEVICE_COMPILE__)   // LDS-address-space builtins exist only in the device pass
+    constexpr int TM = 4, TN = 8, BKB = 128;
+    constexpr int WGM = BM / 64, WGN = BN / 128;
+    static_assert(WGM * WGN == 8, "8 waves of 64 x 128");
+    constexpr int AB = BM * BKB, WH = BN / 2 * BKB;          // bytes of sub-tile A, and of W03 or W47
+    constexpr int SLOT = AB + 2 * WH;
+    constexpr int LA = BM / 64, LW = BN / 2 / 64;            // load instructions (8 rows) per wave and sub-tile
+    extern __shared__ __align__(16) unsigned char smem[];
+
+    const int ntn = N / BN, ntm = (M + BM - 1) / BM;
+    const int ngrp = rw ? (ntm + tpw - 1) / tpw : (ntn + tpw - 1) / tpw;
+    const int total = rw ? ngrp * ntn : ngrp * ntm;
+    const int per = (total + 7) >> 3;
+    const int L = blockIdx.x;
+    const int id = (L & 7) * per + (L >> 3);
+    if (id >= total) return;
+    const int m0 = rw ? (id / ntn) * tpw * BM : (id / ngrp) * BM;
+    const int tn0 = rw ? id % ntn : (id % ngrp) * tpw;
+    // (EPI_RESID_LN: one, see the launcher)
+    const int nn = epi_resid_ln(EPI) ? 1 : (rw ? min(tpw, ntm - m0 / BM) : min(tpw, ntn - tn0));
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int grp = wave >> 2;
+    const int wm = wave % WGM, wn = wave / WGM;
+    const int g = lane >> 4, r16 = lane & 15;
+    const unsigned Kb = (unsigned)K * (FP8 ? 1 : 2);
+    const unsigned astep = rw ? (unsigned)BM * Kb : 0u, wstep = rw ? 0u : (unsigned)BN * Kb;
+    const __amdgpu_buffer_rsrc_t ars = make_rsrc(A, (unsigned)M * Kb);
+    const __amdgpu_buffer_rsrc_t wrs = make_rsrc(W, (unsigned)N * Kb);
+
+    // load instruction u of this wave fills sub-tile rows 8 (wave + 8 u) ..;
+    // sub-tile row r of W03 is tile row 128 (r / 64) + r % 64 (W47: + 64)
+    unsigned voa[LA], vow[LW];
+    const int lrow = lane >> 3;
+#pragma unroll
+    for (int u = 0; u < LA; ++u) {
+        const int r = 8 * (wave + 8 * u) + lrow;
+        voa[u] = (unsigned)(m0 + r) * Kb + (((lane & 7) ^ swz<FP8>(r)) << 4);
+    }
+#pragma unroll
+    for (int u = 0; u < LW; ++u) {
+        const int r = 8 * (wave + 8 * u) + lrow;
+        vow[u] = (unsigned)(tn0 * BN + ((r >> 6) << 7) + (r & 63)) * Kb + (((lane & 7) ^ swz<FP8>(r)) << 4);
+    }
+    const int nk = (int)(Kb / BKB);
+    const int S = nn * nk;
+    // the next stage of A and W03 (cursor 0) and of W47 (cursor 1): its slot
+    // and the byte offsets of its tile and k
+    int lkt[2] = {0, 0}, ls[2] = {0, 0};
+    unsigned lk[2] = {0, 0}, lslot[2] = {0, 0}, la = 0, lw[2] = {0, 0};
+    auto advance = [&](int c) {
+        ++ls[c];
+        lslot[c] ^= SLOT;
+        lk[c] += BKB;
+        if (++lkt[c] == nk) {
+            lkt[c] = 0;
+            lk[c] = 0;
+            lw[c] += wstep;
+            if (c == 0) la += astep;
+        }
+    };
+    auto load_w = [&](int h) {      // W03 (h = 0) or W47
+#pragma unroll
+        for (int u = 0; u < LW; ++u)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lds_void *)(smem + lslot[h] + AB + h * WH + 1024 * (wave + 8 * u)),
+                                                     16, vow[u], lw[h] + lk[h] + (h ? 64u * Kb : 0u), 0, 0);
+    };
+    auto load_aw = [&]() {          // A and W03 (A's row advance in the vector offset: rows past M must read zero)
+#pragma unroll
+        for (int u = 0; u < LA; ++u)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ars, (lds_void *)(smem + lslot[0] + 1024 * (wave + 8 * u)), 16,
+                                                     voa[u] + la, lk[0], 0, 0);
+        load_w(0);
+        advance(0);
+    };
+
+    // fragment chunks of a row: bf16 k-step o reads chunk 4 o + g, e4m3 the
+    // chunks 2 g and 2 g + 1 of its one k-step
+    int aoff[2], woff[2];
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+        const int pc = (FP8 ? 2 * g + o : 4 * o + g) ^ swz<FP8>(r16);
+        aoff[o] = (wm * 64 + r16) * BKB + (pc << 4);
+        woff[o] = AB + (wn * 64 + r16) * BKB + (pc << 4);
+    }
+
+    load_aw();
+    load_w(1);
+    advance(1);
+    if (S > 1) load_aw();
+    // A and W03 of stage 0 have landed
+    if (S > 1) wait_vmcnt<LA + 2 * LW>();
+    else wait_vmcnt<LW>();
+    __builtin_amdgcn_s_barrier();
+
+    auto body = [&](auto swap_tag) {
+    constexpr bool SWAP = decltype(swap_tag)::value;
+    f32x4 acc[TN][TM];
+    // LDS is read as ext_vector values: before a read of a struct type (uint4)
+    // the compiler waits for every LDS load in flight
+    i32x4 a[TM][2], w[4][2];      // A and the current half of W: [tile][chunk]
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    auto read_a = [&](const unsigned char *sl) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int o = 0; o < 2; ++o) a[i][o] = *(const i32x4 *)(sl + aoff[o] + 16 * i * BKB);
+    };
+    auto read_w = [&](const unsigned char *sl) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int o = 0; o < 2; ++o) w[j][o] = *(const i32x4 *)(sl + woff[o] + 16 * j * BKB);
+    };
+    // the matrix part: every row tile by feature tiles j0 .. j0 + 3
+    auto mma = [&](auto first_tag, int j0) {
+        constexpr bool FIRST = decltype(first_tag)::value;
+        __builtin_amdgcn_s_setprio(1);
+        if constexpr (FP8) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
 #pragma unroll
                 for (int i = 0; i < TM; ++i) {
-                    const long mg = (long)min(mt + wm * WM + 16 * i + r16, M - 1) + ep.row0;
-                    const unsigned tt = (unsigned)(mg % ep.T);
-                    const unsigned yx = (unsigned)(ep.rY * ep.rX);
-                    const int z = (int)(tt / yx), y = (int)((tt / (unsigned)ep.rX) % (unsigned)ep.rY),
-                              x = (int)(tt % (unsigned)ep.rX);
+                    const i32x8 af = __builtin_shufflevector(a[i][0], a[i][1], 0, 1, 2, 3, 4, 5, 6, 7);
+                    const i32x8 wf = __builtin_shufflevector(w[j][0], w[j][1], 0, 1, 2, 3, 4, 5, 6, 7);
+                    f32x4 &c = acc[j0 + j][i];
+                    c = SWAP ? __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(af, wf, FIRST ? zero : c, 0, 0, 0, 0, 0, 0)
+                             : __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(wf, af, FIRST ? zero : c, 0, 0, 0, 0, 0, 0);
+                }
+        } else {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int pr = 4 * g + q;
-                        const int row = pr < 4 ? z : (pr < 10 ? ep.rZ + y : ep.rZ + ep.rY + x);
-                        rc[i][q] = *(const float2 *)(ep.rope + 2 * (row * 16 + pr));
+            for (int o = 0; o < 2; ++o)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+                        const bf16x8 af = __builtin_bit_cast(bf16x8, a[i][o]), wf = __builtin_bit_cast(bf16x8, w[j][o]);
+                        f32x4 &c = acc[j0 + j][i];
+                        c = SWAP ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, wf, FIRST && o == 0 ? zero : c, 0, 0, 0)
+                                 : __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, af, FIRST && o == 0 ? zero : c, 0, 0, 0);
                     }
-                }
-            }
         }
-        // Bias of the features this lane stores.  On gfx9 a wait for a load
-        // also waits for every store issued before it, so a load between the
-        // stores puts a store round trip on the path: the bias is loaded
-        // before the first store (where registers allow) or once per column
-        // pair, together with that pair's residual rows.  Tile j covers
-        // features 16j + 4g .. (perm: pair j, j+1 covers 16j + 8g .. +7).
-        constexpr bool PRE_B = !FP8 && (EPI == EPI_QKV || EPI == EPI_GELU || EPI == EPI_STORE);
-        float4 bz[TN];
-        auto load_bias = [&](int j) {
-            bz[j] = *(const float4 *)(ep.bias + n0 + wn * WN + 16 * (j & ~1) +
-                                      (ep.perm ? 8 * g + 4 * (j & 1) : 4 * g + 16 * (j & 1)));
-        };
-        if constexpr (PRE_B) {
-#pragma unroll
-            for (int j = 0; j < TN; ++j) load_bias(j);
+        __builtin_amdgcn_s_setprio(0);
+    };
+    int st = 0;                  // global stage
+    unsigned slot = 0;
+    // wait for the sub-tiles of the phase after phase q of stage st
+    auto wait_next = [&](int q) {
+        if (st + 1 + q < S) wait_vmcnt<LA + 2 * LW>();
+        else if (q) wait_vmcnt<LW>();
+        else wait_vmcnt<0>();
+    };
+    // end of a part (skip: those sub-tiles have landed before the last epilogue)
+    auto end_mem = [&](int q, bool skip) {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xc07f);      // lgkmcnt(0)
+        if (grp == 1 && !skip) wait_next(q);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto end_mma = [&](int q, bool skip, bool last) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (grp == 0 && !skip) wait_next(q);
+        // (group 1 started the tile one barrier later and ends it without one)
+        if (!(last && grp == 1)) __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto stage = [&](auto first_tag, bool skip, bool last) {
+        const unsigned char *sl = smem + slot;
+        read_a(sl);
+        read_w(sl);                                  // W03
+        if (ls[1] < S) {
+            load_w(1);
+            advance(1);
         }
-        float mlo = 0.f, mhi = 0.f;
-#pragma unroll
-        for (int j = 0; j < TN; j += 2) {
-            if constexpr (!PRE_B) {
-                load_bias(j);
-                load_bias(j + 1);
-            }
-            // residual rows of this column pair, loaded RI row groups at a
-            // time (one wait per batch; FP8 keeps fewer in registers)
-            constexpr int RI = FP8 ? 2 : TM;
-            float4 rz[TM][2];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                if constexpr (EPI == EPI_RESID) {
-                    if (i % RI == 0) {
-#pragma unroll
-                        for (int ii = i; ii < i + RI; ++ii) {
-                            const int m = min(mt + wm * WM + 16 * ii + r16, M - 1);
-                            const float *r = state_row(ep.resid, ep.resid_ptrs, (unsigned)ep.T, ep.dT,
-                                                       (unsigned)(m + ep.row0), N) + n0 + wn * WN + 16 * j + 4 * g;
-                            rz[ii][0] = *(const float4 *)r;
-                            rz[ii][1] = *(const float4 *)(r + 16);
-                        }
-                    }
-                }
-                const int m = mt + wm * WM + 16 * i + r16;
-                const long mg = (long)m + ep.row0;
-                float a = 0.f;
-                if (m < M) {
-                    if (ep.perm) {
-                        const int n = n0 + wn * WN + 16 * j + 8 * g;
-                        a = epilogue8<EPI>(ep, N, mg, n, acc[j][i], acc[j + 1][i], qkv_base, n - (part - ep.part0) * ep.C, qs,
-                                           dq[i], rc[i], bz[j], bz[j + 1]);
-                    } else {
-                        const int n = n0 + wn * WN + 16 * j + 4 * g;
-                        float4 r0 = {}, r1 = {};
-                        if constexpr (EPI == EPI_RESID) {
-                            r0 = rz[i][0];
-                            r1 = rz[i][1];
-                        }
-                        a = fmaxf(epilogue4<EPI>(ep, N, mg, n, acc[j][i], qkv_base, n - (part - ep.part0) * ep.C, qs, dq[i],
-                                                 bz[j], r0),
-                                  epilogue4<EPI>(ep, N, mg, n + 16, acc[j + 1][i], qkv_base, n + 16 - (part - ep.part0) * ep.C,
-                                                 qs, dq[i], bz[j + 1], r1));
-                    }
-                }
-                if constexpr (!ZSTART) {
-                    acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-                    acc[j + 1][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-                }
-                if (ep.out_amax) {
-                    if (srow[i] == s_lo) mlo = fmaxf(mlo, a);
-                    else if (srow[i] == s_lo + 1) mhi = fmaxf(mhi, a);
-                    else if (m < M)
-                        atomicMax(ep.out_amax + (blockIdx.x % AMAX_SHARDS) * AMAX_STRIDE + srow[i] * ep.amax_stride + part,
-                                  __float_as_uint(a));
-                }
-            }
+        end_mem(0, skip);
+        mma(first_tag, 0);
+        end_mma(0, skip, false);
+        read_w(sl + WH);                             // W47
+        if (ls[0] < S) load_aw();
+        end_mem(1, skip);
+        mma(first_tag, 4);
+        end_mma(1, skip, last);
+        slot ^= SLOT;
+        ++st;
+    };
+    for (int t = 0; t < nn; ++t) {
+        if (grp == 1) __builtin_amdgcn_s_barrier();  // one part behind group 0
+        stage(std::true_type{}, t > 0, nk == 1);
+        for (int kt = 1; kt < nk; ++kt) stage(std::false_type{}, false, kt == nk - 1);
+        const int n0 = (rw ? tn0 : tn0 + t) * BN;
+        const int mt = rw ? m0 + t * BM : m0;        // first row of this tile
+        // The loads in flight belong to the next tile.  They are waited for
+        // before the first store, since a later wait for them would also wait
+        // for the stores; the first phases of the next tile then wait for none.
+        auto pre_store = [] { wait_vmcnt<0>(); };
+        if constexpr (epi_resid_ln(EPI)) {
+            // one tile per workgroup (the launcher): no load is in flight, and
+            // both groups are past their last LDS read
+            static_assert((2 * WGN * BM + 2 * BN) * 4 <= SLOT && BN <= 1024, "row sums and ln_g, ln_b fit a slot");
+            resid_ln_epilogue<TM, TN, WGN, BM, FP8, EPI == EPI_RESID_LN_SPLIT>(ep, M, N, mt, wm * 64, wn, wn * 128, g, r16, tid, 512, acc, (float *)smem);
+        } else if constexpr (SWAP) {
+            vt_epilogue<TM, TN, FP8>(ep, ep.bias + 2 * ep.C, M, mt + wm * 64, n0 - 2 * ep.C + wn * 128, acc, g, r16, pre_store);
+        } else {
+            tile_epilogue<EPI, FP8, PERM, TM, TN>(ep, M, N, mt + wm * 64, n0, wn * 128, g, r16, acc, pre_store);
         }
-        if (ep.out_amax) {
-            mlo = wave_max(mlo);
-            mhi = wave_max(mhi);
-            if (lane == 0) {
-                unsigned *sh = ep.out_amax + (blockIdx.x % AMAX_SHARDS) * AMAX_STRIDE;
-                atomicMax(sh + s_lo * ep.amax_stride + part, __float_as_uint(mlo));
-                if ((long)(s_lo + 1) * ep.T < (long)ep.Mtot)
-                    atomicMax(sh + (s_lo + 1) * ep.amax_stride + part, __float_as_uint(mhi));
-            }
-        }
+        if (t + 1 < nn) __builtin_amdgcn_s_barrier();    // every wave's loads for the next phases have landed
     }
     };
     if constexpr (epi_qkv(EPI)) {
@@ -781,52 +986,15 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
 // (measured); other N of 1536 or more take 2, smaller N take 1.
 inline int wide_tpw(int N) { return N == 1536 ? 3 : (N == 2048 ? 4 : (N >= 1536 ? 2 : 1)); }
 
-// RLN: the instantiation for EPI_RESID_LN alone (its tile spans N), which
-// takes no other epilogue.
-template <int BM, int BN, int BKB, int D, int WGM, int WGN, int OCC, bool FP8, bool RLN = false>
-hipError_t launch_cfg(const void *A, const void *W, int M, int N, int K, EpiKind epi, const EpiArgs &ep,
-                      hipStream_t stream, int tpw_default = 1, int rw_default = 0) {
-    constexpr size_t lds = (size_t)D * (BM + BN) * BKB;
-    static_assert(lds * OCC <= 160 * 1024, "LDS per CU");
-    constexpr int NTH = 64 * WGM * WGN;
-    if (RLN != (epi == EPI_RESID_LN) || (RLN && N != BN)) return hipErrorInvalidValue;
-    // LDS limit of the variants, set once per process (a local static's
-    // initialisation is thread-safe; the server thread launches too)
-    static const hipError_t attr_err = [] {
-        if constexpr (RLN) {
-            return hipFuncSetAttribute((const void *)gemm_lds_kernel<BM, BN, BKB, D, WGM, WGN, OCC, EPI_RESID_LN, FP8>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        } else {
-            const void *fns[5] = {(const void *)gemm_lds_kernel<BM, BN, BKB, D, WGM, WGN, OCC, EPI_QKV, FP8>,
-                                  (const void *)gemm_lds_kernel<BM, BN, BKB, D, WGM, WGN, OCC, EPI_QKV_ROPE, FP8>,
-                                  (const void *)gemm_lds_kernel<BM, BN, BKB, D, WGM, WGN, OCC, EPI_GELU, FP8>,
-                                  (const void *)gemm_lds_kernel<BM, BN, BKB, D, WGM, WGN, OCC, EPI_RESID, FP8>,
-                                  (const void *)gemm_lds_kernel<BM, BN, BKB, D, WGM, WGN, OCC, EPI_STORE, FP8>};
-            for (const void *f : fns) {
-                const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                if (e != hipSuccess) return e;
-            }
-            return hipSuccess;
-        }
-    }();
-    if (attr_err != hipSuccess) return attr_err;
+// Launches `kernel` for every row chunk: A is addressed with 32-bit byte
+// offsets from the chunk's first row, so M is split into row chunks below
+// 2 GiB of A.  tpw_req tiles per workgroup, walking feature tiles (rw = 0)
+// or row blocks (rw = 1).
+typedef void (*gemm_fn)(const void *, const void *, int, int, int, EpiArgs, int, int);
+inline hipError_t launch_chunks(gemm_fn kernel, int BM, int BN, int nth, size_t lds, size_t row_bytes, const void *A,
+                                const void *W, int M, int N, int K, const EpiArgs &ep, int tpw_req, int rw,
+                                hipStream_t stream) {
     const int ntn = N / BN;
-    // Output-feature tiles per workgroup (WM_GEMM_TPW overrides, for tuning).
-    static const int tpw_env = [] {
-        const char *v = getenv("WM_GEMM_TPW");
-        return v ? atoi(v) : 0;
-    }();
-    const int tpw_req = tpw_env > 0 ? tpw_env : tpw_default;
-    // Tile order (WM_GEMM_ORDER overrides, for tuning): 0 walks feature
-    // tiles, 1 walks row blocks.
-    static const int order_env = [] {
-        const char *v = getenv("WM_GEMM_ORDER");
-        return v ? atoi(v) : -1;
-    }();
-    const int rw = order_env >= 0 ? (order_env != 0) : rw_default;
-    // A is addressed with 32-bit byte offsets from the chunk's first row:
-    // split M into row chunks below 2 GiB of A.
-    const size_t row_bytes = (size_t)K * (FP8 ? 1 : 2);
     const int chunk = (int)std::min<size_t>((size_t)M, ((size_t)0x7fffffff / row_bytes) / BM * BM);
     for (int r0 = 0; r0 < M; r0 += chunk) {
         const int Mc = std::min(chunk, M - r0);
@@ -838,40 +1006,85 @@ hipError_t launch_cfg(const void *A, const void *W, int M, int N, int K, EpiKind
         const int tpw = std::max(1, std::min(tpw_req, rw ? ntm : ntn));
         const int total = rw ? ((ntm + tpw - 1) / tpw) * ntn : ((ntn + tpw - 1) / tpw) * ntm;
         const int grid = ((total + 7) >> 3) << 3;
-        if constexpr (RLN) {
-            gemm_lds_kernel<BM, BN, BKB, D, WGM, WGN, OCC, EPI_RESID_LN, FP8><<<grid, NTH, lds, stream>>>(Ac, W, Mc, N, K, e, tpw, rw);
-        } else switch (epi) {
-        case EPI_QKV:
-            gemm_lds_kernel<BM, BN, BKB, D, WGM, WGN, OCC, EPI_QKV, FP8><<<grid, NTH, lds, stream>>>(Ac, W, Mc, N, K, e, tpw, rw);
-            break;
-        case EPI_QKV_ROPE:
-            gemm_lds_kernel<BM, BN, BKB, D, WGM, WGN, OCC, EPI_QKV_ROPE, FP8><<<grid, NTH, lds, stream>>>(Ac, W, Mc, N, K, e, tpw, rw);
-            break;
-        case EPI_GELU:
-            gemm_lds_kernel<BM, BN, BKB, D, WGM, WGN, OCC, EPI_GELU, FP8><<<grid, NTH, lds, stream>>>(Ac, W, Mc, N, K, e, tpw, rw);
-            break;
-        case EPI_RESID:
-            gemm_lds_kernel<BM, BN, BKB, D, WGM, WGN, OCC, EPI_RESID, FP8><<<grid, NTH, lds, stream>>>(Ac, W, Mc, N, K, e, tpw, rw);
-            break;
-        default:
-            gemm_lds_kernel<BM, BN, BKB, D, WGM, WGN, OCC, EPI_STORE, FP8><<<grid, NTH, lds, stream>>>(Ac, W, Mc, N, K, e, tpw, rw);
-            break;
-        }
+        kernel<<<grid, nth, lds, stream>>>(Ac, W, Mc, N, K, e, tpw, rw);
         const hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
     }
     return hipSuccess;
 }
 
-// 128-byte stages in rings of 2, one stage ahead.  Measured on the block's
-// shapes (8x90x180, C = 512): 64-byte stages in rings of 4 or 5 (three or
-// four stages ahead) are 8-10% slower, and so are two 4-wave workgroups per
-// CU on 128 x 256 or 256 x 128 tiles: the per-stage barrier costs more than
-// the load latency that deeper rings hide.
+// The instantiation of a kernel family F for an epilogue kind: permuted W
+// rows (perm) exist for the QKV and GELU epilogues, rotary only with them.
+template <typename F>
+inline gemm_fn pick(EpiKind epi, const EpiArgs &ep) {
+    const int perm = ep.perm;
+    switch (epi) {
+    case EPI_QKV: return perm ? F::template get<EPI_QKV, true>() : F::template get<EPI_QKV, false>();
+    case EPI_QKV_ROPE: return perm ? F::template get<EPI_QKV_ROPE, true>() : nullptr;
+    case EPI_GELU: return perm ? F::template get<EPI_GELU, true>() : F::template get<EPI_GELU, false>();
+    case EPI_RESID:
+        if (perm) return nullptr;
+        return splits(ep) ? F::template get<EPI_RESID_SPLIT, false>() : F::template get<EPI_RESID, false>();
+    case EPI_STORE: return perm ? nullptr : F::template get<EPI_STORE, false>();
+    default: return nullptr;
+    }
+}
+
+// LDS limit of a kernel, set once per process and kernel (a local static's
+// initialisation is thread-safe; the server thread launches too).
+template <size_t LDS, typename K>
+inline gemm_fn with_lds(K kernel) {
+    return hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS) == hipSuccess
+               ? (gemm_fn)kernel : nullptr;
+}
+
+template <int BM, int BN, int D, int WGM, int WGN, int OCC, bool FP8>
+struct LdsGemm {
+    static constexpr size_t lds = (size_t)D * (BM + BN) * 128;
+    static_assert(lds * OCC <= 160 * 1024, "LDS per CU");
+    template <int EPI, bool PERM>
+    static gemm_fn get() {
+        static const gemm_fn f = with_lds<lds>(gemm_lds_kernel<BM, BN, 128, D, WGM, WGN, OCC, EPI, FP8, PERM>);
+        return f;
+    }
+};
+
+template <int BM, int BN, bool FP8>
+struct PpGemm {
+    static constexpr size_t lds = (size_t)2 * (BM + BN) * 128;
+    template <int EPI, bool PERM>
+    static gemm_fn get() {
+        static const gemm_fn f = with_lds<lds>(gemm_pp_kernel<BM, BN, EPI, FP8, PERM>);
+        return f;
+    }
+};
+
 template <int BM, int BN, int WGM, int WGN, int OCC, bool FP8>
 hipError_t launch_sa(const void *A, const void *W, int M, int N, int K, EpiKind epi, const EpiArgs &ep,
-                     hipStream_t stream, int tpw_default = 1, int rw_default = 0) {
-    return launch_cfg<BM, BN, 128, 2, WGM, WGN, OCC, FP8>(A, W, M, N, K, epi, ep, stream, tpw_default, rw_default);
+                     hipStream_t stream, int tpw = 1, int rw = 0) {
+    typedef LdsGemm<BM, BN, 2, WGM, WGN, OCC, FP8> G;
+    const gemm_fn f = pick<G>(epi, ep);
+    if (!f) return hipErrorInvalidValue;
+    return launch_chunks(f, BM, BN, 64 * WGM * WGN, G::lds, (size_t)K * (FP8 ? 1 : 2), A, W, M, N, K, ep, tpw, rw, stream);
+}
+
+template <bool FP8>
+hipError_t launch_pp(const void *A, const void *W, int M, int N, int K, EpiKind epi, const EpiArgs &ep,
+                     hipStream_t stream, int tpw, int rw) {
+    typedef PpGemm<256, 256, FP8> G;
+    const gemm_fn f = pick<G>(epi, ep);
+    if (!f) return hipErrorInvalidValue;
+    return launch_chunks(f, 256, 256, 512, G::lds, (size_t)K * (FP8 ? 1 : 2), A, W, M, N, K, ep, tpw, rw, stream);
+}
+
+// EPI_RESID_LN: the tile spans N = 512; one row block per workgroup (the row
+// sums use the stage slots, which a next tile's loads would be filling).
+template <bool FP8>
+hipError_t launch_resid_ln(const void *A, const void *W, int M, int N, int K, const EpiArgs &ep, hipStream_t stream) {
+    typedef PpGemm<128, 512, FP8> G;
+    const gemm_fn f = splits(ep) ? G::template get<EPI_RESID_LN_SPLIT, false>() : G::template get<EPI_RESID_LN, false>();
+    if (!f) return hipErrorInvalidValue;
+    return launch_chunks(f, 128, 512, 512, G::lds, (size_t)K * (FP8 ? 1 : 2), A, W, M, N, K, ep, 1, 1, stream);
 }
 
 }  // namespace glds
@@ -891,40 +1104,26 @@ hipError_t launch_gemm_lds(const void *A, const void *W, int M, int N, int K, Ep
     // (wide_tpw) so that each next tile's loads overlap the previous tile's
     // epilogue, and N = 512 walks two row blocks of one feature tile for the
     // same overlap.  Other N: 128x128 tiles, 2 stages, two workgroups per CU.
-    // WM_GEMM_CFG selects other shapes for tuning.
-    static const int cfg = [] {
-        const char *v = getenv("WM_GEMM_CFG");
-        return v ? atoi(v) : -1;
-    }();
-    // EPI_RESID_LN: 128 x 512 tiles (8 waves, 2 x 4, the same 64 x 128
-    // wave tile), two stages of 80 KB, two row blocks per workgroup
+    if (ep.out8) return hipErrorInvalidValue;
     if (epi == EPI_RESID_LN) {
-        if (!gemm_resid_ln_applies(N) || ep.out8 || ep.out_amax || ep.perm || !ep.ln_g || !ep.ln_b || !ep.ln_out) return hipErrorInvalidValue;
-        return launch_cfg<128, 512, 128, 2, 2, 4, 1, false, true>(A, W, M, N, K, epi, ep, stream, 2, 1);
+        if (!gemm_resid_ln_applies(N) || ep.perm || !ep.ln_g || !ep.ln_b || !ep.ln_out) return hipErrorInvalidValue;
+        return launch_resid_ln<false>(A, W, M, N, K, ep, stream);
     }
     // (a QKV feature tile must not straddle two of Q, K and V: BN divides C)
     const bool n256 = N % 256 == 0 && (!epi_qkv(epi) || ep.C % 256 == 0);
-    switch (cfg) {
-    case 0: return launch_sa<128, 128, 2, 2, 2, false>(A, W, M, N, K, epi, ep, stream);
-    case 3: return launch_cfg<256, 128, 128, 2, 4, 2, 1, false>(A, W, M, N, K, epi, ep, stream);
-    default: break;
-    }
-    auto wide = [&](int tpw, int rw) -> hipError_t {
-        return launch_sa<256, 256, 4, 2, 1, false>(A, W, M, N, K, epi, ep, stream, tpw, rw);
-    };
     if (epi_qkv(epi) && ep.vt) {
         // a workgroup's feature tiles must be all V or none: walk 2 when a
         // part (C columns) holds an even number of tiles, else 1
         const int bn = n256 ? 256 : 128, per_part = ep.C / bn;
-        if (n256) return wide(per_part % 2 ? 1 : 2, 0);
+        if (n256) return launch_pp<false>(A, W, M, N, K, epi, ep, stream, per_part % 2 ? 1 : 2, 0);
         return launch_sa<128, 128, 2, 2, 2, false>(A, W, M, N, K, epi, ep, stream, per_part % 2 ? 1 : 2, 0);
     }
     if (n256) {
         // N = 512 (the out-projection and MLP2 at C = 512): two row blocks of
         // one feature tile per workgroup (measured 2-3% faster than one tile
         // per workgroup; walking feature tiles is faster for wide N)
-        if (N == 512) return wide(2, 1);
-        return wide(wide_tpw(N), 0);
+        if (N == 512) return launch_pp<false>(A, W, M, N, K, epi, ep, stream, 2, 1);
+        return launch_pp<false>(A, W, M, N, K, epi, ep, stream, wide_tpw(N), 0);
     }
     return launch_sa<128, 128, 2, 2, 2, false>(A, W, M, N, K, epi, ep, stream);
 }
@@ -933,30 +1132,25 @@ hipError_t launch_gemm_fp8(const void *A, const void *W, int M, int N, int K, Ep
                            hipStream_t stream) {
     if (M <= 0) return hipSuccess;
     if (N % 128 || K % 128 || (unsigned long long)N * K >= (1ull << 31)) return hipErrorInvalidValue;
-    static const int cfg = [] {
-        const char *v = getenv("WM_GEMM_CFG");
-        return v ? atoi(v) : -1;
-    }();
     if (epi == EPI_RESID_LN) {
-        // as in launch_gemm_lds; one dequantization scale for all rows, and
-        // the LayerNorm output as e4m3 codes (out8) at a given scale
-        if (!gemm_resid_ln_applies(N) || ep.a_amax || !ep.out8 || !ep.ln_amax || ep.out_amax || ep.perm || !ep.ln_g ||
-            !ep.ln_b || !ep.ln_out)
+        // as in launch_gemm_lds; the LayerNorm output as e4m3 codes (out8) at
+        // a given scale
+        if (!gemm_resid_ln_applies(N) || !ep.out8 || !ep.ln_amax || ep.perm || !ep.ln_g || !ep.ln_b || !ep.ln_out)
             return hipErrorInvalidValue;
-        return launch_cfg<128, 512, 128, 2, 2, 4, 1, true, true>(A, W, M, N, K, epi, ep, stream, 2, 1);
+        return launch_resid_ln<true>(A, W, M, N, K, ep, stream);
     }
+    if (!ep.out8 != !ep.perm) return hipErrorInvalidValue;   // e4m3 outputs go with permuted W rows
     if (epi_qkv(epi) && ep.vt) {
-        if (ep.a_amax) return hipErrorInvalidValue;   // V tiles dequantize with the one scale a_dequant
         // a workgroup's feature tiles must be all V or none (as in launch_gemm_lds)
         const bool n256 = N % 256 == 0 && ep.C % 256 == 0;
         const int per_part = ep.C / (n256 ? 256 : 128);
-        if (n256) return launch_sa<256, 256, 4, 2, 1, true>(A, W, M, N, K, epi, ep, stream, per_part % 2 ? 1 : 2, 0);
+        if (n256) return launch_pp<true>(A, W, M, N, K, epi, ep, stream, per_part % 2 ? 1 : 2, 0);
         return launch_sa<128, 128, 2, 2, 2, true>(A, W, M, N, K, epi, ep, stream, per_part % 2 ? 1 : 2, 0);
     }
-    if (N % 256 == 0 && (!epi_qkv(epi) || ep.C % 256 == 0) && cfg != 0) {
+    if (N % 256 == 0 && (!epi_qkv(epi) || ep.C % 256 == 0)) {
         // N = 512 (MLP2 at C = 512): row walk, as in launch_gemm_lds
-        if (N == 512) return launch_sa<256, 256, 4, 2, 1, true>(A, W, M, N, K, epi, ep, stream, 2, 1);
-        return launch_sa<256, 256, 4, 2, 1, true>(A, W, M, N, K, epi, ep, stream, wide_tpw(N), 0);
+        if (N == 512) return launch_pp<true>(A, W, M, N, K, epi, ep, stream, 2, 1);
+        return launch_pp<true>(A, W, M, N, K, epi, ep, stream, wide_tpw(N), 0);
     }
     return launch_sa<128, 128, 2, 2, 2, true>(A, W, M, N, K, epi, ep, stream);
 }

@@ -65,16 +65,10 @@ struct EpiArgs {
     int C, H;           // EPI_QKV: model width and heads (d = 32)
     int part0;          // EPI_QKV: part (0 Q, 1 K, 2 V) of output column 0
     float qscale;       // EPI_QKV: factor on Q columns
-    // FP8 operands: acc * (a_amax[state of row] / 448) * w_dequant, or
-    // acc * a_dequant * w_dequant when a_amax is null (one scale for all rows)
-    const float *a_amax;
+    // FP8 operands: acc * a_dequant * w_dequant (one scale for all rows)
     float a_dequant;
     float w_dequant;
     long T;             // tokens per state
-    // optional: per-state amax of the stored outputs (float bits), index
-    // state * amax_stride + (QKV part or 0)
-    unsigned *out_amax;
-    int amax_stride;
     // W rows permuted within aligned groups of 32 (perm_row), so a lane's
     // two adjacent MFMA tiles hold 8 consecutive output features and store
     // them at once; set for processor weights, not for caller-supplied W
