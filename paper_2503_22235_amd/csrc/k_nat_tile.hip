@@ -627,17 +627,16 @@ __global__ __launch_bounds__(256, 3) void nat_ring_kernel(NatArgs p, TileDiv dm)
                 const unsigned char *vr = sl + vbase + 4 * hf * 1024;
 #pragma unroll
                 for (int tt = 0; tt < 2; ++tt) {
-                    uint4 w0, w1;
-                    {
-                        const uint2 a0 = *(const uint2 *)(vr + 128 * tt);
-                        const uint2 a1 = *(const uint2 *)(vr + 128 * tt + 1024);
-                        w0 = make_uint4(a0.x, a0.y, a1.x, a1.y);
-                    }
-                    {
-                        const unsigned char *v1 = vr + 128 * tt + 4;
-                        w1 = make_uint4(*(const unsigned *)v1, *(const unsigned *)(v1 + 252),
-                                        *(const unsigned *)(v1 + 1024), *(const unsigned *)(v1 + 1276));
-                    }
+                    // group 0: lon columns 0..3 of the lane's block; group 1:
+                    // columns 2, 3 of it and 0, 1 of the next.  (Typed scalar
+                    // loads without overlap: before a load that carries no
+                    // type, as of a struct or merged from overlapping ones,
+                    // the compiler waits for the level in flight.)
+                    const unsigned long a0 = *(const unsigned long *)(vr + 128 * tt);
+                    const unsigned long a1 = *(const unsigned long *)(vr + 128 * tt + 1024);
+                    const unsigned n0 = *(const unsigned *)(vr + 128 * tt + 256), n1 = *(const unsigned *)(vr + 128 * tt + 1280);
+                    const uint4 w0 = make_uint4((unsigned)a0, (unsigned)(a0 >> 32), (unsigned)a1, (unsigned)(a1 >> 32));
+                    const uint4 w1 = make_uint4((unsigned)(a0 >> 32), n0, (unsigned)(a1 >> 32), n1);
                     oacc[0][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w0), pb[0],
                                                                           oacc[0][tt], 0, 0, 0);
                     oacc[1][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w1), pb[1],
