@@ -3,26 +3,18 @@
 //
 //   D[m][n] = sum_k A[m][k] * W[n][k]      (A: tokens x K, W: [out][in])
 //
-// A workgroup of WGM x WGN waves computes a BM x BN tile; each wave owns a
-// (BM/WGM) x (BN/WGN) sub-tile of 16x16x32 MFMA tiles.  The default for the
-// block's shapes is 256 x 256 with 8 waves (wave tile 64 x 128), one
-// workgroup per CU; 128 x 128 with 4 waves and two workgroups per CU covers
-// N not divisible by 256.  K advances in stages of BKB bytes per row (64
-// bf16 or 128 e4m3 values for 128-byte rows).  Each stage is written
-// straight from global memory into LDS by buffer_load_dwordx4 ... lds (no
-// register staging): the activation tile and the weight tile through rings
-// of D slots each, D - 1 stages ahead (D = 2 on the shapes launched here).
-// A workgroup
-// owns one token tile and walks one or more
-// output-feature tiles; the stage stream runs on across tile boundaries, so
-// the next tile's first loads are in flight while the previous tile's
-// epilogue runs.  Rows of A past M come back as zeros from the buffer range
-// check, which handles the ragged last token tile.  16-byte chunks of an LDS
-// row are XOR-swizzled so the 16 rows one fragment read touches fall in
-// distinct banks.  The MFMA "A" operand is the weight tile and "B" the
-// activation tile, so every lane ends up with four consecutive output
-// features of one token for the epilogue.  Tiles go out in an XCD-aware
-// order (consecutive ids on one XCD share an activation tile in its L2).
+// K advances in stages of 128 bytes per row (64 bf16 or 128 e4m3 values),
+// written straight from global memory into LDS by buffer_load_dwordx4 ... lds
+// (no register staging).  Rows of A past M come back as zeros from the buffer
+// range check, which handles the ragged last token tile.  16-byte chunks of an
+// LDS row are XOR-swizzled so that fragment reads have no bank conflicts.  The
+// MFMA "A" operand is the weight tile and "B" the activation tile, so every
+// lane ends up with four consecutive output features of one token for the
+// epilogue (V tiles of the QKV projection swap them).  Tiles go out in an
+// XCD-aware order (consecutive ids on one XCD share an activation tile in its
+// L2).  gemm_pp_kernel computes wide tiles (256 x 256, or 128 x 512 with the
+// LayerNorm epilogue) in two groups of waves half a phase apart,
+// gemm_lds_kernel the narrow ones; plan_tiles chooses.
 #include <algorithm>
 #include <type_traits>
 
@@ -112,64 +104,27 @@ __device__ __forceinline__ void wait_stages(int later) {
     wait_vmcnt<0>();
 }
 
-// The MFMAs of one K stage for a wave's TM x TN tiles.  FIRST: the stage is
-// the tile's first, so its first k-step adds to zero instead of acc.
-// SWAP: the activation tile is the MFMA "A" operand, so a lane holds four
-// consecutive tokens of one output feature (the blocked V layout).
-// The bf16 MFMA block of each k-step runs at raised wave priority, so that a
-// wave with its operands in registers issues ahead of waves still loading
-// from LDS or in their epilogue (measured 1-3% faster on the bf16
-// projections; the e4m3 stage, whose weight loads sit between its MFMAs, was
-// no faster with it).
-template <bool FIRST, bool FP8, int TM, int TN, int KSTEPS, int BKB, bool SWAP = false>
-__device__ __forceinline__ void mma_stage(const unsigned char *sa, const unsigned char *sw, const int *aoff,
-                                          const int *woff, f32x4 (&acc)[TN][TM]) {
-    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) {
-        if constexpr (FP8) {
-            // gfx950 16x16x128 f8f6f4 MFMA (e4m3 x e4m3): a lane holds 32
-            // k-values of its row for both operands, the k chunk 32 g .. 32 g
-            // + 31 of the stage read as two 16-byte pieces (aoff[2 ks],
-            // aoff[2 ks + 1]); both operands use the same k assignment, which
-            // is all a contraction over k needs.
-            i32x8 af[TM];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                const uint4 lo = *(const uint4 *)(sa + aoff[2 * ks] + 16 * i * BKB);
-                const uint4 hi = *(const uint4 *)(sa + aoff[2 * ks + 1] + 16 * i * BKB);
-                af[i] = i32x8{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
-            }
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const uint4 lo = *(const uint4 *)(sw + woff[2 * ks] + 16 * j * BKB);
-                const uint4 hi = *(const uint4 *)(sw + woff[2 * ks + 1] + 16 * j * BKB);
-                const i32x8 wf = {(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-                    acc[j][i] = SWAP ? __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
-                                           af[i], wf, FIRST && ks == 0 ? zero : acc[j][i], 0, 0, 0, 0, 0, 0)
-                                     : __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
-                                           wf, af[i], FIRST && ks == 0 ? zero : acc[j][i], 0, 0, 0, 0, 0, 0);
-            }
-        } else {
-            bf16x8 af[TM], wf[TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) af[i] = *(const bf16x8 *)(sa + aoff[ks] + 16 * i * BKB);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) wf[j] = *(const bf16x8 *)(sw + woff[ks] + 16 * j * BKB);
-            __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-                    acc[j][i] = SWAP ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], wf[j], FIRST && ks == 0 ? zero : acc[j][i],
-                                                                               0, 0, 0)
-                                     : __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], af[i], FIRST && ks == 0 ? zero : acc[j][i],
-                                                                               0, 0, 0);
-            __builtin_amdgcn_s_setprio(0);
-        }
-    }
+// One MFMA k-step: acc of the tile of W rows wf by activation rows af, from
+// zero if FIRST.  SWAP: the activation tile is the MFMA "A" operand, so a lane
+// holds four consecutive tokens of one output feature (the blocked V layout).
+template <bool FIRST, bool SWAP>
+__device__ __forceinline__ f32x4 mma_bf16(i32x4 wf, i32x4 af, f32x4 c) {
+    const bf16x8 w = __builtin_bit_cast(bf16x8, wf), a = __builtin_bit_cast(bf16x8, af);
+    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+    return SWAP ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, w, FIRST ? z : c, 0, 0, 0)
+                : __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, a, FIRST ? z : c, 0, 0, 0);
+}
+// gfx950 16x16x128 f8f6f4 MFMA (e4m3 x e4m3): a lane holds 32 k-values of its
+// row for both operands, the k chunk 32 g .. 32 g + 31 of the stage as two
+// 16-byte pieces; both operands use the same k assignment, which is all a
+// contraction over k needs.
+template <bool FIRST, bool SWAP>
+__device__ __forceinline__ f32x4 mma_fp8(const i32x4 (&wf)[2], const i32x4 (&af)[2], f32x4 c) {
+    const i32x8 w = __builtin_shufflevector(wf[0], wf[1], 0, 1, 2, 3, 4, 5, 6, 7);
+    const i32x8 a = __builtin_shufflevector(af[0], af[1], 0, 1, 2, 3, 4, 5, 6, 7);
+    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+    return SWAP ? __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, w, FIRST ? z : c, 0, 0, 0, 0, 0, 0)
+                : __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(w, a, FIRST ? z : c, 0, 0, 0, 0, 0, 0);
 }
 
 // Epilogue of a V tile of the QKV projection (swapped operands): acc[j][i]
@@ -557,47 +512,31 @@ __device__ __forceinline__ void tile_epilogue(const EpiArgs &ep, int M, int N, i
     }
 }
 
-// FP8: operands are e4m3 bytes (128 k-values per 128-byte stage, MFMA
-// 16x16x128 f8f6f4, one k-step per stage); the epilogue dequantizes per row.
-// WGM x WGN waves tile the BM x BN output; OCC workgroups share a CU.
-// The activation and weight tiles of each K stage stream through two rings
-// of D slots each, D - 1 stages ahead of the MFMAs.
-template <int BM, int BN, int BKB, int D, int WGM, int WGN, int OCC, int EPI, bool FP8, bool PERM>
+// The narrow tiles: WGM x WGN waves compute one BM x BN tile, OCC workgroups
+// share a CU, and the activation and weight tiles of each K stage stream
+// through a ring of D slots, D - 1 stages ahead of the MFMAs.
+template <int BM, int BN, int D, int WGM, int WGN, int OCC, int EPI, bool FP8, bool PERM>
 __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const void *__restrict__ A, const void *__restrict__ W,
-                                                         int M, int N, int K, EpiArgs ep, int tpw, int rw) {
+                                                         int M, int N, int K, EpiArgs ep, int, int) {
 #if defined(__HIP_DEVICE_COMPILE__)   // LDS-address-space builtins exist only in the device pass
+    constexpr int BKB = 128;
     constexpr int NW = WGM * WGN;
     constexpr int WM = BM / WGM, WN = BN / WGN;
     constexpr int TM = WM / 16, TN = WN / 16;
-    constexpr int ABYTES = BM * BKB, WBYTES = BN * BKB;   // one slot of each ring
-    constexpr int CPR = BKB / 16;                  // 16-byte chunks per LDS row
-    constexpr int RPI = 64 / CPR;                  // rows one load instruction fills
-    constexpr int LPA = BM / RPI / NW;             // activation load instructions per wave per stage
-    constexpr int LPB = BN / RPI / NW;             // weight load instructions per wave per stage
-    static_assert(BKB == 128, "stage row bytes");
-    static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "rows per stage must split over the waves");
-    static_assert(WM % 16 == 0 && WN % 16 == 0, "wave tile");
-    static_assert(D >= 2 && D <= 5, "ring depth");
+    constexpr int SLOT = (BM + BN) * BKB;          // one stage: the activation rows, then the weight rows
+    constexpr int LPA = BM / 8 / NW;               // load instructions (8 rows) per wave and stage
+    constexpr int LPB = BN / 8 / NW;
+    static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "rows per stage must split over the waves");
+    static_assert(WM % 16 == 0 && WN % 32 == 0, "wave tile");
     extern __shared__ __align__(16) unsigned char smem[];
-    unsigned char *const aring = smem, *const wring = smem + D * ABYTES;
 
-    // A workgroup computes nn tiles: feature tiles tn0 .. tn0+nn-1 of row
-    // block m0 (rw == 0), or row blocks m0, m0+BM, .. of feature tile tn0
-    // (rw == 1: the workgroups sharing a row block are consecutive ids, so
-    // they run together on one XCD and read that block once into its L2).
     const int ntn = N / BN, ntm = (M + BM - 1) / BM;
-    const int ngrp = rw ? (ntm + tpw - 1) / tpw : (ntn + tpw - 1) / tpw;
-    const int total = rw ? ngrp * ntn : ngrp * ntm;
+    const int total = ntn * ntm;
     const int per = (total + 7) >> 3;
     const int L = blockIdx.x;
     const int id = (L & 7) * per + (L >> 3);
     if (id >= total) return;
-    const int m0 = rw ? (id / ntn) * tpw * BM : (id / ngrp) * BM;
-    const int tn0 = rw ? id % ntn : (id % ngrp) * tpw;
-    const int nn = rw ? min(tpw, ntm - m0 / BM) : min(tpw, ntn - tn0);
-    // per-tile advance of the activation rows and of the weight rows (bytes)
-    const unsigned astep = rw ? (unsigned)BM * (unsigned)K * (FP8 ? 1u : 2u) : 0u;
-    const unsigned wstep = rw ? 0u : (unsigned)BN * (unsigned)K * (FP8 ? 1u : 2u);
+    const int m0 = (id / ntn) * BM, n0 = (id % ntn) * BN;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -607,128 +546,105 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
     const __amdgpu_buffer_rsrc_t ars = make_rsrc(A, (unsigned)M * Kb);
     const __amdgpu_buffer_rsrc_t wrs = make_rsrc(W, (unsigned)N * Kb);
 
-    // per-lane global byte offsets of this wave's load instructions:
-    // instruction i of wave w fills rows RPI (w + NW i) .. +RPI-1 of a slot
+    // per-lane global byte offsets: instruction i of wave w fills rows
+    // 8 (w + NW i) .. +7 of a slot's part
     unsigned voa[LPA], vob[LPB];
 #pragma unroll
     for (int i = 0; i < LPA; ++i) {
-        const int row = RPI * (wave + NW * i) + lane / CPR;
-        voa[i] = (unsigned)(m0 + row) * Kb + (((lane % CPR) ^ swz<FP8>(row)) << 4);
+        const int row = 8 * (wave + NW * i) + (lane >> 3);
+        voa[i] = (unsigned)(m0 + row) * Kb + (((lane & 7) ^ swz<FP8>(row)) << 4);
     }
 #pragma unroll
     for (int i = 0; i < LPB; ++i) {
-        const int row = RPI * (wave + NW * i) + lane / CPR;
-        vob[i] = (unsigned)(tn0 * BN + row) * Kb + (((lane % CPR) ^ swz<FP8>(row)) << 4);
+        const int row = 8 * (wave + NW * i) + (lane >> 3);
+        vob[i] = (unsigned)(n0 + row) * Kb + (((lane & 7) ^ swz<FP8>(row)) << 4);
     }
-    const int nk = K / (FP8 ? BKB : BKB / 2);
-    // stage s of the stream = k-stage (s % nk) of tile (s / nk)
-    auto issue_a = [&](int s) {
-        const int t = s / nk, kt = s - t * nk;
-        unsigned char *sbase = aring + (s % D) * ABYTES;
-        // the row advance goes into the vector offset: rows past M must fail
-        // the buffer range check and read zero
-        const unsigned aadv = (unsigned)t * astep;
+    const int nk = (int)(Kb / BKB);
+    int lslot = 0;
+    unsigned lk = 0;
+    auto load = [&]() {
+        unsigned char *dst = smem + lslot * SLOT;
 #pragma unroll
         for (int i = 0; i < LPA; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(ars, (lds_void *)(sbase + RPI * (wave + NW * i) * BKB), 16,
-                                                     voa[i] + aadv, kt * BKB, 0, 0);
-    };
-    auto issue_w = [&](int s) {
-        const int t = s / nk, kt = s - t * nk;
-        unsigned char *sbase = wring + (s % D) * WBYTES;
-        const unsigned wsoff = (unsigned)t * wstep + kt * BKB;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ars, (lds_void *)(dst + 1024 * (wave + NW * i)), 16, voa[i], lk, 0, 0);
 #pragma unroll
         for (int i = 0; i < LPB; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lds_void *)(sbase + RPI * (wave + NW * i) * BKB), 16,
-                                                     vob[i], wsoff, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lds_void *)(dst + BM * BKB + 1024 * (wave + NW * i)), 16, vob[i], lk, 0, 0);
+        lk += BKB;
+        lslot = lslot == D - 1 ? 0 : lslot + 1;
     };
 
-    constexpr bool ZSTART = !FP8 && EPI != EPI_QKV_ROPE;
-
-    // lane-constant fragment offsets inside a stage (swizzle depends on r16
-    // only): bf16 k-step ks reads 16 bytes at k = 32ks + 8g; fp8 k-step ks
-    // reads 8 bytes at k = 32ks + 8g.
-    // fp8: one 16x16x128 k-step per 128-byte stage; a lane reads chunks
-    // 2g and 2g + 1 (k = 32 g .. 32 g + 31) of its row.
-    constexpr int KSTEPS = FP8 ? BKB / 128 : BKB / 64;
-    constexpr int NOFF = FP8 ? 2 * KSTEPS : KSTEPS;
-    static_assert(!FP8 || BKB == 128, "fp8 stages hold one 128-k MFMA step");
-    int aoff[NOFF], woff[NOFF];
+    // fragment chunks of a row: as in gemm_pp_kernel
+    int aoff[2], woff[2];
 #pragma unroll
-    for (int o = 0; o < NOFF; ++o) {
-        const int pc = FP8 ? (((8 * (o >> 1) + 2 * g + (o & 1)) ^ swz<FP8>(r16)) << 4)
-                           : (((4 * o + g) ^ swz<FP8>(r16)) << 4);
-        aoff[o] = (wm * WM + r16) * BKB + pc;
-        woff[o] = (wn * WN + r16) * BKB + pc;
+    for (int o = 0; o < 2; ++o) {
+        const int pc = (FP8 ? 2 * g + o : 4 * o + g) ^ swz<FP8>(r16);
+        aoff[o] = (wm * WM + r16) * BKB + (pc << 4);
+        woff[o] = BM * BKB + (wn * WN + r16) * BKB + (pc << 4);
     }
 
-    // Issue order: A(0), W(0), .., A(D-2), W(D-2), then in iteration st
-    // A(st+D-1), W(st+D-1).  So when iteration st waits, the loads of stages
-    // st+1 .. st+D-2 (those that exist) may stay in flight.
-    const int S = nn * nk;
-#pragma unroll
-    for (int s0 = 0; s0 < D - 1; ++s0)
-        if (s0 < S) {
-            issue_a(s0);
-            issue_w(s0);
-        }
+    for (int s0 = 0; s0 < D - 1 && s0 < nk; ++s0) load();
 
-    // The tiles of this workgroup.  SWAP (the V tiles of a QKV projection
-    // with ep.vt set; a workgroup's tiles are all V or none):
-    // swapped MFMA operands and the blocked-layout epilogue.  The two bodies
-    // are separate instantiations, so neither carries the other's registers.
+    // SWAP (the V tiles of a QKV projection with ep.vt set): swapped MFMA
+    // operands and the blocked-layout epilogue.
     auto body = [&](auto swap_tag) {
     constexpr bool SWAP = decltype(swap_tag)::value;
     f32x4 acc[TN][TM];
+    int slot = 0;
+    auto stage = [&](auto first_tag, int kt) {
+        constexpr bool FIRST = decltype(first_tag)::value;
+        // This wave's loads of stage kt have landed once at most the loads of
+        // the later stages already issued are outstanding (loads return in
+        // order); the barrier then makes all waves' parts of stage kt visible
+        // and frees the slot read in stage kt - 1.  (A bare s_barrier:
+        // __syncthreads() would also drain the loads still in flight.)
+        wait_stages<LPA + LPB, D>(nk - 1 - kt);
+        __builtin_amdgcn_s_barrier();
+        if (kt + D - 1 < nk) load();
+        const unsigned char *sl = smem + slot * SLOT;
+        slot = slot == D - 1 ? 0 : slot + 1;
+        // (typed reads: see gemm_pp_kernel)
+        i32x4 a[TM][2], w[TN][2];
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int i = 0; i < TM; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int t = 0; t < nn; ++t) {
-        for (int kt = 0; kt < nk; ++kt) {
-            const int st = t * nk + kt;
-            // This wave's loads of stage st have landed once at most the
-            // loads of the later stages already issued are outstanding (loads
-            // return in order); the barrier then makes all waves' parts of
-            // stage st visible and frees the slots read in iteration st - 1.  (A bare s_barrier: __syncthreads() would
-            // also drain the loads still in flight.)
-            wait_stages<LPA + LPB, D>(S - 1 - st);
-            __builtin_amdgcn_s_barrier();
-            if (st + D - 1 < S) {
-                issue_a(st + D - 1);
-                issue_w(st + D - 1);
-            }
-            const unsigned char *sbA = aring + (st % D) * ABYTES, *sbW = wring + (st % D) * WBYTES;
-            // ZSTART: a tile's first k-step starts its accumulators from an
-            // inline zero operand instead of registers cleared in the previous
-            // epilogue (not for the FP8 and rotary variants, whose
-            // extra registers would spill with a second copy of the stage code)
-            if (ZSTART && kt == 0) mma_stage<ZSTART, FP8, TM, TN, KSTEPS, BKB, SWAP>(sbA, sbW, aoff, woff, acc);
-            else mma_stage<false, FP8, TM, TN, KSTEPS, BKB, SWAP>(sbA, sbW, aoff, woff, acc);
-        }
-        const int n0 = (rw ? tn0 : tn0 + t) * BN;
-        const int mt = rw ? m0 + t * BM : m0;    // first row of this tile
-        if constexpr (SWAP) {
-            vt_epilogue<TM, TN, FP8>(ep, ep.bias + 2 * ep.C, M, mt + wm * WM, n0 - 2 * ep.C + wn * WN, acc, g, r16, [] {});
-            if constexpr (!ZSTART) {
+            for (int o = 0; o < 2; ++o) a[i][o] = *(const i32x4 *)(sl + aoff[o] + 16 * i * BKB);
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-                    for (int i = 0; i < TM; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-            continue;
-        }
-        tile_epilogue<EPI, FP8, PERM, TM, TN>(ep, M, N, mt + wm * WM, n0, wn * WN, g, r16, acc, [] {});
-        if constexpr (!ZSTART) {
+            for (int o = 0; o < 2; ++o) w[j][o] = *(const i32x4 *)(sl + woff[o] + 16 * j * BKB);
+        __builtin_amdgcn_s_setprio(1);
+        if constexpr (FP8) {
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int i = 0; i < TM; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int i = 0; i < TM; ++i) acc[j][i] = mma_fp8<FIRST, SWAP>(w[j], a[i], acc[j][i]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int i = 0; i < TM; ++i) acc[j][i] = mma_bf16<FIRST, SWAP>(w[j][0], a[i][0], acc[j][i]);
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int i = 0; i < TM; ++i) acc[j][i] = mma_bf16<false, SWAP>(w[j][1], a[i][1], acc[j][i]);
         }
+        __builtin_amdgcn_s_setprio(0);
+    };
+    stage(std::true_type{}, 0);
+    for (int kt = 1; kt < nk; ++kt) stage(std::false_type{}, kt);
+    if constexpr (epi_resid_ln(EPI)) {
+        static_assert((2 * WGN * BM + 2 * BN) * 4 <= SLOT && BN <= 2 * NW * 64, "row sums and ln_g, ln_b fit a slot");
+        resid_ln_epilogue<TM, TN, WGN, BM, FP8, EPI == EPI_RESID_LN_SPLIT>(ep, M, N, m0, wm * WM, wn, wn * WN, g, r16, tid, NW * 64,
+                                                                           acc, (float *)smem);
+    } else if constexpr (SWAP) {
+        vt_epilogue<TM, TN, FP8>(ep, ep.bias + 2 * ep.C, M, m0 + wm * WM, n0 - 2 * ep.C + wn * WN, acc, g, r16, [] {});
+    } else {
+        tile_epilogue<EPI, FP8, PERM, TM, TN>(ep, M, N, m0 + wm * WM, n0, wn * WN, g, r16, acc, [] {});
     }
     };
     if constexpr (epi_qkv(EPI)) {
-        if (ep.vt && tn0 * BN >= 2 * ep.C) {
+        if (ep.vt && n0 >= 2 * ep.C) {
             body(std::true_type{});
             return;
         }
@@ -863,7 +779,6 @@ __global__ __launch_bounds__(512, 1) void gemm_pp_kernel(const void *__restrict_
     // LDS is read as ext_vector values: before a read of a struct type (uint4)
     // the compiler waits for every LDS load in flight
     i32x4 a[TM][2], w[4][2];      // A and the current half of W: [tile][chunk]
-    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     auto read_a = [&](const unsigned char *sl) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -884,25 +799,16 @@ __global__ __launch_bounds__(512, 1) void gemm_pp_kernel(const void *__restrict_
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int i = 0; i < TM; ++i) {
-                    const i32x8 af = __builtin_shufflevector(a[i][0], a[i][1], 0, 1, 2, 3, 4, 5, 6, 7);
-                    const i32x8 wf = __builtin_shufflevector(w[j][0], w[j][1], 0, 1, 2, 3, 4, 5, 6, 7);
-                    f32x4 &c = acc[j0 + j][i];
-                    c = SWAP ? __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(af, wf, FIRST ? zero : c, 0, 0, 0, 0, 0, 0)
-                             : __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(wf, af, FIRST ? zero : c, 0, 0, 0, 0, 0, 0);
-                }
+                for (int i = 0; i < TM; ++i) acc[j0 + j][i] = mma_fp8<FIRST, SWAP>(w[j], a[i], acc[j0 + j][i]);
         } else {
 #pragma unroll
-            for (int o = 0; o < 2; ++o)
+            for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
+                for (int i = 0; i < TM; ++i) acc[j0 + j][i] = mma_bf16<FIRST, SWAP>(w[j][0], a[i][0], acc[j0 + j][i]);
 #pragma unroll
-                    for (int i = 0; i < TM; ++i) {
-                        const bf16x8 af = __builtin_bit_cast(bf16x8, a[i][o]), wf = __builtin_bit_cast(bf16x8, w[j][o]);
-                        f32x4 &c = acc[j0 + j][i];
-                        c = SWAP ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, wf, FIRST && o == 0 ? zero : c, 0, 0, 0)
-                                 : __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, af, FIRST && o == 0 ? zero : c, 0, 0, 0);
-                    }
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < TM; ++i) acc[j0 + j][i] = mma_bf16<false, SWAP>(w[j][1], a[i][1], acc[j0 + j][i]);
         }
         __builtin_amdgcn_s_setprio(0);
     };
@@ -981,10 +887,61 @@ __global__ __launch_bounds__(512, 1) void gemm_pp_kernel(const void *__restrict_
 #endif
 }
 
-// Feature tiles per workgroup for 256-wide tiles: the block's QKV (N = 3C =
-// 1536) and MLP1 (N = 4C = 2048) GEMMs at C = 512 run fastest with 3 and 4
-// (measured); other N of 1536 or more take 2, smaller N take 1.
-inline int wide_tpw(int N) { return N == 1536 ? 3 : (N == 2048 ? 4 : (N >= 1536 ? 2 : 1)); }
+// Tile choice.  Three tiles give the same bits (every accumulator adds the
+// same k-steps in the same order), so the choice is by time alone:
+//   256 x 256 (gemm_pp_kernel)   fewest LDS and L2 bytes per FLOP, but one
+//                                 workgroup per CU: 1.0 to 1.9 rounds over the
+//                                 256 CUs cost two;
+//   128 x 128 (gemm_lds_kernel)  two workgroups per CU, finer rounds;
+//   64 x 64                      four per CU, for outputs too small to give
+//                                 every CU a larger tile.
+// The estimates below (us) are fits to times measured over M = 100 .. 129600
+// at (N, K) = (1536, 512), (2048, 512), (512, 2048), (512, 512), (3072, 1024),
+// (1024, 4096), (768, 256), (256, 1024), in bf16 and e4m3; nk: stages of 128
+// bytes per row.  They place the lines between the tiles; measured, bf16, us,
+// (M, N, K): 256 x 256 / 128 x 128 / 64 x 64
+//   (129600, 2048, 512) 347 / 467 / 589     (32000, 512, 2048)  70 /  75 / 101
+//   ( 40000, 512, 2048) 105 /  96 / 127     (20250,  512, 512)  31 /  28 /  26
+//   (  8640, 2048, 512)  41 /  30 /  33     ( 2880, 512, 2048)  51 /  25 /  19
+//   (  1200, 512, 512)   18 /  10 /   7     (  405, 1024, 4096) 85 /  41 /  31
+struct TilePlan {
+    int bm;        // 256, 128 or 64
+    int tpw;       // 256: tiles per workgroup
+    int rw;        // 256: walk row blocks (1) or feature tiles (0)
+};
+// n256: whether 256-wide feature tiles are possible; wmax: most feature tiles
+// a 256 x 256 workgroup may walk (a QKV workgroup's are all V or none).
+inline TilePlan plan_tiles(int M, int N, int nk, bool n256, int wmax) {
+    auto cdiv = [](long a, long b) { return (a + b - 1) / b; };
+    const long t64 = cdiv(M, 64) * (N / 64), t128 = cdiv(M, 128) * (N / 128);
+    // (past some 7500 tiles of 128 x 128 the bf16 output no longer fits the 256
+    // MB cache behind the L2s, and the smaller tiles' extra reads cost a third)
+    const double far = t128 > 7500 ? 1.3 : 1.0;
+    const double c64 = 4.0 + (0.35 + 0.22 * nk) * cdiv(t64, 256) * far;
+    const double c128 = t128 <= 256 ? 5.5 + 0.65 * nk
+                                    : (4.5 + 1.1 * nk) * (t128 <= 512 ? 1.0 : std::max(2.0, t128 / 512.0)) * far;
+    TilePlan best{c64 <= c128 ? 64 : 128, 1, 0};
+    double c = std::min(c64, c128);
+    if (!n256) return best;
+    // 256 x 256: a workgroup that walks w tiles overlaps each next tile's
+    // loads with the previous epilogue (one tile alone: 3 us more), unless
+    // that leaves a round of workgroups short.  N = 512 walks row blocks (the
+    // workgroups that share a row block are neighbours on one XCD), wider N
+    // feature tiles; the block's MLP1 (N = 2048) runs fastest with 4.
+    const long ntm = cdiv(M, 256), ntn = N / 256;
+    const int rw = N == 512 && wmax > 1;
+    for (int w = 1; w <= wmax; ++w) {
+        const long groups = rw ? cdiv(ntm, w) * ntn : ntm * cdiv(ntn, w);
+        const double t = 4.0 + cdiv(groups, 256) * (3.0 + w * (11.0 + 1.15 * nk));
+        if (t < c) {
+            c = t;
+            best = TilePlan{256, w, rw};
+        }
+    }
+    return best;
+}
+// Most tiles a 256 x 256 workgroup walks.
+inline int wide_max(int N) { return N >= 2048 ? 4 : (N >= 1536 ? 3 : (N == 512 ? 2 : 1)); }
 
 // Launches `kernel` for every row chunk: A is addressed with 32-bit byte
 // offsets from the chunk's first row, so M is split into row chunks below
@@ -1044,7 +1001,7 @@ struct LdsGemm {
     static_assert(lds * OCC <= 160 * 1024, "LDS per CU");
     template <int EPI, bool PERM>
     static gemm_fn get() {
-        static const gemm_fn f = with_lds<lds>(gemm_lds_kernel<BM, BN, 128, D, WGM, WGN, OCC, EPI, FP8, PERM>);
+        static const gemm_fn f = with_lds<lds>(gemm_lds_kernel<BM, BN, D, WGM, WGN, OCC, EPI, FP8, PERM>);
         return f;
     }
 };
@@ -1059,32 +1016,48 @@ struct PpGemm {
     }
 };
 
-template <int BM, int BN, int WGM, int WGN, int OCC, bool FP8>
-hipError_t launch_sa(const void *A, const void *W, int M, int N, int K, EpiKind epi, const EpiArgs &ep,
-                     hipStream_t stream, int tpw = 1, int rw = 0) {
-    typedef LdsGemm<BM, BN, 2, WGM, WGN, OCC, FP8> G;
+template <int BM, int BN, int D, int WGM, int WGN, int OCC, bool FP8>
+hipError_t launch_lds(const void *A, const void *W, int M, int N, int K, EpiKind epi, const EpiArgs &ep, hipStream_t stream) {
+    typedef LdsGemm<BM, BN, D, WGM, WGN, OCC, FP8> G;
     const gemm_fn f = pick<G>(epi, ep);
     if (!f) return hipErrorInvalidValue;
-    return launch_chunks(f, BM, BN, 64 * WGM * WGN, G::lds, (size_t)K * (FP8 ? 1 : 2), A, W, M, N, K, ep, tpw, rw, stream);
+    return launch_chunks(f, BM, BN, 64 * WGM * WGN, G::lds, (size_t)K * (FP8 ? 1 : 2), A, W, M, N, K, ep, 1, 0, stream);
 }
 
 template <bool FP8>
-hipError_t launch_pp(const void *A, const void *W, int M, int N, int K, EpiKind epi, const EpiArgs &ep,
-                     hipStream_t stream, int tpw, int rw) {
-    typedef PpGemm<256, 256, FP8> G;
-    const gemm_fn f = pick<G>(epi, ep);
-    if (!f) return hipErrorInvalidValue;
-    return launch_chunks(f, 256, 256, 512, G::lds, (size_t)K * (FP8 ? 1 : 2), A, W, M, N, K, ep, tpw, rw, stream);
+hipError_t launch_tiles(const void *A, const void *W, int M, int N, int K, EpiKind epi, const EpiArgs &ep, hipStream_t stream) {
+    const size_t row_bytes = (size_t)K * (FP8 ? 1 : 2);
+    // a QKV feature tile must not straddle two of Q, K and V (BN divides C),
+    // and a workgroup's must be all V or none when V goes to the blocked layout
+    const bool n256 = N % 256 == 0 && (!epi_qkv(epi) || ep.C % 256 == 0);
+    const int wmax = epi_qkv(epi) && ep.vt ? ((ep.C / 256) % 2 ? 1 : 2) : wide_max(N);
+    const TilePlan t = plan_tiles(M, N, (int)(row_bytes / 128), n256, wmax);
+    auto run = [&](auto tag, int BM, int BN, int nth) -> hipError_t {
+        typedef decltype(tag) G;
+        const gemm_fn f = pick<G>(epi, ep);
+        if (!f) return hipErrorInvalidValue;
+        return launch_chunks(f, BM, BN, nth, G::lds, row_bytes, A, W, M, N, K, ep, t.tpw, t.rw, stream);
+    };
+    if (t.bm == 256) return run(PpGemm<256, 256, FP8>{}, 256, 256, 512);
+    if (t.bm == 128) return run(LdsGemm<128, 128, 2, 2, 2, 2, FP8>{}, 128, 128, 256);
+    return run(LdsGemm<64, 64, 2, 2, 2, 4, FP8>{}, 64, 64, 256);
 }
 
 // EPI_RESID_LN: the tile spans N = 512; one row block per workgroup (the row
-// sums use the stage slots, which a next tile's loads would be filling).
+// sums use the stage slots, which a next tile's loads would be filling).  64
+// rows while that gives every workgroup a CU (M = 14400, bf16: 28 us against
+// 41 with 128 rows, which fill half the CUs; M = 21600: 49 against 44).  The
+// row sums run over the same lanes and waves in both.
 template <bool FP8>
 hipError_t launch_resid_ln(const void *A, const void *W, int M, int N, int K, const EpiArgs &ep, hipStream_t stream) {
-    typedef PpGemm<128, 512, FP8> G;
-    const gemm_fn f = splits(ep) ? G::template get<EPI_RESID_LN_SPLIT, false>() : G::template get<EPI_RESID_LN, false>();
-    if (!f) return hipErrorInvalidValue;
-    return launch_chunks(f, 128, 512, 512, G::lds, (size_t)K * (FP8 ? 1 : 2), A, W, M, N, K, ep, 1, 1, stream);
+    auto run = [&](auto tag, int BM) -> hipError_t {
+        typedef decltype(tag) G;
+        const gemm_fn f = splits(ep) ? G::template get<EPI_RESID_LN_SPLIT, false>() : G::template get<EPI_RESID_LN, false>();
+        if (!f) return hipErrorInvalidValue;
+        return launch_chunks(f, BM, 512, 512, G::lds, (size_t)K * (FP8 ? 1 : 2), A, W, M, N, K, ep, 1, 1, stream);
+    };
+    if (M <= 64 * 256) return run(LdsGemm<64, 512, 2, 2, 4, 1, FP8>{}, 64);
+    return run(PpGemm<128, 512, FP8>{}, 128);
 }
 
 }  // namespace glds
@@ -1098,34 +1071,12 @@ bool gemm_lds_applies(int M, int N, int K) {
 
 hipError_t launch_gemm_lds(const void *A, const void *W, int M, int N, int K, EpiKind epi, const EpiArgs &ep,
                            hipStream_t stream) {
-    // Default for N a multiple of 256: 256x256 tiles, 8 waves (4 x 2, wave
-    // tile 64 x 128), 2 stages of 64 KB, one workgroup per CU; wide outputs
-    // (six or more feature tiles) walk several feature tiles per workgroup
-    // (wide_tpw) so that each next tile's loads overlap the previous tile's
-    // epilogue, and N = 512 walks two row blocks of one feature tile for the
-    // same overlap.  Other N: 128x128 tiles, 2 stages, two workgroups per CU.
     if (ep.out8) return hipErrorInvalidValue;
     if (epi == EPI_RESID_LN) {
         if (!gemm_resid_ln_applies(N) || ep.perm || !ep.ln_g || !ep.ln_b || !ep.ln_out) return hipErrorInvalidValue;
         return launch_resid_ln<false>(A, W, M, N, K, ep, stream);
     }
-    // (a QKV feature tile must not straddle two of Q, K and V: BN divides C)
-    const bool n256 = N % 256 == 0 && (!epi_qkv(epi) || ep.C % 256 == 0);
-    if (epi_qkv(epi) && ep.vt) {
-        // a workgroup's feature tiles must be all V or none: walk 2 when a
-        // part (C columns) holds an even number of tiles, else 1
-        const int bn = n256 ? 256 : 128, per_part = ep.C / bn;
-        if (n256) return launch_pp<false>(A, W, M, N, K, epi, ep, stream, per_part % 2 ? 1 : 2, 0);
-        return launch_sa<128, 128, 2, 2, 2, false>(A, W, M, N, K, epi, ep, stream, per_part % 2 ? 1 : 2, 0);
-    }
-    if (n256) {
-        // N = 512 (the out-projection and MLP2 at C = 512): two row blocks of
-        // one feature tile per workgroup (measured 2-3% faster than one tile
-        // per workgroup; walking feature tiles is faster for wide N)
-        if (N == 512) return launch_pp<false>(A, W, M, N, K, epi, ep, stream, 2, 1);
-        return launch_pp<false>(A, W, M, N, K, epi, ep, stream, wide_tpw(N), 0);
-    }
-    return launch_sa<128, 128, 2, 2, 2, false>(A, W, M, N, K, epi, ep, stream);
+    return launch_tiles<false>(A, W, M, N, K, epi, ep, stream);
 }
 
 hipError_t launch_gemm_fp8(const void *A, const void *W, int M, int N, int K, EpiKind epi, const EpiArgs &ep,
@@ -1140,19 +1091,7 @@ hipError_t launch_gemm_fp8(const void *A, const void *W, int M, int N, int K, Ep
         return launch_resid_ln<true>(A, W, M, N, K, ep, stream);
     }
     if (!ep.out8 != !ep.perm) return hipErrorInvalidValue;   // e4m3 outputs go with permuted W rows
-    if (epi_qkv(epi) && ep.vt) {
-        // a workgroup's feature tiles must be all V or none (as in launch_gemm_lds)
-        const bool n256 = N % 256 == 0 && ep.C % 256 == 0;
-        const int per_part = ep.C / (n256 ? 256 : 128);
-        if (n256) return launch_pp<true>(A, W, M, N, K, epi, ep, stream, per_part % 2 ? 1 : 2, 0);
-        return launch_sa<128, 128, 2, 2, 2, true>(A, W, M, N, K, epi, ep, stream, per_part % 2 ? 1 : 2, 0);
-    }
-    if (N % 256 == 0 && (!epi_qkv(epi) || ep.C % 256 == 0)) {
-        // N = 512 (MLP2 at C = 512): row walk, as in launch_gemm_lds
-        if (N == 512) return launch_pp<true>(A, W, M, N, K, epi, ep, stream, 2, 1);
-        return launch_pp<true>(A, W, M, N, K, epi, ep, stream, wide_tpw(N), 0);
-    }
-    return launch_sa<128, 128, 2, 2, 2, true>(A, W, M, N, K, epi, ep, stream);
+    return launch_tiles<true>(A, W, M, N, K, epi, ep, stream);
 }
 
 }  // namespace wm

@@ -83,3 +83,23 @@ def test_states_straddling_waves(env, prec):
     for b in range(B):
         assert torch.equal(bufs[b], xb[b:b + 1])
     p.close()
+
+
+@pytest.mark.parametrize("prec", [1, 2])
+@pytest.mark.parametrize("C,shape", [(128, (5, 45, 90)), (256, (5, 20, 22)), (512, (8, 60, 36))])
+def test_tile_choice_does_not_show(env, C, shape, prec):
+    """The GEMM tiles depend on the number of rows (64, 128 or 256 rows; 64 or
+    128 with the fused LayerNorm): a state alone and in a batch of 4 runs on
+    different ones and gets the same bits."""
+    wm, torch, ctx = env
+    g = S.Grid(Z=shape[0], Y=shape[1], X=shape[2], C=C, heads=C // 32, Kz=3, Ky=5, Kx=5)
+    print("tile choice", C, shape, "prec", prec, flush=True)
+    p = wm.wm_processor_create(ctx, g, 1, 4, prec, S.processor_params(g, 1, 1))
+    x = torch.from_numpy(S.latent_state(g, 1, 6)).cuda()
+    xb = x.repeat(4, 1, 1, 1, 1).contiguous()
+    xb[1:3].neg_()
+    xs = x.clone()
+    wm.wm_processor_step(ctx, p, 4, xb)
+    wm.wm_processor_step(ctx, p, 1, xs)
+    assert torch.equal(xb[:1], xs) and torch.equal(xb[3:], xs)
+    p.close()
