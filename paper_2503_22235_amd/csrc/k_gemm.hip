@@ -1,4 +1,5 @@
-// MFMA GEMM for the block's linear maps, with fused epilogues.
+// Launcher of the linear maps, and the MFMA GEMM for weights of 2 GiB and
+// more, beyond the 32-bit buffer offsets of the LDS-ring kernels.
 //
 //   D[m][n] = sum_k A[m][k] * W[n][k]
 //
@@ -223,14 +224,12 @@ hipError_t launch_cfg(const void *A, const void *W, int M, int N, int K, EpiKind
 hipError_t launch_gemm(const void *A, const void *W, int M, int N, int K, bool a_bf16, EpiKind epi,
                        const EpiArgs &ep, hipStream_t stream) {
     if (M <= 0) return hipSuccess;
+    if (N % 64 || K % (a_bf16 ? 64 : 32)) return hipErrorInvalidValue;
     if (a_bf16 && gemm_lds_applies(M, N, K)) return launch_gemm_lds(A, W, M, N, K, epi, ep, stream);
+    if (!a_bf16 && (unsigned long long)N * K * 4 < (1ull << 31)) return launch_gemm_f32(A, W, M, N, K, epi, ep, stream);
     // permuted W rows and the blocked V layout are the LDS kernels' only
     if (ep.perm || ep.vt || ep.out8 || epi == EPI_RESID_LN) return hipErrorInvalidValue;
-    if (a_bf16) {
-        if (N % 128 == 0) return launch_cfg<bf16, 128, 128>(A, W, M, N, K, epi, ep, stream);
-        return launch_cfg<bf16, 128, 64>(A, W, M, N, K, epi, ep, stream);
-    }
-    if (N % 128 == 0) return launch_cfg<float, 128, 128>(A, W, M, N, K, epi, ep, stream);
+    if (a_bf16) return launch_cfg<bf16, 128, 64>(A, W, M, N, K, epi, ep, stream);
     return launch_cfg<float, 128, 64>(A, W, M, N, K, epi, ep, stream);
 }
 

@@ -127,6 +127,62 @@ __device__ __forceinline__ f32x4 mma_fp8(const i32x4 (&wf)[2], const i32x4 (&af)
                 : __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(w, a, FIRST ? z : c, 0, 0, 0, 0, 0, 0);
 }
 
+// Float32 operands on the bf16 matrix cores: x = x1 + x2 + x3 exactly, each
+// part x's remainder rounded to nearest bf16 (8 significant bits; so |x2| <=
+// 2^-9 |x|, |x3| <= 2^-18 |x|).  A product is the sum of the six partial
+// products x_i w_j with i + j <= 4, smallest first; the three left out are
+// below 2^-26 of it, with either sign.  The products of bf16 values are exact
+// and the sum takes 6 roundings per 32 k where 16x16x4 f32 MFMAs take 8, at
+// six bf16 MFMAs of 16 cycles instead of eight of 32.  Measured (N(0,1) rows,
+// N(0,0.02) weights) the relative error against float64 is 1.54e-7, 3.36e-7,
+// 4.9e-7 and 1.00e-6 at K = 128, 512, 1024 and 4096, against 2.04e-7, 4.06e-7,
+// 5.7e-7 and 1.15e-6 with f32 MFMAs.  M = 129600, N = 1536, K = 512: 2158 ->
+// 1191 us (171 TFLOP/s of products; the f32 MFMA kernel reached 94).  Lane and
+// k layout are those of one 16x16x32 operand (8 consecutive k).
+struct Split3 {
+    i32x4 p[3];
+};
+__device__ __forceinline__ Split3 split3(const i32x4 (&raw)[2]) {
+    Split3 s;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        float a = __int_as_float(raw[q >> 1][2 * (q & 1)]), b = __int_as_float(raw[q >> 1][2 * (q & 1) + 1]);
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            const unsigned u = pack_bf16x2(a, b);
+            s.p[t][q] = (int)u;
+            a -= __uint_as_float(u << 16);
+            b -= __uint_as_float(u & 0xffff0000u);
+        }
+    }
+    return s;
+}
+
+// A wave's tiles once more with f32 MFMAs, operands straight from global
+// memory: where the partial sums above are not finite (an operand is, or the
+// sum overflows), this gives what float32 arithmetic gives.
+template <int TM, int TN>
+__device__ void f32_tiles(const float *A, const float *W, int M, int K, int r0, int n0, int g, int r16, f32x4 (&acc)[TN][TM]) {
+    const float *ar[TM], *wr[TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) ar[i] = A + (size_t)min(r0 + 16 * i + r16, M - 1) * K + 8 * g;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) wr[j] = W + (size_t)(n0 + 16 * j + r16) * K + 8 * g;
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // lane group g contracts k = 8 g + s over the 8 steps s
+    for (int k = 0; k < K; k += 32)
+#pragma unroll 1
+        for (int s = 0; s < 8; ++s)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+                    acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(wr[j][k + s], ar[i][k + s], acc[j][i], 0, 0, 0);
+}
+
 // Epilogue of a V tile of the QKV projection (swapped operands): acc[j][i]
 // holds tokens r0 + 16 i + 4 g + (0..3) (chunk rows) of V feature
 // f0 + 16 j + r16 (head f >> 5, channel f & 31; V bias `bias`); each lane
@@ -512,14 +568,104 @@ __device__ __forceinline__ void tile_epilogue(const EpiArgs &ep, int M, int N, i
     }
 }
 
+// tile_epilogue of the float32 kernels: every kind but EPI_RESID stores
+// float32 (16 bytes per lane, row and feature tile); W rows in natural order.
+template <int EPI, int TM, int TN>
+__device__ __forceinline__ void tile_epilogue_f32(const EpiArgs &ep, int M, int N, int r0, int n0, int ncol, int g, int r16,
+                                                  const f32x4 (&acc)[TN][TM]) {
+    if constexpr (epi_resid(EPI)) {
+        resid_update<TM, TN, false, EPI == EPI_RESID_SPLIT>(ep, M, N, r0, n0 + ncol, g, r16, 1.0f, acc, [](int, int, f32x4) {});
+        return;
+    } else {
+    const int part = epi_qkv(EPI) ? ep.part0 + n0 / ep.C : 0;
+    const int rows = min(max(M - r0, 0), 16 * TM);
+    const int rs_len = epi_qkv(EPI) ? 32 : N;
+    const float om = epi_qkv(EPI) && part == 0 ? ep.qscale : 1.0f;
+    const float *base = (const float *)ep.out;
+    size_t pair = 0;
+    unsigned bytes;
+    if constexpr (epi_qkv(EPI)) {
+        const int hc = n0 + ncol - (part - ep.part0) * ep.C;
+        base += (((size_t)part * ep.H + (hc >> 5)) * ep.Mtot + r0 + ep.row0) * 32;
+        pair = (size_t)ep.Mtot * 32;
+        bytes = (unsigned)(rows * 32) * 4u;
+    } else {
+        base += (size_t)(r0 + ep.row0) * N + n0 + ncol;
+        bytes = rows ? (unsigned)(rows * N - n0 - ncol) * 4u : 0u;
+    }
+    unsigned off[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) off[i] = (unsigned)((16 * i + r16) * rs_len + 4 * g) * 4u;
+    // rotary (cos, sin) of each row's channel pairs 2g, 2g+1 and 8 + 2g, 9 + 2g
+    float2 rc[TM][4];
+    if constexpr (EPI == EPI_QKV_ROPE) {
+        if (part < 2) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                const long mg = (long)min(r0 + 16 * i + r16, M - 1) + ep.row0;
+                const unsigned tt = (unsigned)(mg % ep.T);
+                const unsigned yx = (unsigned)(ep.rY * ep.rX);
+                const int z = (int)(tt / yx), y = (int)((tt / (unsigned)ep.rX) % (unsigned)ep.rY),
+                          x = (int)(tt % (unsigned)ep.rX);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int pr = 8 * (q >> 1) + 2 * g + (q & 1);
+                    const int row = pr < 4 ? z : (pr < 10 ? ep.rZ + y : ep.rZ + ep.rY + x);
+                    rc[i][q] = *(const float2 *)(ep.rope + 2 * (row * 16 + pr));
+                }
+            }
+        }
+    }
+    f32x4 bz[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) bz[j] = *(const f32x4 *)(ep.bias + n0 + ncol + 16 * j + 4 * g);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const RowSpan span(base + (epi_qkv(EPI) ? (j >> 1) * pair : 0), bytes);
+        const __amdgpu_buffer_rsrc_t rs = span.at(epi_qkv(EPI) ? 64 * (j & 1) : 64 * j);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            f32x4 v;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[c] = acc[j][i][c] + bz[j][c];
+            if constexpr (EPI == EPI_QKV_ROPE) {
+                if (part < 2) {
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        const float2 cs = rc[i][2 * (j & 1) + q];
+                        const float a = v[2 * q], b = v[2 * q + 1];
+                        v[2 * q] = fmaf(a, cs.x, -(b * cs.y));
+                        v[2 * q + 1] = fmaf(a, cs.y, b * cs.x);
+                    }
+                }
+            }
+            if constexpr (epi_qkv(EPI)) {
+                if (part == 0) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) v[c] *= om;
+                }
+            }
+            if constexpr (EPI == EPI_GELU) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c] = gelu_as(v[c]);
+            }
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs, off[i], 0, 0);
+        }
+    }
+    }
+}
+
 // The narrow tiles: WGM x WGN waves compute one BM x BN tile, OCC workgroups
 // share a CU, and the activation and weight tiles of each K stage stream
 // through a ring of D slots, D - 1 stages ahead of the MFMAs.
-template <int BM, int BN, int D, int WGM, int WGN, int OCC, int EPI, bool FP8, bool PERM>
+enum OperandType : int { T_BF16 = 0, T_E4M3 = 1, T_F32 = 2 };
+template <int BM, int BN, int D, int WGM, int WGN, int OCC, int EPI, int TY, bool PERM>
 __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const void *__restrict__ A, const void *__restrict__ W,
                                                          int M, int N, int K, EpiArgs ep, int, int) {
 #if defined(__HIP_DEVICE_COMPILE__)   // LDS-address-space builtins exist only in the device pass
     constexpr int BKB = 128;
+    constexpr bool FP8 = TY == T_E4M3, F32 = TY == T_F32;
+    constexpr bool HALVES = FP8 || F32;            // a lane's 32 bytes of a row: chunks 2 g and 2 g + 1
     constexpr int NW = WGM * WGN;
     constexpr int WM = BM / WGM, WN = BN / WGN;
     constexpr int TM = WM / 16, TN = WN / 16;
@@ -542,7 +688,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WGM, wn = wave / WGM;
     const int g = lane >> 4, r16 = lane & 15;
-    const unsigned Kb = (unsigned)K * (FP8 ? 1 : 2);
+    const unsigned Kb = (unsigned)K * (F32 ? 4 : (FP8 ? 1 : 2));
     const __amdgpu_buffer_rsrc_t ars = make_rsrc(A, (unsigned)M * Kb);
     const __amdgpu_buffer_rsrc_t wrs = make_rsrc(W, (unsigned)N * Kb);
 
@@ -552,12 +698,12 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
 #pragma unroll
     for (int i = 0; i < LPA; ++i) {
         const int row = 8 * (wave + NW * i) + (lane >> 3);
-        voa[i] = (unsigned)(m0 + row) * Kb + (((lane & 7) ^ swz<FP8>(row)) << 4);
+        voa[i] = (unsigned)(m0 + row) * Kb + (((lane & 7) ^ swz<HALVES>(row)) << 4);
     }
 #pragma unroll
     for (int i = 0; i < LPB; ++i) {
         const int row = 8 * (wave + NW * i) + (lane >> 3);
-        vob[i] = (unsigned)(n0 + row) * Kb + (((lane & 7) ^ swz<FP8>(row)) << 4);
+        vob[i] = (unsigned)(n0 + row) * Kb + (((lane & 7) ^ swz<HALVES>(row)) << 4);
     }
     const int nk = (int)(Kb / BKB);
     int lslot = 0;
@@ -578,7 +724,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
     int aoff[2], woff[2];
 #pragma unroll
     for (int o = 0; o < 2; ++o) {
-        const int pc = (FP8 ? 2 * g + o : 4 * o + g) ^ swz<FP8>(r16);
+        const int pc = (HALVES ? 2 * g + o : 4 * o + g) ^ swz<HALVES>(r16);
         aoff[o] = (wm * WM + r16) * BKB + (pc << 4);
         woff[o] = BM * BKB + (wn * WN + r16) * BKB + (pc << 4);
     }
@@ -619,6 +765,22 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
             for (int j = 0; j < TN; ++j)
 #pragma unroll
                 for (int i = 0; i < TM; ++i) acc[j][i] = mma_fp8<FIRST, SWAP>(w[j], a[i], acc[j][i]);
+        } else if constexpr (F32) {
+            Split3 as[TM];
+#pragma unroll
+            for (int i = 0; i < TM; ++i) as[i] = split3(a[i]);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const Split3 ws = split3(w[j]);
+                // (part of W, part of A), smallest products first
+                constexpr int pw[6] = {2, 0, 1, 1, 0, 0}, pa[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+                for (int t = 0; t < 6; ++t)
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+                        acc[j][i] = t == 0 ? mma_bf16<FIRST, false>(ws.p[pw[t]], as[i].p[pa[t]], acc[j][i])
+                                           : mma_bf16<false, false>(ws.p[pw[t]], as[i].p[pa[t]], acc[j][i]);
+            }
         } else {
 #pragma unroll
             for (int j = 0; j < TN; ++j)
@@ -633,7 +795,18 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
     };
     stage(std::true_type{}, 0);
     for (int kt = 1; kt < nk; ++kt) stage(std::false_type{}, kt);
-    if constexpr (epi_resid_ln(EPI)) {
+    if constexpr (F32) {
+        bool bad = false;
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) bad |= !__builtin_isfinite(acc[j][i][c]);
+        if (__builtin_amdgcn_ballot_w64(bad))
+            f32_tiles<TM, TN>((const float *)A, (const float *)W, M, K, m0 + wm * WM, n0 + wn * WN, g, r16, acc);
+        tile_epilogue_f32<EPI, TM, TN>(ep, M, N, m0 + wm * WM, n0, wn * WN, g, r16, acc);
+    } else if constexpr (epi_resid_ln(EPI)) {
         static_assert((2 * WGN * BM + 2 * BN) * 4 <= SLOT && BN <= 2 * NW * 64, "row sums and ln_g, ln_b fit a slot");
         resid_ln_epilogue<TM, TN, WGN, BM, FP8, EPI == EPI_RESID_LN_SPLIT>(ep, M, N, m0, wm * WM, wn, wn * WN, g, r16, tid, NW * 64,
                                                                            acc, (float *)smem);
@@ -643,7 +816,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
         tile_epilogue<EPI, FP8, PERM, TM, TN>(ep, M, N, m0 + wm * WM, n0, wn * WN, g, r16, acc, [] {});
     }
     };
-    if constexpr (epi_qkv(EPI)) {
+    if constexpr (epi_qkv(EPI) && !F32) {
         if (ep.vt && n0 >= 2 * ep.C) {
             body(std::true_type{});
             return;
@@ -973,6 +1146,17 @@ inline hipError_t launch_chunks(gemm_fn kernel, int BM, int BN, int nth, size_t 
 // The instantiation of a kernel family F for an epilogue kind: permuted W
 // rows (perm) exist for the QKV and GELU epilogues, rotary only with them.
 template <typename F>
+inline gemm_fn pick_natural(EpiKind epi, const EpiArgs &ep) {
+    switch (epi) {
+    case EPI_QKV: return F::template get<EPI_QKV, false>();
+    case EPI_QKV_ROPE: return F::template get<EPI_QKV_ROPE, false>();
+    case EPI_GELU: return F::template get<EPI_GELU, false>();
+    case EPI_RESID: return splits(ep) ? F::template get<EPI_RESID_SPLIT, false>() : F::template get<EPI_RESID, false>();
+    case EPI_STORE: return F::template get<EPI_STORE, false>();
+    default: return nullptr;
+    }
+}
+template <typename F>
 inline gemm_fn pick(EpiKind epi, const EpiArgs &ep) {
     const int perm = ep.perm;
     switch (epi) {
@@ -995,13 +1179,13 @@ inline gemm_fn with_lds(K kernel) {
                ? (gemm_fn)kernel : nullptr;
 }
 
-template <int BM, int BN, int D, int WGM, int WGN, int OCC, bool FP8>
+template <int BM, int BN, int D, int WGM, int WGN, int OCC, int TY>
 struct LdsGemm {
     static constexpr size_t lds = (size_t)D * (BM + BN) * 128;
     static_assert(lds * OCC <= 160 * 1024, "LDS per CU");
     template <int EPI, bool PERM>
     static gemm_fn get() {
-        static const gemm_fn f = with_lds<lds>(gemm_lds_kernel<BM, BN, D, WGM, WGN, OCC, EPI, FP8, PERM>);
+        static const gemm_fn f = with_lds<lds>(gemm_lds_kernel<BM, BN, D, WGM, WGN, OCC, EPI, TY, PERM>);
         return f;
     }
 };
@@ -1031,7 +1215,7 @@ hipError_t launch_tiles(const void *A, const void *W, int M, int N, int K, EpiKi
     // and a workgroup's must be all V or none when V goes to the blocked layout
     const bool n256 = N % 256 == 0 && (!epi_qkv(epi) || ep.C % 256 == 0);
     const int wmax = epi_qkv(epi) && ep.vt ? ((ep.C / 256) % 2 ? 1 : 2) : wide_max(N);
-    const TilePlan t = plan_tiles(M, N, (int)(row_bytes / 128), n256, wmax);
+    const TilePlan t = N % 128 == 0 ? plan_tiles(M, N, (int)(row_bytes / 128), n256, wmax) : TilePlan{64, 1, 0};
     auto run = [&](auto tag, int BM, int BN, int nth) -> hipError_t {
         typedef decltype(tag) G;
         const gemm_fn f = pick<G>(epi, ep);
@@ -1039,8 +1223,8 @@ hipError_t launch_tiles(const void *A, const void *W, int M, int N, int K, EpiKi
         return launch_chunks(f, BM, BN, nth, G::lds, row_bytes, A, W, M, N, K, ep, t.tpw, t.rw, stream);
     };
     if (t.bm == 256) return run(PpGemm<256, 256, FP8>{}, 256, 256, 512);
-    if (t.bm == 128) return run(LdsGemm<128, 128, 2, 2, 2, 2, FP8>{}, 128, 128, 256);
-    return run(LdsGemm<64, 64, 2, 2, 2, 4, FP8>{}, 64, 64, 256);
+    if (t.bm == 128) return run(LdsGemm<128, 128, 2, 2, 2, 2, FP8 ? T_E4M3 : T_BF16>{}, 128, 128, 256);
+    return run(LdsGemm<64, 64, 2, 2, 2, 4, FP8 ? T_E4M3 : T_BF16>{}, 64, 64, 256);
 }
 
 // EPI_RESID_LN: the tile spans N = 512; one row block per workgroup (the row
@@ -1056,8 +1240,23 @@ hipError_t launch_resid_ln(const void *A, const void *W, int M, int N, int K, co
         if (!f) return hipErrorInvalidValue;
         return launch_chunks(f, BM, 512, 512, G::lds, (size_t)K * (FP8 ? 1 : 2), A, W, M, N, K, ep, 1, 1, stream);
     };
-    if (M <= 64 * 256) return run(LdsGemm<64, 512, 2, 2, 4, 1, FP8>{}, 64);
+    if (M <= 64 * 256) return run(LdsGemm<64, 512, 2, 2, 4, 1, FP8 ? T_E4M3 : T_BF16>{}, 64);
     return run(PpGemm<128, 512, FP8>{}, 128);
+}
+
+// float32: 128 x 128 tiles once they give every CU one, else 64 x 64 (at 276
+// tiles of 128 x 128, M = 2880, N = 1536, K = 512: 52 against 46 us; at 368,
+// N = 2048: 54 against 55; at 816, M = 8640, N = 1536: 101 against 111).
+inline hipError_t launch_f32(const void *A, const void *W, int M, int N, int K, EpiKind epi, const EpiArgs &ep, hipStream_t stream) {
+    auto run = [&](auto tag, int B) -> hipError_t {
+        typedef decltype(tag) G;
+        const gemm_fn f = pick_natural<G>(epi, ep);
+        if (!f) return hipErrorInvalidValue;
+        return launch_chunks(f, B, B, 256, G::lds, (size_t)K * 4, A, W, M, N, K, ep, 1, 0, stream);
+    };
+    const bool n128 = N % 128 == 0 && (!epi_qkv(epi) || ep.C % 128 == 0);
+    if (n128 && (long)((M + 127) / 128) * (N / 128) > 300) return run(LdsGemm<128, 128, 2, 2, 2, 2, T_F32>{}, 128);
+    return run(LdsGemm<64, 64, 2, 2, 2, 4, T_F32>{}, 64);
 }
 
 }  // namespace glds
@@ -1066,7 +1265,7 @@ using namespace glds;
 
 bool gemm_lds_applies(int M, int N, int K) {
     (void)M;
-    return N % 128 == 0 && K % 64 == 0 && (unsigned long long)N * K * 2 < (1ull << 31);
+    return N % 64 == 0 && K % 64 == 0 && (unsigned long long)N * K * 2 < (1ull << 31);
 }
 
 hipError_t launch_gemm_lds(const void *A, const void *W, int M, int N, int K, EpiKind epi, const EpiArgs &ep,
@@ -1077,6 +1276,12 @@ hipError_t launch_gemm_lds(const void *A, const void *W, int M, int N, int K, Ep
         return launch_resid_ln<false>(A, W, M, N, K, ep, stream);
     }
     return launch_tiles<false>(A, W, M, N, K, epi, ep, stream);
+}
+
+hipError_t launch_gemm_f32(const void *A, const void *W, int M, int N, int K, EpiKind epi, const EpiArgs &ep,
+                           hipStream_t stream) {
+    if (ep.perm || ep.vt || ep.out8) return hipErrorInvalidValue;
+    return launch_f32(A, W, M, N, K, epi, ep, stream);
 }
 
 hipError_t launch_gemm_fp8(const void *A, const void *W, int M, int N, int K, EpiKind epi, const EpiArgs &ep,

@@ -140,6 +140,10 @@ hipError_t launch_gemm(const void *A, const void *W, int M, int N, int K, bool a
 bool gemm_lds_applies(int M, int N, int K);
 hipError_t launch_gemm_lds(const void *A, const void *W, int M, int N, int K, EpiKind epi,
                            const EpiArgs &ep, hipStream_t stream);
+// float32 operands on the bf16 matrix cores; needs N % 64 == 0, K % 32 == 0 and
+// W below 2 GiB.
+hipError_t launch_gemm_f32(const void *A, const void *W, int M, int N, int K, EpiKind epi,
+                           const EpiArgs &ep, hipStream_t stream);
 // e4m3 operands (A [M][K], W [N][K] bytes); needs N % 128 == 0, K % 128 == 0.
 hipError_t launch_gemm_fp8(const void *A, const void *W, int M, int N, int K, EpiKind epi,
                            const EpiArgs &ep, hipStream_t stream);

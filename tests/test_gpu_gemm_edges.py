@@ -103,3 +103,66 @@ def test_tile_choice_does_not_show(env, C, shape, prec):
     wm.wm_processor_step(ctx, p, 1, xs)
     assert torch.equal(xb[:1], xs) and torch.equal(xb[3:], xs)
     p.close()
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 64, 32), (63, 192, 96), (65, 128, 64), (129, 384, 32), (700, 512, 2048), (5200, 1024, 160)])
+@pytest.mark.parametrize("epi", [0, 1, 2])
+def test_f32_split(env, M, N, K, epi):
+    """float32 maps run as six bf16 products of three-way split operands, on
+    64- or 128-wide tiles: as exact as float32 arithmetic.  Bound: a sum of K
+    products rounded K / 32 * 6 times, each by at most 2^-24 of a partial sum
+    of at most sqrt(K) |a||w| here: 2^-24 sqrt(6 K / 32), plus 3e-7 for the
+    GELU's erf and 2^-24 for the store; held with a factor of 2."""
+    wm, torch, ctx = env
+    print("f32", M, N, K, epi, flush=True)
+    r = np.random.default_rng(M + N + K + epi)
+    a = torch.from_numpy(r.standard_normal((M, K)).astype(np.float32)).cuda()
+    w = torch.from_numpy((r.standard_normal((N, K)) / np.sqrt(K)).astype(np.float32)).cuda()
+    b = torch.from_numpy((0.1 * r.standard_normal(N)).astype(np.float32)).cuda()
+    x0 = torch.from_numpy(r.standard_normal((M, N)).astype(np.float32)).cuda()
+    out = x0.clone()
+    wm.wm_linear(M, N, K, wm.WM_F32, a, w, b, epi, out)
+    ref = a.double().cpu().numpy() @ w.double().cpu().numpy().T + b.double().cpu().numpy()
+    if epi == 2:
+        ref = x0.double().cpu().numpy() + ref
+    elif epi == 1:
+        ref = O.gelu(ref)
+    tol = 2 * (2.0 ** -24 * (np.sqrt(6 * K / 32) + 1) + (6e-7 if epi == 1 else 0))
+    assert O.rel_l2(out.double().cpu().numpy(), ref) < tol
+    out1 = x0[:1].clone()
+    wm.wm_linear(1, N, K, wm.WM_F32, a, w, b, epi, out1)
+    assert torch.equal(out1, out[:1])
+
+
+@pytest.mark.parametrize("M,N", [(70, 64), (5200, 1024)])
+def test_f32_not_finite(env, M, N):
+    """Infinities, NaN and values next to the largest float32 in the operands
+    give what float32 arithmetic gives: the split's parts alone would give NaN
+    for inf * 1 and for a value that rounds up to infinity in bf16."""
+    wm, torch, ctx = env
+    K = 64
+    print("f32 not finite", M, N, flush=True)
+    r = np.random.default_rng(5)
+    a = r.integers(-4, 5, (M, K)).astype(np.float32)
+    w = r.integers(1, 5, (N, K)).astype(np.float32)
+    big = np.finfo(np.float32).max
+    a[3, 5], a[4, 6], a[5, 7] = np.inf, -np.inf, np.nan
+    a[6] = 0.0
+    a[6, 9] = big
+    w[:, 9] = 1.0                    # row 6: the largest float32 times 1
+    a[7] = big                       # row 7: overflows
+    w[2, 11] = np.inf
+    a[:, 11] = np.abs(a[:, 11]) + 1  # inf times a positive value (NaN and inf rows keep theirs)
+    a[6, 11] = 1.0
+    b = np.zeros(N, np.float32)
+    dev = [torch.from_numpy(t).cuda() for t in (a, w, b)]
+    out = torch.empty((M, N), device="cuda")
+    wm.wm_linear(M, N, K, wm.WM_F32, dev[0], dev[1], dev[2], 0, out)
+    with np.errstate(all="ignore"):
+        ref = a.astype(np.float64) @ w.astype(np.float64).T
+        ref[6] = np.where(np.arange(N) == 2, np.inf, big)      # (+ w[n, 11], far below big's last bit)
+        ref = ref.astype(np.float32)
+    got = out.cpu().numpy()
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    ok = ~np.isnan(ref)
+    assert np.array_equal(got[ok], ref[ok])
