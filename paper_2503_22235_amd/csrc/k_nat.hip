@@ -68,154 +68,215 @@ __device__ __forceinline__ int coord(const Axis &a, int s) {
     return c;
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void nat_generic_kernel(NatArgs p) {
-    const int ngz = (p.Z + GZ - 1) / GZ, ngy = (p.Y + GY - 1) / GY, ngx = (p.X + GX - 1) / GX;
-    const long ngroups = (long)ngz * ngy * ngx;
-    const long total = ngroups * p.H * p.B;
-    const long wid = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (wid >= total) return;
-    const int lane = threadIdx.x & 63, g = lane >> 4, r16 = lane & 15;
+// Vector loads and stores at the element's own alignment (the caller's tensors
+// need no more; the hardware takes any).
+template <typename T, int N>
+struct Vec {
+    typedef T type __attribute__((ext_vector_type(N), aligned(sizeof(T))));
+};
 
-    long t = wid;
-    const int gx = (int)(t % ngx); t /= ngx;
+constexpr int UB = 512;                 // halo units (level, lat, 4 lons) per pass: whole chunks of 8
+constexpr int BIAS_LDS = 8192;          // longest bias table (floats) that is copied to LDS
+
+// A workgroup: four waves, groups of the same levels and lats that follow each
+// other in lon.  The units of their common halo -- 4 lon slots of one (level,
+// lat) -- are listed in LDS, UB at a time, with the offset of their row; so are
+// the lon slots of each wave and the head's bias table.  A key's address is then
+// one addition and a chunk has no divisions or wrap-arounds.  What bounds it:
+// the f32 MFMAs (32 of 32 cycles per chunk) and as many cycles of other
+// instructions beside them.  K is loaded one chunk ahead.  A lane takes V
+// channels 2 r and 2 r + 1 (8 bytes of f32, 4 of bf16), so a key's 32 channels
+// are one run per 16 lanes and a lane's output is 8 consecutive channels.
+// The softmax reference follows the maximum only when it is passed by 2^SLACK;
+// in bf16 at once, so that probabilities are rounded at the same place whatever
+// came before.
+//   FAR: rows beyond 32-bit byte offsets, or too many lon slots for the table:
+//   row and slot hold tokens and the address is computed in 64 bits.
+template <typename T, bool FAR>
+__global__ __launch_bounds__(256, 4) void nat_generic_kernel(NatArgs p, int ngq, int per, int nslot, bool bias_lds) {
+    __shared__ i32x4 unit[UB + 8];                 // row offset, slots on the level and lat axes, first lon slot
+    extern __shared__ __align__(16) float dyn[];                 // [4][nslot] lon offsets (not FAR), then 4 + table + 8 biases
+    const int ngz = (p.Z + GZ - 1) / GZ, ngy = (p.Y + GY - 1) / GY, ngx = (p.X + GX - 1) / GX;
+    const int L = blockIdx.x;
+    long t = (long)(L & 7) * per + (L >> 3);       // XCD-aware: neighbours share an L2
+    if (t >= (long)ngq * ngy * ngz * p.H * p.B) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, g = lane >> 4, r16 = lane & 15;
+    const int gxw = 4 * (int)(t % ngq) + wave; t /= ngq;
     const int gy = (int)(t % ngy); t /= ngy;
     const int gz = (int)(t % ngz); t /= ngz;
     const int h = (int)(t % p.H); t /= p.H;
     const int b = (int)t;
+    const int gx = min(gxw, ngx - 1);
     const int z0 = gz * GZ, y0 = gy * GY, x0 = gx * GX;
 
     const int zq = z0 + (r16 >> 2), yq = y0 + ((r16 >> 1) & 1), xq = x0 + (r16 & 1);
-    const bool active = zq < p.Z && yq < p.Y && xq < p.X;
+    const bool active = gxw < ngx && zq < p.Z && yq < p.Y && xq < p.X;
     const int zc = min(zq, p.Z - 1), yc = min(yq, p.Y - 1), xc = min(xq, p.X - 1);
 
     const Axis az = make_axis(z0, GZ, zc, p.Z, p.Kz, p.periodic & 1);
     const Axis ay = make_axis(y0, GY, yc, p.Y, p.Ky, (p.periodic >> 1) & 1);
     const Axis ax = make_axis(x0, GX, xc, p.X, p.Kx, (p.periodic >> 2) & 1);
-    const int nxp = (ax.n + 3) & ~3;
-    const int nf = az.n * ay.n * nxp;
-    const int nchunk = (nf + 31) >> 5;
-    const int By = 2 * p.Ky - 1, Bx = 2 * p.Kx - 1;
-    const float *rpb = p.rpb + (size_t)h * (2 * p.Kz - 1) * By * Bx;
+    const int nx4 = nslot >> 2;                    // units per (level, lat)
+    const int nunit = az.n * ay.n * nx4;
+    const int By = 2 * p.Ky - 1, Bx = 2 * p.Kx - 1, tbl = (2 * p.Kz - 1) * By * Bx;
+    const float *rpb = p.rpb + (size_t)h * tbl;
+    const int bias0 = (az.boff * By + ay.boff) * Bx + ax.boff;
+    const unsigned tsb = (unsigned)p.ts * (unsigned)sizeof(T);     // (used where offsets fit 32 bits)
 
     const T *qb = (const T *)p.q + (size_t)b * p.bs + (size_t)h * p.hs;
     const T *kb = (const T *)p.k + (size_t)b * p.bs + (size_t)h * p.hs;
     const T *vb = (const T *)p.v + (size_t)b * p.bs + (size_t)h * p.hs;
     const long qtok = ((long)zc * p.Y + yc) * p.X + xc;
 
-    // Q fragment of this lane's query: d in [8g, 8g+8).
-    float qf[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) qf[e] = Elt<T>::ld(qb + qtok * p.ts + 8 * g + e);
+    typedef typename Vec<T, 8>::type T8;
+    typedef typename Vec<T, 2>::type T2;
+    const T8 qf = *(const T8 *)(qb + qtok * p.ts + 8 * g);    // channels 8g .. of this lane's query
 
+    unsigned *lons = (unsigned *)dyn + wave * nslot;
+    float *bias_s = dyn + (FAR ? 0 : 4 * nslot) + 4;
+    // lon of slot s (a slot past the halo: slot 0's, a key of the halo; its score is masked)
+    auto lon = [&](int s) { return coord(ax, s < ax.n ? s : 0); };
+    if constexpr (!FAR)
+        for (int e = lane; e < nslot; e += 64) lons[e] = (unsigned)lon(e) * tsb;
+    if (bias_lds)
+        for (int e = (int)threadIdx.x - 4; e < tbl + 8; e += 256)
+            bias_s[e] = e >= 0 && e < tbl ? rpb[e] * p.bscale : 0.f;
+    auto load_k = [&](unsigned off, int slot) {
+        if constexpr (FAR) return *(const T8 *)(kb + (long)((int)off + lon(slot)) * p.ts + 8 * g);
+        else return *(const T8 *)((const char *)kb + (off + lons[slot] + 8u * g * (unsigned)sizeof(T)));
+    };
+
+    constexpr float SLACK = sizeof(T) == 2 ? 0.f : 8.f;
     const float NEG = -INFINITY;
     float m_run = -1e30f, l_run = 0.f;
     f32x4 o0 = {0.f, 0.f, 0.f, 0.f}, o1 = {0.f, 0.f, 0.f, 0.f};
 
-    for (int c = 0; c < nchunk; ++c) {
-        f32x4 sacc[2];
-        long ktok[2][4];
-        bool kval[2][4];
-        // ---- scores S^T = K . Q^T ----
+    for (int ub = 0; ub < nunit; ub += UB) {
+        const int nu = min(UB, nunit - ub), nchunk = (nu + 7) >> 3;
+        if (ub > 0) __syncthreads();
+        for (int e = threadIdx.x; e < 8 * nchunk; e += 256) {
+            const int u = min(ub + e, nunit - 1), row = u / nx4;
+            const int sz = row / ay.n, sy = row - sz * ay.n;
+            const unsigned tok = (unsigned)(coord(az, sz) * p.Y + coord(ay, sy)) * (unsigned)p.X;
+            unit[e] = i32x4{(int)(FAR ? tok : tok * tsb), e < nu ? sz : 0x3fffffff, sy, 4 * (u - row * nx4)};
+        }
+        __syncthreads();
+        T8 kn[2];
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            // MFMA A operand: key row f_a = 32c + 16j + r16, d in [8g, 8g+8)
-            const int fa = 32 * c + 16 * j + r16;
-            float kf[8];
-            bool ok = fa < nf;
-            long kt = 0;
-            if (ok) {
-                const int sx = fa % nxp, rest = fa / nxp;
-                const int sy = rest % ay.n, sz = rest / ay.n;
-                ok = sx < ax.n;
-                kt = ((long)coord(az, sz) * p.Y + coord(ay, sy)) * p.X + coord(ax, sx);
-            }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) kf[e] = ok ? Elt<T>::ld(kb + kt * p.ts + 8 * g + e) : 0.f;
-            sacc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if constexpr (sizeof(T) == 2) {
-                bf16x8 av, bv;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) { av[e] = f2bf(kf[e]); bv[e] = f2bf(qf[e]); }
-                sacc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, sacc[j], 0, 0, 0);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    sacc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[e], qf[e], sacc[j], 0, 0, 0);
-            }
+            const i32x4 u = unit[4 * j + (r16 >> 2)];
+            kn[j] = load_k((unsigned)u[0], u[3] + (r16 & 3));
         }
-        // ---- mask + bias on this lane's 8 keys: f = 32c + 16j + 4g + i ----
-        float s[2][4];
-        float cmax = NEG;
+        for (int c = 0; c < nchunk; ++c) {
+            const T8 kf[2] = {kn[0], kn[1]};
+            // keys f = 32 c + 16 j + 4 g + i of this lane: V, bias and window
+            T2 vv[2][4];
+            float bias[2][4];
+            int xw[2];                             // lon slot in the window; beyond it where level or lat are
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int f0 = 32 * c + 16 * j + 4 * g;
-            const bool qok = f0 < nf;
-            const int sx0 = f0 % nxp, rest = f0 / nxp;
-            const int sy = rest % ay.n, sz = rest / ay.n;
-            const bool zyok = qok && (unsigned)(sz - az.ws) < (unsigned)p.Kz &&
-                              (unsigned)(sy - ay.ws) < (unsigned)p.Ky;
-            const long rowtok = ((long)coord(az, sz) * p.Y + coord(ay, sy)) * p.X;
-            const int bzy = ((sz + az.boff) * By + (sy + ay.boff)) * Bx;
+            for (int j = 0; j < 2; ++j) {
+                const i32x4 u = unit[8 * c + 4 * j + g];
+                const bool zyok = (unsigned)(u[1] - az.ws) < (unsigned)p.Kz && (unsigned)(u[2] - ay.ws) < (unsigned)p.Ky;
+                xw[j] = zyok ? u[3] - ax.ws : 0x3fffffff;
+                const int bo = zyok ? (u[1] * By + u[2]) * Bx + u[3] + bias0 : 0;
+                if constexpr (FAR) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int sx = sx0 + i;
-                // The key exists in the halo (its V row feeds every query of
-                // the group through the P.V product) ...
-                const bool exists = qok && sx < ax.n;
-                kval[j][i] = exists;
-                ktok[j][i] = exists ? rowtok + coord(ax, sx) : qtok;
-                // ... but only scores inside this lane's window count.
-                const bool ok = zyok && sx < ax.n && (unsigned)(sx - ax.ws) < (unsigned)p.Kx;
-                const float bias = ok ? rpb[bzy + sx + ax.boff] : 0.f;
-                s[j][i] = ok ? fmaf(sacc[j][i], p.qscale, bias * p.bscale) : NEG;
-                cmax = fmaxf(cmax, s[j][i]);
+                    for (int i = 0; i < 4; ++i)
+                        vv[j][i] = *(const T2 *)(vb + (long)(u[0] + lon(u[3] + i)) * p.ts + 2 * r16);
+                } else {
+                    const i32x4 x = *(const i32x4 *)(lons + u[3]);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        vv[j][i] = *(const T2 *)((const char *)vb +
+                                                 ((unsigned)u[0] + (unsigned)x[i] + 2u * r16 * (unsigned)sizeof(T)));
+                }
+                if (bias_lds) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) bias[j][i] = bias_s[bo + i];
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) bias[j][i] = rpb[max(0, min(bo + i, tbl - 1))] * p.bscale;
+                }
             }
-        }
-        cmax = fmaxf(cmax, __shfl_xor(cmax, 16, 64));
-        cmax = fmaxf(cmax, __shfl_xor(cmax, 32, 64));
-        const float m_new = fmaxf(m_run, cmax);
-        const float alpha = exp2f(m_run - m_new);
-        m_run = m_new;
-        float pv[2][4];
-        float psum = 0.f;
+            if (c + 1 < nchunk) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                pv[j][i] = exp2f(s[j][i] - m_new);
-                psum += pv[j][i];
+                for (int j = 0; j < 2; ++j) {
+                    const i32x4 u = unit[8 * c + 8 + 4 * j + (r16 >> 2)];
+                    kn[j] = load_k((unsigned)u[0], u[3] + (r16 & 3));
+                }
             }
-        l_run = l_run * alpha + psum;
+            // ---- scores S^T = K . Q^T ----
+            f32x4 sacc[2];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { o0[i] *= alpha; o1[i] *= alpha; }
-        // ---- O^T += V^T . P^T ----
+            for (int j = 0; j < 2; ++j) {
+                sacc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if constexpr (sizeof(T) == 2) {
+                    sacc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[j]),
+                                                                      __builtin_bit_cast(bf16x8, qf), sacc[j], 0, 0, 0);
+                } else {
 #pragma unroll
-        for (int tt = 0; tt < 2; ++tt) {
-            const int dcol = 16 * tt + r16;
-            float vf[2][4];
+                    for (int e = 0; e < 8; ++e)
+                        sacc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][e], qf[e], sacc[j], 0, 0, 0);
+                }
+            }
+            // ---- mask + bias, online softmax ----
+            float s[2][4];
+            float cmax = NEG;
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    vf[j][i] = kval[j][i] ? Elt<T>::ld(vb + ktok[j][i] * p.ts + dcol) : 0.f;
-            f32x4 &o = tt ? o1 : o0;
+                for (int i = 0; i < 4; ++i) {
+                    const bool ok = (unsigned)(xw[j] + i) < (unsigned)p.Kx;
+                    s[j][i] = ok ? fmaf(sacc[j][i], p.qscale, bias[j][i]) : NEG;
+                    cmax = fmaxf(cmax, s[j][i]);
+                }
+            float alpha = 1.f;
+            if (__builtin_amdgcn_ballot_w64(cmax > m_run + SLACK)) {
+                cmax = fmaxf(cmax, __shfl_xor(cmax, 16, 64));
+                cmax = fmaxf(cmax, __shfl_xor(cmax, 32, 64));
+                const float m_new = fmaxf(m_run, cmax);
+                alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+                m_run = m_new;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { o0[i] *= alpha; o1[i] *= alpha; }
+            }
+            float pv[2][4];
+            float psum = 0.f;
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    pv[j][i] = __builtin_amdgcn_exp2f(s[j][i] - m_run);
+                    psum += pv[j][i];
+                }
+            l_run = fmaf(l_run, alpha, psum);
+            // ---- O^T += V^T . P^T ----
             if constexpr (sizeof(T) == 2) {
-                bf16x8 av, bv;
+                uint4 v0, v1;
+                bf16x8 pw;
+                unsigned d[8];
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        av[4 * j + i] = f2bf(vf[j][i]);
-                        bv[4 * j + i] = f2bf(pv[j][i]);
+                        d[4 * j + i] = __builtin_bit_cast(unsigned, vv[j][i]);
+                        pw[4 * j + i] = f2bf(pv[j][i]);
                     }
-                o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, o, 0, 0, 0);
+                v0 = make_uint4(__builtin_amdgcn_perm(d[1], d[0], 0x05040100u), __builtin_amdgcn_perm(d[3], d[2], 0x05040100u),
+                                __builtin_amdgcn_perm(d[5], d[4], 0x05040100u), __builtin_amdgcn_perm(d[7], d[6], 0x05040100u));
+                v1 = make_uint4(__builtin_amdgcn_perm(d[1], d[0], 0x07060302u), __builtin_amdgcn_perm(d[3], d[2], 0x07060302u),
+                                __builtin_amdgcn_perm(d[5], d[4], 0x07060302u), __builtin_amdgcn_perm(d[7], d[6], 0x07060302u));
+                o0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, v0), pw, o0, 0, 0, 0);
+                o1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, v1), pw, o1, 0, 0, 0);
             } else {
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        o = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[j][i], pv[j][i], o, 0, 0, 0);
+                    for (int i = 0; i < 4; ++i) {
+                        o0 = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[j][i][0], pv[j][i], o0, 0, 0, 0);
+                        o1 = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[j][i][1], pv[j][i], o1, 0, 0, 0);
+                    }
             }
         }
     }
@@ -223,12 +284,18 @@ __global__ __launch_bounds__(256) void nat_generic_kernel(NatArgs p) {
     l_tot += __shfl_xor(l_tot, 32, 64);
     const float inv = 1.0f / l_tot;
     if (active) {
-        T *ob = (T *)p.out + (size_t)b * p.obs + (size_t)qtok * p.ots + h * 32;
+        T8 o;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            Elt<T>::st(ob + 4 * g + i, o0[i] * inv);
-            Elt<T>::st(ob + 16 + 4 * g + i, o1[i] * inv);
+            if constexpr (sizeof(T) == 2) {
+                o[2 * i] = f2bf(o0[i] * inv);
+                o[2 * i + 1] = f2bf(o1[i] * inv);
+            } else {
+                o[2 * i] = o0[i] * inv;
+                o[2 * i + 1] = o1[i] * inv;
+            }
         }
+        *(T8 *)((T *)p.out + (size_t)b * p.obs + (size_t)qtok * p.ots + h * 32 + 8 * g) = o;
     }
 }
 
@@ -247,12 +314,20 @@ hipError_t launch_nat(const NatArgs &a, bool bf16in, hipStream_t stream) {
 
 hipError_t launch_nat_generic(const NatArgs &a, bool bf16in, hipStream_t stream) {
     if (a.vt || a.q8 || a.o8) return hipErrorInvalidValue;     // reads token-major bf16/f32 q, k, v only
-    const long ngroups = (long)((a.Z + GZ - 1) / GZ) * ((a.Y + GY - 1) / GY) * ((a.X + GX - 1) / GX);
-    const long waves = ngroups * a.H * a.B;
-    if (waves == 0) return hipSuccess;
-    const unsigned grid = (unsigned)((waves + 3) / 4);
-    if (bf16in) nat_generic_kernel<bf16><<<grid, 256, 0, stream>>>(a);
-    else nat_generic_kernel<float><<<grid, 256, 0, stream>>>(a);
+    const int ngq = ((a.X + GX - 1) / GX + 3) / 4;      // workgroups of four lon groups
+    const long total = (long)((a.Z + GZ - 1) / GZ) * ((a.Y + GY - 1) / GY) * ngq * a.H * a.B;
+    if (total == 0) return hipSuccess;
+    const int per = (int)((total + 7) / 8);
+    const unsigned grid = (unsigned)per * 8u;
+    const int nslot = (GX + a.Kx - 1 + 3) & ~3;
+    const long tbl = (long)(2 * a.Kz - 1) * (2 * a.Ky - 1) * (2 * a.Kx - 1);
+    const size_t span = (size_t)a.Z * a.Y * a.X * (size_t)a.ts * (bf16in ? 2 : 4);
+    const bool far = span >= (1ull << 32) || nslot > 1024;
+    const bool bias_lds = tbl <= BIAS_LDS;
+    const size_t lds = (far ? 0 : 16 * (size_t)nslot) + (bias_lds ? 4 * (size_t)(tbl + 12) : 0);
+    auto go = [&](auto kernel) { kernel<<<grid, 256, lds, stream>>>(a, ngq, per, nslot, bias_lds); };
+    if (bf16in) far ? go(nat_generic_kernel<bf16, true>) : go(nat_generic_kernel<bf16, false>);
+    else far ? go(nat_generic_kernel<float, true>) : go(nat_generic_kernel<float, false>);
     return hipGetLastError();
 }
 
