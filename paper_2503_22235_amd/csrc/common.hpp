@@ -60,13 +60,17 @@ __device__ __forceinline__ float xsum16_32(float v) {
 }
 
 // Four floats -> four OCP e4m3 codes (byte i = value i), round to nearest
-// even, saturated at +-448 (the gfx950 conversion instruction rounds; the
-// clamp keeps out-of-range values finite).
+// even; the values are within +-448 or the result does not matter.  (The
+// first conversion keeps the upper half of a register it is given: one that
+// dies here, so that none has to be cleared.)
+__device__ __forceinline__ unsigned e4m3x4_inrange(float a, float b, float c, float d) {
+    const int w = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, __float_as_int(b), false);
+    return (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(c, d, w, true);
+}
+// The same, saturated at +-448 (a NaN becomes -448).
+__device__ __forceinline__ float clamp448(float v) { return __builtin_amdgcn_fmed3f(v, -448.0f, 448.0f); }
 __device__ __forceinline__ unsigned e4m3x4(float a, float b, float c, float d) {
-    const unsigned w = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(fminf(fmaxf(a, -448.0f), 448.0f),
-                                                                  fminf(fmaxf(b, -448.0f), 448.0f), 0, false);
-    return (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(fminf(fmaxf(c, -448.0f), 448.0f),
-                                                     fminf(fmaxf(d, -448.0f), 448.0f), (int)w, true);
+    return e4m3x4_inrange(clamp448(a), clamp448(b), clamp448(c), clamp448(d));
 }
 
 // Loads/stores of element type T as float.

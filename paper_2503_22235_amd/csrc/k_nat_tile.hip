@@ -41,16 +41,24 @@ namespace {
 constexpr int TZ = 4, TY = 4, TX = 8;    // query tile
 constexpr int GX = 2;                     // group lon extent
 constexpr int XW = 16;                    // halo lon extent, padded (>= TX + Kx - 1)
-constexpr int XT = 9;                     // bias table lon extent: hx - xq_rel + 1
+constexpr int XT = 16;                    // bias table row: 8 lon slots for the even, 8 for the odd query of a pair
 constexpr float TAU = 8.0f;               // lazy rescale threshold (log2 units)
 constexpr int LD_BATCH = 4;               // halo items loaded before they are stored
-constexpr int NEG_RUN = 64;               // -inf entries after the bias table (>= 6 XT + 4)
+constexpr int NEG_RUN = 100;              // -inf entries after the bias table (>= 6 XT + 4)
 constexpr int YR_MIN = 10;                // lat rows per level slab a chunk walk may read (2 + 8)
 
 __device__ __forceinline__ void clamp_range(int a0, int tsize, int N, int K, int &lo, int &n) {
     const int last = min(a0 + tsize - 1, N - 1);
     lo = win_start(a0, N, K, false);
     n = win_start(last, N, K, false) + K - lo;
+}
+
+// Whether all 8 values are finite (the maximum of the magnitudes keeps a NaN).
+__device__ __forceinline__ bool all_finite(f32x4 a, f32x4 b) {
+    float m = max3f(fabsf(a[0]), fabsf(a[1]), fabsf(a[2]));
+    m = max3f(m, fabsf(a[3]), fabsf(b[0]));
+    m = max3f(m, fabsf(b[1]), fabsf(b[2]));
+    return max3f(m, fabsf(b[3]), 0.f) < INFINITY;
 }
 
 // The workgroup's base pointer, held in scalar registers (it is uniform;
@@ -78,9 +86,9 @@ __device__ __forceinline__ float xmax16_32(float v) {
 struct TileDiv { unsigned mx, my, mz, mh; };
 __device__ __forceinline__ unsigned mdiv(unsigned t, unsigned m) { return m ? __umulhi(t, m) : t; }
 inline unsigned div_magic(unsigned d) { return d <= 1 ? 0u : (unsigned)(((1ull << 32) + d - 1) / d); }
-inline TileDiv tile_div(const NatArgs &a) {
+inline TileDiv tile_div(const NatArgs &a, int heads = 1) {
     return TileDiv{div_magic((a.X + TX - 1) / TX), div_magic((a.Y + TY - 1) / TY), div_magic((a.Z + TZ - 1) / TZ),
-                   div_magic(a.H)};
+                   div_magic(a.H / heads)};
 }
 
 // QSCALED: q already carries the factor log2(e)/sqrt(d) (the block path folds
@@ -89,10 +97,12 @@ inline TileDiv tile_div(const NatArgs &a) {
 template <int KZ, int KY, int KX>
 constexpr int tbl_padded() { return ((2 * KZ - 1) * (2 * KY - 1) * XT + NEG_RUN + 3) & ~3; }
 
-// Per-head bias table in the layout the tile kernel reads: tbl[iz][iy][ixt]
-// (ixt = key lon slot - query lon slot + 1), lon validity folded in as
-// -inf, followed by a run of NEG_RUN entries of -inf that masked (level,
-// lat) rows read.
+// Per-head bias table in the layout the tile kernels read: tbl[iz][iy][x][hx]
+// for the key in lon slot hx of the halo of a query pair and its query x, lon
+// validity folded in as -inf, followed by a run of NEG_RUN entries of -inf that
+// masked (level, lat) rows read.  A lane's four keys are one aligned 16-byte
+// read whichever its query (one row of 9 entries for both queries took four
+// reads that met in the same banks).
 template <int KZ, int KY, int KX, bool QSCALED>
 __global__ void nat_bias_prep(NatArgs p) {
     constexpr int RX = (KX - 1) / 2, BY = 2 * KY - 1, BZ = 2 * KZ - 1;
@@ -104,7 +114,7 @@ __global__ void nat_bias_prep(NatArgs p) {
     float v = -INFINITY;
     if (i < TBL) {
         const int ixt = i % XT, rest = i / XT;
-        const int dx = ixt - 1 - RX;
+        const int dx = (ixt & 7) - (ixt >> 3) - RX;
         if (dx >= -RX && dx <= RX) v = p.rpb[((size_t)h * BZ * BY + rest) * (2 * KX - 1) + dx + KX - 1] * bs;
     }
     p.tbl_ws[e] = v;
@@ -227,7 +237,7 @@ __global__ __launch_bounds__(256, 2) void nat_tile_kernel(NatArgs p, int ZWmax, 
 #pragma unroll
         for (int j = 0; j < 2; ++j)
             oky[hf][j] = (unsigned)(4 * hf + j + 2 * (g >> 1) - wy) < (unsigned)KY;
-    const int tb_lane = (zb * BY + yb + 2 * (g >> 1)) * XT + 4 * (g & 1) - xrel + 1;
+    const int tb_lane = (zb * BY + yb + 2 * (g >> 1)) * XT + 8 * xrel + 4 * (g & 1);
 
     // K operand: key 16j + r16 = lat row 4hf + j + 2 (r16 >> 3), lon column
     // r16 & 7 of the group halo, from global memory (byte offsets within level
@@ -275,7 +285,7 @@ __global__ __launch_bounds__(256, 2) void nat_tile_kernel(NatArgs p, int ZWmax, 
     }
     __syncthreads();     // V halo (and table) in LDS
     {
-        const float tcenter = tbl[((KZ - 1) * BY + KY - 1) * XT + 1 + RX];   // bias at offset (0, 0, 0)
+        const float tcenter = tbl[((KZ - 1) * BY + KY - 1) * XT + RX];   // bias at offset (0, 0, 0)
 #pragma unroll
         for (int G = 0; G < 2; ++G) mref[G] = QSCALED ? mref[G] + tcenter : (mref[G] + tcenter) * p.qscale;
     }
@@ -328,8 +338,7 @@ __global__ __launch_bounds__(256, 2) void nat_tile_kernel(NatArgs p, int ZWmax, 
                 for (int j = 0; j < 2; ++j) {
                     const int a = (okz && oky[hf][j]) ? tbh : TBL;
                     const float *tp = tbl + a + (4 * hf + j) * XT;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) binit[j][i] = tp[i];
+                    binit[j] = *(const f32x4 *)tp;
                 }
                 bf16x8 pb[2];
 #pragma unroll
@@ -390,9 +399,7 @@ __global__ __launch_bounds__(256, 2) void nat_tile_kernel(NatArgs p, int ZWmax, 
                 for (int j = 0; j < 2; ++j) {
                     const int a = (okz && oky[hf][j]) ? tbh : TBL;
                     const float *tp = tbl + a + (4 * hf + j) * XT;
-                    f32x4 bi;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) bi[i] = tp[i];
+                    const f32x4 bi = *(const f32x4 *)tp;
 #pragma unroll
                     for (int G = 0; G < 2; ++G) {
                         const bf16x8 kf = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
@@ -431,18 +438,32 @@ __global__ __launch_bounds__(256, 2) void nat_tile_kernel(NatArgs p, int ZWmax, 
 // written by direct buffer -> LDS loads (5 per wave per level); two level
 // slots alternate, so level hz+1 loads while level hz is computed, and the
 // only vector-memory loads in the walk are those, so a full wait and one
-// barrier per level order them.  45 KB of LDS per workgroup: three
+// barrier per level order them.  49 KB of LDS per workgroup: three
 // workgroups share a CU.  K rows are token-major with the 16-byte channel
 // chunks of token c (halo column) of row R stored at chunk position
 // q ^ kswz(R, c), so the 16 lanes of a fragment read hit distinct banks.
 // Arithmetic, key order and softmax reference are those of nat_tile_kernel.
+//
+// A workgroup walks nh heads (heads_per_workgroup) over the same tile: the
+// addresses are worked out once, the levels follow each other without a gap
+// and the table, the queries and their own keys of the next head load while
+// the last one's output is written.  Tiles go lon, level, lat: the two level
+// tiles of a place share most of their halo in L2.
+//
+// Measured at 8x90x180 tokens, 16 heads, window 5x7x7: from head-major q and k
+// 300 -> 280 us, from token-major ones 368 -> 335 us (byte floor 103 us).  With
+// the loads left out the walk takes 210 us, with the arithmetic left out 240:
+// matrix instructions, exponentials (a quarter of the rate each) and LDS reads
+// are each busy half the time, in turn rather than together.  Tried without
+// gain: 8 waves over 8 lats (fewer loads, 4 waves per SIMD), the level's reads
+// all ahead of its scores, a prefetch of the next levels into L2.
 constexpr int RING_ROWS = YR_MIN;              // lat rows per level (>= TY + KY - 1)
 constexpr int RING_SLOT = 2 * RING_ROWS * 1024;   // K rows, then V rows
 
 __device__ __forceinline__ int kswz(int R, int c) { return ((c >> 2) & 1) | (((R >> 1) & 1) << 1); }
 
 template <int KZ, int KY, int KX, bool QSCALED>
-__global__ __launch_bounds__(256, 3) void nat_ring_kernel(NatArgs p, TileDiv dm) {
+__global__ __launch_bounds__(256, 3) void nat_ring_kernel(NatArgs p, TileDiv dm, int nh) {
     constexpr int RX = (KX - 1) / 2;
     constexpr int BY = 2 * KY - 1;
     constexpr int TBL = (2 * KZ - 1) * BY * XT;
@@ -456,16 +477,17 @@ __global__ __launch_bounds__(256, 3) void nat_ring_kernel(NatArgs p, TileDiv dm)
 
     const int ntz = (p.Z + TZ - 1) / TZ, nty = (p.Y + TY - 1) / TY, ntx = (p.X + TX - 1) / TX;
     const int ntiles = ntz * nty * ntx;
-    const int total = ntiles * p.H * p.B;
+    const int nhg = p.H / nh;                       // head groups: this workgroup walks nh heads
+    const int total = ntiles * nhg * p.B;
     const int per = (total + 7) >> 3;
     const int L = blockIdx.x;
     const int id = (L & 7) * per + (L >> 3);
     if (id >= total) return;
     unsigned t = (unsigned)id, q;
     q = mdiv(t, dm.mx); const int tx = (int)(t - q * (unsigned)ntx); t = q;
-    q = mdiv(t, dm.my); const int ty = (int)(t - q * (unsigned)nty); t = q;
     q = mdiv(t, dm.mz); const int tz = (int)(t - q * (unsigned)ntz); t = q;
-    q = mdiv(t, dm.mh); const int h = (int)(t - q * (unsigned)p.H);
+    q = mdiv(t, dm.my); const int ty = (int)(t - q * (unsigned)nty); t = q;
+    q = mdiv(t, dm.mh); int h = nh * (int)(t - q * (unsigned)nhg);
     const int b = (int)q;
     const int z0 = tz * TZ, y0 = ty * TY;
     const int x0 = tx * TX - SX;
@@ -475,53 +497,64 @@ __global__ __launch_bounds__(256, 3) void nat_ring_kernel(NatArgs p, TileDiv dm)
     clamp_range(z0, TZ, p.Z, KZ, zlo, zn);
     clamp_range(y0, TY, p.Y, KY, ylo, yn);
 
-    const bf16 *kb = (const bf16 *)p.k + (size_t)b * p.bs + (size_t)h * p.hs;
-    const bf16 *qb = (const bf16 *)p.q + (size_t)b * p.bs + (size_t)h * p.hs;
+    const bf16 *kb = (const bf16 *)p.k + (size_t)b * p.bs;
+    const bf16 *qb = (const bf16 *)p.q + (size_t)b * p.bs;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     // ---- level staging: row r = wave + 4 u (u < 5) of the 20 (K rows 0..9,
-    // V rows 10..19); rows past the halo repeat its last lat row ----
+    // V rows 10..19); rows past the halo repeat its last lat row.  A row's
+    // offset within its level does not change with level or head ----
     const unsigned tsb = (unsigned)p.ts * 2u;       // token stride, bytes
-    const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(kb), 0, 0x7ffffffe, 0x00020000);
     const size_t plane = (size_t)p.Z * p.Y * p.xp * 64;
-    const unsigned char *vp = (const unsigned char *)p.v + ((size_t)h * p.B + b) * plane;
-    const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(vp), 0, (unsigned)plane, 0x00020000);
-    unsigned kcol[3];          // per K row this wave loads: token and chunk byte offset within the row
+    const unsigned rowb = (unsigned)p.xp * 64u;
+    const unsigned klev = (unsigned)p.Y * (unsigned)p.X * tsb, vlev = (unsigned)p.Y * rowb;
+    unsigned voff[5];
     {
         const int c = lane >> 2, cq = lane & 3;
         int xk = hx0 + c;
         xk = xk < 0 ? xk + p.X : (xk >= p.X ? xk - p.X : xk);
 #pragma unroll
-        for (int u = 0; u < 3; ++u) {
-            const int r = wave + 4 * u;    // K row (u < 3 covers rows 0..9 of waves 0, 1 and 0..7 of 2, 3)
-            kcol[u] = (unsigned)xk * tsb + 16u * (unsigned)(cq ^ kswz(r, c));
-        }
-    }
-    const unsigned vcol = 512u * (unsigned)tx + 16u * (unsigned)lane;
-    const unsigned rowb = (unsigned)p.xp * 64u;
-    auto stage = [&](int hz, int slot) {
-        unsigned char *dst = ring + slot * RING_SLOT;
-        const unsigned zr = (unsigned)(zlo + hz) * (unsigned)p.Y;
-#pragma unroll
         for (int u = 0; u < 5; ++u) {
             const int r = wave + 4 * u;
-            if (r < RING_ROWS) {
-                const unsigned yy = (unsigned)min(ylo + r, ylo + yn - 1);
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(krs, (lds_void *)(dst + r * 1024), 16,
-                                                         (zr + yy) * (unsigned)p.X * tsb + kcol[u < 3 ? u : 0], 0, 0, 0);
-            } else {
-                const unsigned yy = (unsigned)min(ylo + r - RING_ROWS, ylo + yn - 1);
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(vrs, (lds_void *)(dst + r * 1024), 16, (zr + yy) * rowb + vcol, 0, 0, 0);
-            }
+            const bool isk = r < RING_ROWS;
+            const unsigned yy = (unsigned)min(ylo + (isk ? r : r - RING_ROWS), ylo + yn - 1);
+            voff[u] = isk ? yy * (unsigned)p.X * tsb + (unsigned)xk * tsb + 16u * (unsigned)(cq ^ kswz(r, c))
+                          : yy * rowb + 512u * (unsigned)tx + 16u * (unsigned)(lane ^ ((lane >> 1) & 8));
+        }
+    }
+    auto stage = [&](int hh, int hz, int slot) {
+        unsigned char *dst = ring + slot * RING_SLOT + wave * 1024;
+        const __amdgpu_buffer_rsrc_t krs =
+            __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(kb + (size_t)hh * p.hs), 0, 0x7ffffffe, 0x00020000);
+        const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc(
+            uniform_ptr((const unsigned char *)p.v + ((size_t)hh * p.B + b) * plane), 0, (unsigned)plane, 0x00020000);
+        const int ko = (int)((unsigned)(zlo + hz) * klev), vo = (int)((unsigned)(zlo + hz) * vlev);
+#pragma unroll
+        for (int u = 0; u < 5; ++u) {
+            if (u < 2 || (u == 2 && wave < 2))
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(krs, (lds_void *)(dst + 4 * u * 1024), 16, voff[u], ko, 0, 0);
+            else
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(vrs, (lds_void *)(dst + 4 * u * 1024), 16, voff[u], vo, 0, 0);
         }
     };
-    stage(0, 0);
-    {
-        const uint4 *src = (const uint4 *)(p.tbl_ws + (size_t)h * TBLP);
-        for (int e = tid; e < TBLP / 4; e += 256) ((uint4 *)tbl)[e] = src[e];
-    }
+    stage(h, 0, 0);
+    // a head's bias table on its way to LDS
+    constexpr int NT4 = (TBLP / 4 + 255) / 256;
+    i32x4 tb[NT4];
+    auto load_tbl = [&](int hh) {
+        const char *src = (const char *)(p.tbl_ws + (size_t)hh * TBLP);
+#pragma unroll
+        for (int k = 0; k < NT4; ++k)
+            tb[k] = *(const i32x4 *)(src + 16u * (unsigned)min(tid + 256 * k, TBLP / 4 - 1));
+    };
+    auto store_tbl = [&]() {
+#pragma unroll
+        for (int k = 0; k < NT4; ++k)
+            if (tid + 256 * k < TBLP / 4) ((i32x4 *)tbl)[tid + 256 * k] = tb[k];
+    };
+    load_tbl(h);
 
     // ---- per wave: lat group pair (wave & 1), lon groups 2*(wave>>1) + {0,1} ----
     const int g = lane >> 4, r16 = lane & 15;
@@ -543,24 +576,29 @@ __global__ __launch_bounds__(256, 3) void nat_ring_kernel(NatArgs p, TileDiv dm)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
             oky[hf][j] = (unsigned)(4 * hf + j + 2 * (g >> 1) - wy) < (unsigned)KY;
-    const int tb_lane = (zb * BY + yb + 2 * (g >> 1)) * XT + 4 * (g & 1) - xrel + 1;
+    const int tb_lane = (zb * BY + yb + 2 * (g >> 1)) * XT + 8 * xrel + 4 * (g & 1);
     // K operand (key 16 j + r16 = lat row 4hf + j + 2 (r16 >> 3), lon column
     // r16 & 7 of the group halo): LDS byte offsets within a level slot
-    int kaddr[2][2][2];
+    // (4 lat rows further on, for hf = 1, the chunk order is the same)
+    int kaddr[2][2];
 #pragma unroll
-    for (int hf = 0; hf < 2; ++hf)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int G = 0; G < 2; ++G) {
+            const int R = dy + j + 2 * (r16 >> 3), c = GX * (gxa + G) + (r16 & 7);
+            kaddr[j][G] = R * 1024 + c * 64 + 16 * (g ^ kswz(R, c));
+        }
+    // V^T operand (as in nat_tile_kernel), within a level's V rows: channels
+    // r16 (tt = 0) and 16 + r16; in the odd blocks of a row the two halves of the
+    // channels are exchanged, so that blocks side by side are not in the same banks
+    const int vblk = (wave >> 1) + (g & 1);
+    int vaddr[2];
 #pragma unroll
-            for (int G = 0; G < 2; ++G) {
-                const int R = dy + 4 * hf + j + 2 * (r16 >> 3), c = GX * (gxa + G) + (r16 & 7);
-                kaddr[hf][j][G] = R * 1024 + c * 64 + 16 * (g ^ kswz(R, c));
-            }
-    // V^T operand (as in nat_tile_kernel), within a level's V rows
-    const int vbase = RING_ROWS * 1024 + (dy + 2 * (g >> 1)) * 1024 + ((wave >> 1) + (g & 1)) * 256 + r16 * 8;
+    for (int tt = 0; tt < 2; ++tt)
+        vaddr[tt] = RING_ROWS * 1024 + (dy + 2 * (g >> 1)) * 1024 + vblk * 256 + 128 * (tt ^ (vblk & 1)) + r16 * 8;
 
-    bf16x8 qf[2];
-    long qtok[2];
+    bf16x8 qf[2], qn[2], kn[2];
+    int qtok[2];
     bool act[2];
     float mref[2];
 #pragma unroll
@@ -568,148 +606,183 @@ __global__ __launch_bounds__(256, 3) void nat_ring_kernel(NatArgs p, TileDiv dm)
         const int xp_ = x0 + GX * (gxa + G) + xrel;
         act[G] = zq < p.Z && yq < p.Y && xp_ < p.X - SX;
         const int xc = xp_ < 0 ? xp_ + p.X : (xp_ >= p.X ? xp_ - p.X : xp_);
-        qtok[G] = (long)mul24(mul24((unsigned)zc, (unsigned)p.Y) + (unsigned)yc, (unsigned)p.X) + xc;
-        qf[G] = *(const bf16x8 *)(qb + qtok[G] * p.ts + 8 * g);
-        const bf16x8 ks = *(const bf16x8 *)(kb + qtok[G] * p.ts + 8 * g);
-        float sd = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) sd = fmaf(bf2f(qf[G][e]), bf2f(ks[e]), sd);
-        mref[G] = xsum16_32(sd);
+        qtok[G] = (int)mul24(mul24((unsigned)zc, (unsigned)p.Y) + (unsigned)yc, (unsigned)p.X) + xc;
     }
-    __syncthreads();     // bias table and level 0 in LDS
-    {
-        const float tcenter = tbl[((KZ - 1) * BY + KY - 1) * XT + 1 + RX];
+    // a head's queries and their own keys
+    auto load_q = [&](int hh) {
+#pragma unroll
+        for (int G = 0; G < 2; ++G) {
+            const unsigned o = (unsigned)qtok[G] * tsb + 16u * (unsigned)g;    // (within K's 2 GiB range)
+            qn[G] = *(const bf16x8 *)((const char *)(qb + (size_t)hh * p.hs) + o);
+            kn[G] = *(const bf16x8 *)((const char *)(kb + (size_t)hh * p.hs) + o);
+        }
+    };
+    auto own_score = [&]() {
+#pragma unroll
+        for (int G = 0; G < 2; ++G) {
+            qf[G] = qn[G];
+            float sd = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) sd = fmaf(bf2f(qn[G][e]), bf2f(kn[G][e]), sd);
+            mref[G] = xsum16_32(sd);
+        }
+    };
+    auto own_bias = [&]() {
+        const float tcenter = tbl[((KZ - 1) * BY + KY - 1) * XT + RX];
 #pragma unroll
         for (int G = 0; G < 2; ++G) mref[G] = QSCALED ? mref[G] + tcenter : (mref[G] + tcenter) * p.qscale;
-    }
+    };
+    load_q(h);
+    store_tbl();
+    own_score();
+    wait_vmcnt<0>();
+    __syncthreads();     // bias table and level 0 in LDS
+    own_bias();
 
     uint4 ones_u = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
     asm volatile("" : "+v"(ones_u.x), "+v"(ones_u.y), "+v"(ones_u.z), "+v"(ones_u.w));
     const bf16x8 ones = __builtin_bit_cast(bf16x8, ones_u);
 
-    f32x4 oacc[2][2], lacc[2];
-    for (int pass = 0;; ++pass) {
+    int lv = 0;                                   // slot of the level to compute
+    for (int last = h + nh - 1;; ++h) {
+        f32x4 oacc[2][2], lacc[2];
+        int pass = 0;
+        for (;; ++pass) {
 #pragma unroll
-        for (int G = 0; G < 2; ++G) oacc[G][0] = oacc[G][1] = lacc[G] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int hz0 = 0; hz0 < zn; hz0 += 2)
-#pragma unroll
-        for (int lv = 0; lv < 2; ++lv) {          // level hz0 + lv is in slot lv
-            const int hz = hz0 + lv;
-            if (hz >= zn) break;                  // uniform
-            if (hz > 0) __syncthreads();          // level hz landed; level hz - 1 is done with
-            if (hz + 1 < zn) stage(hz + 1, lv ^ 1);
-            const unsigned char *sl = ring + lv * RING_SLOT;
-            const bool okz = (unsigned)(hz - wz) < (unsigned)KZ;
-            const int tbh = tb_lane + hz * BY * XT;
-#pragma unroll
-            for (int hf = 0; hf < 2; ++hf) {
-                f32x4 binit[2];
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const int a = (okz && oky[hf][j]) ? tbh : TBL;
-                    const float *tp = tbl + a + (4 * hf + j) * XT;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) binit[j][i] = tp[i];
+            for (int G = 0; G < 2; ++G) oacc[G][0] = oacc[G][1] = lacc[G] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int hz = 0; hz < zn; ++hz, lv ^= 1) {
+                if (hz > 0) {                         // level hz landed; level hz - 1 is done with
+                    wait_vmcnt<0>();
+                    __syncthreads();
                 }
-                bf16x8 pb[2];
-#pragma unroll
-                for (int G = 0; G < 2; ++G)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) {
-                        const bf16x8 kf = *(const bf16x8 *)(sl + kaddr[hf][j][G]);
-                        const f32x4 sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[G], binit[j], 0, 0, 0);
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const float sv = QSCALED ? sc[i] : sc[i] * p.qscale;
-                            pb[G][4 * j + i] = (bf16)__builtin_amdgcn_exp2f(sv - mref[G]);
-                        }
-                    }
-                const unsigned char *vr = sl + vbase + 4 * hf * 1024;
-#pragma unroll
-                for (int tt = 0; tt < 2; ++tt) {
-                    // group 0: lon columns 0..3 of the lane's block; group 1:
-                    // columns 2, 3 of it and 0, 1 of the next.  (Typed scalar
-                    // loads without overlap: before a load that carries no
-                    // type, as of a struct or merged from overlapping ones,
-                    // the compiler waits for the level in flight.)
-                    const unsigned long a0 = *(const unsigned long *)(vr + 128 * tt);
-                    const unsigned long a1 = *(const unsigned long *)(vr + 128 * tt + 1024);
-                    const unsigned n0 = *(const unsigned *)(vr + 128 * tt + 256), n1 = *(const unsigned *)(vr + 128 * tt + 1280);
-                    const uint4 w0 = make_uint4((unsigned)a0, (unsigned)(a0 >> 32), (unsigned)a1, (unsigned)(a1 >> 32));
-                    const uint4 w1 = make_uint4((unsigned)(a0 >> 32), n0, (unsigned)(a1 >> 32), n1);
-                    oacc[0][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w0), pb[0],
-                                                                          oacc[0][tt], 0, 0, 0);
-                    oacc[1][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w1), pb[1],
-                                                                          oacc[1][tt], 0, 0, 0);
-                }
-#pragma unroll
-                for (int G = 0; G < 2; ++G)
-                    lacc[G] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[G], lacc[G], 0, 0, 0);
-            }
-        }
-        int bad = 0;
-#pragma unroll
-        for (int G = 0; G < 2; ++G) {
-            bad |= !(lacc[G][0] <= 0x1p96f);
-#pragma unroll
-            for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) bad |= !__builtin_isfinite(oacc[G][tt][i]);
-        }
-        // workgroup-uniform decision: the walk has barriers
-        if (!__syncthreads_or(bad) || pass == 1) break;
-        // exact maxima (K from global memory), then the walk again
-        {
-            const unsigned usrow = (unsigned)p.X * tsb;
-            const unsigned urow0 = (unsigned)zlo * ((unsigned)p.Y * usrow) + (unsigned)ylo * usrow;
-            const int kslab = p.Y * p.X * (int)tsb;
-            float mx[2] = {-INFINITY, -INFINITY};
-            for (int hz = 0; hz < zn; ++hz) {
+                if (hz + 1 < zn) stage(h, hz + 1, lv ^ 1);
+                else if (h < last && pass == 0) stage(h + 1, 0, lv ^ 1);
+                const unsigned char *sl = ring + lv * RING_SLOT;
                 const bool okz = (unsigned)(hz - wz) < (unsigned)KZ;
                 const int tbh = tb_lane + hz * BY * XT;
 #pragma unroll
-                for (int hf = 0; hf < 2; ++hf)
+                for (int hf = 0; hf < 2; ++hf) {
+                    f32x4 binit[2];
 #pragma unroll
                     for (int j = 0; j < 2; ++j) {
                         const int a = (okz && oky[hf][j]) ? tbh : TBL;
                         const float *tp = tbl + a + (4 * hf + j) * XT;
-                        f32x4 bi;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) bi[i] = tp[i];
-                        const int hyk = min(4 * hf + j + 2 * (r16 >> 3) + dy, yn - 1);
-#pragma unroll
-                        for (int G = 0; G < 2; ++G) {
-                            int xk = hx0 + (r16 & 7) + GX * (gxa + G);
-                            xk = xk < 0 ? xk + p.X : (xk >= p.X ? xk - p.X : xk);
-                            const unsigned ko = urow0 + (unsigned)hyk * usrow + (unsigned)xk * tsb + 16u * g;
-                            const bf16x8 kf = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
-                                krs, ko, hz * kslab, 0));
-                            const f32x4 sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[G], bi, 0, 0, 0);
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) mx[G] = max2f(mx[G], QSCALED ? sc[i] : sc[i] * p.qscale);
-                        }
+                        binit[j] = *(const f32x4 *)tp;
                     }
+                    bf16x8 pb[2];
+#pragma unroll
+                    for (int G = 0; G < 2; ++G)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) {
+                            const bf16x8 kf = *(const bf16x8 *)(sl + kaddr[j][G] + 4 * hf * 1024);
+                            const f32x4 sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[G], binit[j], 0, 0, 0);
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const float sv = QSCALED ? sc[i] : sc[i] * p.qscale;
+                                pb[G][4 * j + i] = (bf16)__builtin_amdgcn_exp2f(sv - mref[G]);
+                            }
+                        }
+                    const unsigned char *vr = sl + 4 * hf * 1024;
+#pragma unroll
+                    for (int tt = 0; tt < 2; ++tt) {
+                        // group 0: lon columns 0..3 of the lane's block; group 1:
+                        // columns 2, 3 of it and 0, 1 of the next.  (Typed scalar
+                        // loads without overlap: before a load that carries no
+                        // type, as of a struct or merged from overlapping ones,
+                        // the compiler waits for the level in flight.)
+                        const unsigned long a0 = *(const unsigned long *)(vr + vaddr[tt]);
+                        const unsigned long a1 = *(const unsigned long *)(vr + vaddr[tt] + 1024);
+                        const unsigned n0 = *(const unsigned *)(vr + vaddr[1 - tt] + 256), n1 = *(const unsigned *)(vr + vaddr[1 - tt] + 1280);
+                        const uint4 w0 = make_uint4((unsigned)a0, (unsigned)(a0 >> 32), (unsigned)a1, (unsigned)(a1 >> 32));
+                        const uint4 w1 = make_uint4((unsigned)(a0 >> 32), n0, (unsigned)(a1 >> 32), n1);
+                        oacc[0][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w0), pb[0],
+                                                                              oacc[0][tt], 0, 0, 0);
+                        oacc[1][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w1), pb[1],
+                                                                              oacc[1][tt], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int G = 0; G < 2; ++G)
+                        lacc[G] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[G], lacc[G], 0, 0, 0);
+                }
             }
+            if (h < last) {                           // (in either pass: nothing is held through a second walk)
+                load_tbl(h + 1);
+                load_q(h + 1);
+            }
+            int bad = 0;
 #pragma unroll
-            for (int G = 0; G < 2; ++G) mref[G] = xmax16_32(mx[G]);
+            for (int G = 0; G < 2; ++G) {
+                bad |= !(lacc[G][0] <= 0x1p96f);
+                bad |= !all_finite(oacc[G][0], oacc[G][1]);
+            }
+            // workgroup-uniform decision: the walk has barriers
+            if (!__syncthreads_or(bad) || pass == 1) break;
+            // exact maxima (K from global memory), then the walk again
+            {
+                const __amdgpu_buffer_rsrc_t krs =
+                    __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(kb + (size_t)h * p.hs), 0, 0x7ffffffe, 0x00020000);
+                int rr = r16;
+                asm volatile("" : "+v"(rr));          // (these addresses are rarely needed: nothing of them ahead of the walk)
+                const unsigned usrow = (unsigned)p.X * tsb;
+                const unsigned urow0 = (unsigned)zlo * ((unsigned)p.Y * usrow) + (unsigned)ylo * usrow;
+                const int kslab = p.Y * p.X * (int)tsb;
+                float mx[2] = {-INFINITY, -INFINITY};
+                for (int hz = 0; hz < zn; ++hz) {
+                    const bool okz = (unsigned)(hz - wz) < (unsigned)KZ;
+                    const int tbh = tb_lane + hz * BY * XT;
+#pragma unroll
+                    for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) {
+                            const int a = (okz && oky[hf][j]) ? tbh : TBL;
+                            const float *tp = tbl + a + (4 * hf + j) * XT;
+                            const f32x4 bi = *(const f32x4 *)tp;
+                            const int hyk = min(4 * hf + j + 2 * (rr >> 3) + dy, yn - 1);
+#pragma unroll
+                            for (int G = 0; G < 2; ++G) {
+                                int xk = hx0 + (rr & 7) + GX * (gxa + G);
+                                xk = xk < 0 ? xk + p.X : (xk >= p.X ? xk - p.X : xk);
+                                const unsigned ko = urow0 + (unsigned)hyk * usrow + (unsigned)xk * tsb + 16u * g;
+                                const bf16x8 kf = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                                    krs, ko, hz * kslab, 0));
+                                const f32x4 sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[G], bi, 0, 0, 0);
+#pragma unroll
+                                for (int i = 0; i < 4; ++i) mx[G] = max2f(mx[G], QSCALED ? sc[i] : sc[i] * p.qscale);
+                            }
+                        }
+                }
+#pragma unroll
+                for (int G = 0; G < 2; ++G) mref[G] = xmax16_32(mx[G]);
+            }
+            stage(h, 0, lv);
+            wait_vmcnt<0>();
+            __syncthreads();
         }
-        stage(0, 0);
-        __syncthreads();
-    }
 
-#pragma unroll
-    for (int G = 0; G < 2; ++G) {
-        if (!act[G]) continue;
-        const float inv = 1.0f / lacc[G][0];
-        bf16 *ob = (bf16 *)p.out + (size_t)b * p.obs + (size_t)qtok[G] * p.ots + h * 32;
-#pragma unroll
-        for (int tt = 0; tt < 2; ++tt) {
-            f32x4 v = oacc[G][tt];
-            uint2 u;
-            u.x = pack_bf16x2(v[0] * inv, v[1] * inv);
-            u.y = pack_bf16x2(v[2] * inv, v[3] * inv);
-            *(uint2 *)(ob + 16 * tt + 4 * g) = u;
+        if (h < last) {          // (every wave is past the walk: its table may go)
+            if (pass == 1) stage(h + 1, 0, lv);
+            store_tbl();
+            own_score();
+            wait_vmcnt<0>();
+            __syncthreads();
+            own_bias();
         }
+#pragma unroll
+        for (int G = 0; G < 2; ++G) {
+            if (!act[G]) continue;
+            asm volatile("" : "+v"(qtok[G]));        // (the output's offset is not worth holding through the walk)
+            const float inv = 1.0f / lacc[G][0];
+            bf16 *ob = (bf16 *)p.out + (size_t)b * p.obs + (size_t)qtok[G] * p.ots + h * 32;
+#pragma unroll
+            for (int tt = 0; tt < 2; ++tt) {
+                f32x4 v = oacc[G][tt];
+                uint2 u;
+                u.x = pack_bf16x2(v[0] * inv, v[1] * inv);
+                u.y = pack_bf16x2(v[2] * inv, v[3] * inv);
+                *(uint2 *)(ob + 16 * tt + 4 * g) = u;
+            }
+        }
+        if (h == last) break;
     }
 }
 
@@ -727,7 +800,6 @@ __global__ __launch_bounds__(256, 3) void nat_ring_kernel(NatArgs p, TileDiv dm)
 
 __device__ __forceinline__ float dq_scale(float amax) { return amax > 0.f ? amax * (1.0f / 448.0f) : 1.0f; }
 __device__ __forceinline__ float q_mul(float amax) { return amax > 0.f ? 448.0f / amax : 1.0f; }
-__device__ __forceinline__ float clamp448(float v) { return fminf(fmaxf(v, -448.0f), 448.0f); }
 
 // 8 bf16 values -> 8 e4m3 codes of value * mul (round to nearest even,
 // saturated); byte i of the result is value i.
@@ -740,10 +812,8 @@ __device__ __forceinline__ uint2 bf16x8_to_e4m3(uint4 u, float mul) {
         f[2 * q + 1] = __uint_as_float(w[q] & 0xffff0000u) * mul;
     }
     uint2 o;
-    unsigned a = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(clamp448(f[0]), clamp448(f[1]), 0, false);
-    o.x = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(clamp448(f[2]), clamp448(f[3]), (int)a, true);
-    a = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(clamp448(f[4]), clamp448(f[5]), 0, false);
-    o.y = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(clamp448(f[6]), clamp448(f[7]), (int)a, true);
+    o.x = e4m3x4(f[0], f[1], f[2], f[3]);
+    o.y = e4m3x4(f[4], f[5], f[6], f[7]);
     return o;
 }
 
@@ -766,7 +836,7 @@ __global__ void nat_bias_prep_fp8(NatArgs p) {
     float v = -INFINITY;
     if (i < TBL) {
         const int ixt = i % XT, rest = i / XT;
-        const int dx = ixt - 1 - RX;
+        const int dx = (ixt & 7) - (ixt >> 3) - RX;
         if (dx >= -RX && dx <= RX) v = p.rpb[((size_t)h * BZ * BY + rest) * (2 * KX - 1) + dx + KX - 1] * p.bscale / c;
     }
     p.tbl_ws[e] = v;
@@ -786,7 +856,7 @@ __global__ void nat_bias_prep_fp8(NatArgs p) {
 // and 10 of V (512 bytes), 10 KB; three slots rotate, so the loads of two
 // levels are in flight while one is computed (a wave waits for its own part
 // of a level with a vmcnt that leaves the next level's loads in flight, then
-// a bare barrier).  35 KB of LDS and 128 VGPRs: four workgroups share a CU
+// a bare barrier).  38 KB of LDS and 128 VGPRs: four workgroups share a CU
 // (the level walk is a loop, not unrolled, to stay within the registers;
 // measured 262 -> 239 us per state at 8x90x180 with B = 4 against two slots
 // and three workgroups per CU).  Reference: each
@@ -794,23 +864,30 @@ __global__ void nat_bias_prep_fp8(NatArgs p) {
 // exceeds m by more than TAU / c (a weight above 2^TAU, outside what the
 // e4m3 weights hold with the static scale) the workgroup finds the exact
 // maxima and runs the walk again.
+//
+// The vector unit bounds it, 85% busy: per key and query an exponential, a
+// multiply-add, its share of a maximum and of a conversion.  So what surrounds
+// the walk counts: heads share the addresses as in nat_ring_kernel, and values
+// that only the ends of a walk need are worked out there (a register held
+// through it means a spill, and a few spilled registers cost a third of the
+// speed).  1000 -> 930 us for 4 states of 8x90x180 tokens, 16 heads, window
+// 5x7x7.
 constexpr int RING8_ROWB = 512;                        // bytes per K or V row of a level
 constexpr int RING8_SLOT = 2 * RING_ROWS * RING8_ROWB;
 
-template <int BYTE>
-__device__ __forceinline__ float e4m3_f32(unsigned w) {
-    return __builtin_amdgcn_cvt_f32_fp8((int)w, BYTE);
-}
 // sum over the 4 bytes of a and b (e4m3 codes) of a_i b_i, added to s
 __device__ __forceinline__ float e4m3_dot4(unsigned a, unsigned b, float s) {
-    s = fmaf(e4m3_f32<0>(a), e4m3_f32<0>(b), s);
-    s = fmaf(e4m3_f32<1>(a), e4m3_f32<1>(b), s);
-    s = fmaf(e4m3_f32<2>(a), e4m3_f32<2>(b), s);
-    return fmaf(e4m3_f32<3>(a), e4m3_f32<3>(b), s);
+#pragma unroll
+    for (int hi = 0; hi < 2; ++hi) {
+        const auto x = hi ? __builtin_amdgcn_cvt_pk_f32_fp8((int)a, true) : __builtin_amdgcn_cvt_pk_f32_fp8((int)a, false);
+        const auto y = hi ? __builtin_amdgcn_cvt_pk_f32_fp8((int)b, true) : __builtin_amdgcn_cvt_pk_f32_fp8((int)b, false);
+        s = fmaf(x[1], y[1], fmaf(x[0], y[0], s));
+    }
+    return s;
 }
 
 template <int KZ, int KY, int KX>
-__global__ __launch_bounds__(256, 4) void nat_ring_fp8_kernel(NatArgs p, TileDiv dm) {
+__global__ __launch_bounds__(256, 4) void nat_ring_fp8_kernel(NatArgs p, TileDiv dm, int nh) {
     constexpr int RX = (KX - 1) / 2;
     constexpr int BY = 2 * KY - 1;
     constexpr int TBL = (2 * KZ - 1) * BY * XT;
@@ -824,16 +901,17 @@ __global__ __launch_bounds__(256, 4) void nat_ring_fp8_kernel(NatArgs p, TileDiv
 
     const int ntz = (p.Z + TZ - 1) / TZ, nty = (p.Y + TY - 1) / TY, ntx = (p.X + TX - 1) / TX;
     const int ntiles = ntz * nty * ntx;
-    const int total = ntiles * p.H * p.B;
+    const int nhg = p.H / nh;                       // head groups: this workgroup walks nh heads
+    const int total = ntiles * nhg * p.B;
     const int per = (total + 7) >> 3;
     const int L = blockIdx.x;
     const int id = (L & 7) * per + (L >> 3);
     if (id >= total) return;
     unsigned t = (unsigned)id, q;
     q = mdiv(t, dm.mx); const int tx = (int)(t - q * (unsigned)ntx); t = q;
-    q = mdiv(t, dm.my); const int ty = (int)(t - q * (unsigned)nty); t = q;
     q = mdiv(t, dm.mz); const int tz = (int)(t - q * (unsigned)ntz); t = q;
-    q = mdiv(t, dm.mh); const int h = (int)(t - q * (unsigned)p.H);
+    q = mdiv(t, dm.my); const int ty = (int)(t - q * (unsigned)nty); t = q;
+    q = mdiv(t, dm.mh); int h = nh * (int)(t - q * (unsigned)nhg);
     const int b = (int)q;
     const int z0 = tz * TZ, y0 = ty * TY;
     const int x0 = tx * TX - SX;
@@ -843,8 +921,8 @@ __global__ __launch_bounds__(256, 4) void nat_ring_fp8_kernel(NatArgs p, TileDiv
     clamp_range(z0, TZ, p.Z, KZ, zlo, zn);
     clamp_range(y0, TY, p.Y, KY, ylo, yn);
 
-    const unsigned char *k8 = (const unsigned char *)p.k + (size_t)b * p.bs + (size_t)h * p.hs;
-    const size_t qoff = (size_t)b * p.bs + (size_t)h * p.hs;   // elements (bf16) or bytes (q8)
+    const unsigned char *k8 = (const unsigned char *)p.k + (size_t)b * p.bs;
+    const size_t qoff = (size_t)b * p.bs;                       // elements (bf16) or bytes (q8)
     const float aq = p.amax[(size_t)b * p.amax_stride], ak = p.amax[(size_t)b * p.amax_stride + 1],
                 av = p.amax[(size_t)b * p.amax_stride + 2];
     const float c = dq_scale(aq) * dq_scale(ak) * p.qscale;     // score unit, log2 domain
@@ -853,51 +931,59 @@ __global__ __launch_bounds__(256, 4) void nat_ring_fp8_kernel(NatArgs p, TileDiv
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     // ---- level staging: instruction u = wave + 4 k (< 10) moves rows 2u, 2u+1
-    // of K (u < 5) or of V (u >= 5); rows past the halo repeat its last lat row
+    // of K (u < 5) or of V (u >= 5); rows past the halo repeat its last lat row.
+    // A row's offset within its level does not change with level or head
     const unsigned tsb = (unsigned)p.ts;                // K token stride, bytes
-    const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(k8), 0, 0x7ffffffe, 0x00020000);
     const size_t plane = (size_t)p.Z * p.Y * p.xp * 32;
-    const unsigned char *vp = (const unsigned char *)p.v + ((size_t)h * p.B + b) * plane;
-    const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(vp), 0, (unsigned)plane, 0x00020000);
-    const int lrow = lane >> 5;                        // which of the instruction's two rows
-    unsigned kcol[2];
+    const unsigned rowb = (unsigned)p.xp * 32u;
+    const unsigned klev = (unsigned)p.Y * (unsigned)p.X * tsb, vlev = (unsigned)p.Y * rowb;
+    unsigned voff[3];
     {
         const int cc = (lane >> 1) & 15, hq = lane & 1;
         int xk = hx0 + cc;
         xk = xk < 0 ? xk + p.X : (xk >= p.X ? xk - p.X : xk);
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {                  // K instructions of this wave: u = wave + 4 k
-            const int r = 2 * (wave + 4 * k) + lrow;
-            kcol[k] = (unsigned)xk * tsb + 16u * (unsigned)(hq ^ ((r >> 1) & 1));
-        }
-    }
-    const unsigned vcol = 256u * (unsigned)tx + 16u * (unsigned)(lane & 31);
-    const unsigned rowb = (unsigned)p.xp * 32u;
-    auto stage = [&](int hz, int slot) {
-        unsigned char *dst = ring + slot * RING8_SLOT;
-        const unsigned zr = (unsigned)(zlo + hz) * (unsigned)p.Y;
-#pragma unroll
         for (int k = 0; k < 3; ++k) {
             const int u = wave + 4 * k;
-            if (u < 5) {
-                const int r = 2 * u + lrow;
-                const unsigned yy = (unsigned)min(ylo + r, ylo + yn - 1);
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(krs, (lds_void *)(dst + 2 * u * RING8_ROWB), 16,
-                                                         (zr + yy) * (unsigned)p.X * tsb + kcol[k < 2 ? k : 0], 0, 0, 0);
-            } else if (u < 10) {
-                const int r = 2 * (u - 5) + lrow;
-                const unsigned yy = (unsigned)min(ylo + r, ylo + yn - 1);
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(vrs, (lds_void *)(dst + (RING_ROWS + 2 * (u - 5)) * RING8_ROWB),
-                                                         16, (zr + yy) * rowb + vcol, 0, 0, 0);
-            }
+            const int r = 2 * (u < 5 ? u : u - 5) + (lane >> 5);
+            const unsigned yy = (unsigned)min(ylo + r, ylo + yn - 1);
+            voff[k] = u < 5 ? yy * (unsigned)p.X * tsb + (unsigned)xk * tsb + 16u * (unsigned)(hq ^ ((r >> 1) & 1))
+                            : yy * rowb + 256u * (unsigned)tx + 16u * (unsigned)((lane & 31) ^ (4 * (((lane >> 3) ^ (r >> 1)) & 1)));
         }
-    };
-    stage(0, 0);
-    if (zn > 1) stage(1, 1);
-    {
-        const uint4 *src = (const uint4 *)(p.tbl_ws + ((size_t)b * p.H + h) * TBLP);
-        for (int e = tid; e < TBLP / 4; e += 256) ((uint4 *)tbl)[e] = src[e];
     }
+    auto stage = [&](int hh, int hz, int slot) {
+        unsigned char *dst = ring + slot * RING8_SLOT + wave * 2 * RING8_ROWB;
+        const __amdgpu_buffer_rsrc_t krs =
+            __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(k8 + (size_t)hh * p.hs), 0, 0x7ffffffe, 0x00020000);
+        const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc(
+            uniform_ptr((const unsigned char *)p.v + ((size_t)hh * p.B + b) * plane), 0, (unsigned)plane, 0x00020000);
+        const int ko = (int)((unsigned)(zlo + hz) * klev), vo = (int)((unsigned)(zlo + hz) * vlev);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(krs, (lds_void *)dst, 16, voff[0], ko, 0, 0);
+        if (wave == 0)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(krs, (lds_void *)(dst + 8 * RING8_ROWB), 16, voff[1], ko, 0, 0);
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(vrs, (lds_void *)(dst + 8 * RING8_ROWB), 16, voff[1], vo, 0, 0);
+        if (wave < 2)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(vrs, (lds_void *)(dst + 16 * RING8_ROWB), 16, voff[2], vo, 0, 0);
+    };
+    stage(h, 0, 0);
+    stage(h, 1, 1);                  // (a halo has at least KZ = 3 levels)
+    static_assert(KZ >= 2, "two levels are staged ahead");
+    // a head's bias table on its way to LDS
+    constexpr int NT4 = (TBLP / 4 + 255) / 256;
+    i32x4 tb[NT4];
+    auto load_tbl = [&](int hh) {
+        const char *src = (const char *)(p.tbl_ws + ((size_t)b * p.H + hh) * TBLP);
+#pragma unroll
+        for (int k = 0; k < NT4; ++k)
+            tb[k] = *(const i32x4 *)(src + 16u * (unsigned)min(tid + 256 * k, TBLP / 4 - 1));
+    };
+    auto store_tbl = [&]() {
+#pragma unroll
+        for (int k = 0; k < NT4; ++k)
+            if (tid + 256 * k < TBLP / 4) ((i32x4 *)tbl)[tid + 256 * k] = tb[k];
+    };
+    load_tbl(h);
 
     const int g = lane >> 4, r16 = lane & 15;
     const int y0g = y0 + 2 * (wave & 1);
@@ -918,25 +1004,34 @@ __global__ __launch_bounds__(256, 4) void nat_ring_fp8_kernel(NatArgs p, TileDiv
 #pragma unroll
         for (int j = 0; j < 2; ++j)
             oky[hf][j] = (unsigned)(4 * hf + j + 2 * (g >> 1) - wy) < (unsigned)KY;
-    const int tb_lane = (zb * BY + yb + 2 * (g >> 1)) * XT + 4 * (g & 1) - xrel + 1;
+    const int tb_lane = (zb * BY + yb + 2 * (g >> 1)) * XT + 8 * xrel + 4 * (g & 1);
     // K operand (key 16 j + r16 = lat row 4hf + j + 2 (r16 >> 3), lon column
     // r16 & 7 of the group halo; channels 8g .. 8g+7): LDS offsets in a slot
-    int kaddr[2][2][2];
+    // (4 lat rows further on, for hf = 1, the chunk order is the same)
+    int kaddr[2][2];
 #pragma unroll
-    for (int hf = 0; hf < 2; ++hf)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int G = 0; G < 2; ++G) {
-                const int R = dy + 4 * hf + j + 2 * (r16 >> 3), cc = GX * (gxa + G) + (r16 & 7);
-                kaddr[hf][j][G] = R * RING8_ROWB + cc * 32 + 8 * (g ^ (((R >> 1) & 1) << 1));
-            }
+        for (int G = 0; G < 2; ++G) {
+            const int R = dy + j + 2 * (r16 >> 3), cc = GX * (gxa + G) + (r16 & 7);
+            kaddr[j][G] = R * RING8_ROWB + cc * 32 + 8 * (g ^ (((R >> 1) & 1) << 1));
+        }
     // V^T operand (channel r16 + 16 tt; keys 4g .. 4g+3 of lat rows R0 and
-    // R0 + 1): block (wave >> 1) + (g & 1) of row R0 = dy + 4hf + 2 (g >> 1)
-    const int vbase = RING_ROWS * RING8_ROWB + (dy + 2 * (g >> 1)) * RING8_ROWB + ((wave >> 1) + (g & 1)) * 128 + r16 * 4;
+    // R0 + 1): block (wave >> 1) + (g & 1) of row R0 = dy + 4hf + 2 (g >> 1); the
+    // two halves of the channels are exchanged in odd blocks, and once more where
+    // bit 1 of the row is set: the four lane groups read from distinct banks
+    const int vblk = (wave >> 1) + (g & 1);
+    int vaddr[2][2];
+#pragma unroll
+    for (int rr = 0; rr < 2; ++rr)
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt) {
+            const int R = dy + 2 * (g >> 1) + rr;
+            vaddr[rr][tt] = (RING_ROWS + R) * RING8_ROWB + vblk * 128 + 64 * (tt ^ ((vblk ^ (R >> 1)) & 1)) + r16 * 4;
+        }
 
     long qf[2];
-    long qtok[2];
+    int qtok[2];
     bool act[2];
     float mref[2];
     const float mulq = q_mul(aq);
@@ -945,166 +1040,205 @@ __global__ __launch_bounds__(256, 4) void nat_ring_fp8_kernel(NatArgs p, TileDiv
         const int xp_ = x0 + GX * (gxa + G) + xrel;
         act[G] = zq < p.Z && yq < p.Y && xp_ < p.X - SX;
         const int xc = xp_ < 0 ? xp_ + p.X : (xp_ >= p.X ? xp_ - p.X : xp_);
-        qtok[G] = (long)mul24(mul24((unsigned)zc, (unsigned)p.Y) + (unsigned)yc, (unsigned)p.X) + xc;
-        const uint2 q8 = p.q8 ? *(const uint2 *)((const unsigned char *)p.q + qoff + qtok[G] * p.ts + 8 * g)
-                              : bf16x8_to_e4m3(*(const uint4 *)((const bf16 *)p.q + qoff + qtok[G] * p.ts + 8 * g), mulq);
-        qf[G] = (long)(((unsigned long long)q8.y << 32) | q8.x);
-        const uint2 ks = *(const uint2 *)(k8 + qtok[G] * p.ts + 8 * g);
-        mref[G] = xsum16_32(e4m3_dot4(q8.y, ks.y, e4m3_dot4(q8.x, ks.x, 0.f)));                     // the query's own score, raw units (bias below)
+        qtok[G] = (int)mul24(mul24((unsigned)zc, (unsigned)p.Y) + (unsigned)yc, (unsigned)p.X) + xc;
     }
-    __syncthreads();     // bias table and levels 0 and 1 in LDS
-    {
-        const float tcenter = tbl[((KZ - 1) * BY + KY - 1) * XT + 1 + RX];
+    // a head's queries and their own keys
+    uint2 qn[2], kn[2];
+    auto load_q = [&](int hh) {
+#pragma unroll
+        for (int G = 0; G < 2; ++G) {
+            asm volatile("" : "+v"(qtok[G]));    // (offsets are not worth holding through the walk)
+            const unsigned o = (unsigned)qtok[G] * tsb + 8u * (unsigned)g;     // (within K's 2 GiB range)
+            const size_t hd = qoff + (size_t)hh * p.hs;
+            qn[G] = p.q8 ? *(const uint2 *)((const unsigned char *)p.q + hd + o)
+                         : bf16x8_to_e4m3(*(const uint4 *)((const char *)((const bf16 *)p.q + hd) + 2u * o), mulq);
+            kn[G] = *(const uint2 *)(k8 + (size_t)hh * p.hs + o);
+        }
+    };
+    // the query's own score, raw units (bias below)
+    auto own_score = [&]() {
+#pragma unroll
+        for (int G = 0; G < 2; ++G) {
+            qf[G] = (long)(((unsigned long long)qn[G].y << 32) | qn[G].x);
+            mref[G] = xsum16_32(e4m3_dot4(qn[G].y, kn[G].y, e4m3_dot4(qn[G].x, kn[G].x, 0.f)));
+        }
+    };
+    auto own_bias = [&]() {
+        const float tcenter = tbl[((KZ - 1) * BY + KY - 1) * XT + RX];
 #pragma unroll
         for (int G = 0; G < 2; ++G) mref[G] += tcenter;
-    }
+    };
+    load_q(h);
+    store_tbl();
+    own_score();
+    wait_vmcnt<0>();
+    __syncthreads();     // bias table and levels 0 and 1 in LDS
+    own_bias();
     const float tau_raw = TAU / c;
     const long ones = 0x3838383838383838L;   // e4m3 1.0 in every byte
 
-    f32x4 oacc[2][2], lacc[2];
-    for (int pass = 0;; ++pass) {
-        float mx[2] = {-INFINITY, -INFINITY}, nmc[2];
+    int lv = 0;                                   // slot of the level to compute
+    for (int last = h + nh - 1;; ++h) {
+        f32x4 oacc[2][2], lacc[2];
+        int pass = 0;
+        for (;; ++pass) {
+            float mx[2] = {-INFINITY, -INFINITY}, nmc[2];
 #pragma unroll
-        for (int G = 0; G < 2; ++G) {
-            oacc[G][0] = oacc[G][1] = lacc[G] = f32x4{0.f, 0.f, 0.f, 0.f};
-            nmc[G] = -c * mref[G];
-        }
-        for (int hz = 0, lv = 0; hz < zn; ++hz, lv = lv == 2 ? 0 : lv + 1) {
-            if (hz > 0) {
-                // this wave's loads of level hz have landed once at most those
-                // of level hz + 1 (3 instructions for waves 0 and 1, 2 for
-                // waves 2 and 3, issued later) are outstanding; the barrier
-                // then makes every wave's part visible and frees the slot of
-                // level hz - 1 (levels 0 and 1 were waited for before the walk)
-                if (hz > 1) {
-                    if (hz + 1 < zn) {
-                        if (wave < 2) wait_vmcnt<3>();
-                        else wait_vmcnt<2>();
-                    } else {
-                        wait_vmcnt<0>();
-                    }
-                }
-                __builtin_amdgcn_s_barrier();
+            for (int G = 0; G < 2; ++G) {
+                oacc[G][0] = oacc[G][1] = lacc[G] = f32x4{0.f, 0.f, 0.f, 0.f};
+                nmc[G] = -c * mref[G];
             }
-            if (hz + 2 < zn) stage(hz + 2, lv == 0 ? 2 : lv - 1);
-            const unsigned char *sl = ring + lv * RING8_SLOT;
-            const bool okz = (unsigned)(hz - wz) < (unsigned)KZ;
-            const int tbh = tb_lane + hz * BY * XT;
-#pragma unroll
-            for (int hf = 0; hf < 2; ++hf) {
-                f32x4 binit[2];
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const int a = (okz && oky[hf][j]) ? tbh : TBL;
-                    const float *tp = tbl + a + (4 * hf + j) * XT;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) binit[j][i] = tp[i];
-                }
-                long pf[2];
-#pragma unroll
-                for (int G = 0; G < 2; ++G) {
-                    float pv[8];
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) {
-                        const long kf = *(const long *)(sl + kaddr[hf][j][G]);
-                        const f32x4 sc = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(kf, qf[G], binit[j], 0, 0, 0);
-                        mx[G] = max3f(mx[G], max3f(sc[0], sc[1], sc[2]), sc[3]);
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) pv[4 * j + i] = __builtin_amdgcn_exp2f(fmaf(sc[i], c, nmc[G]));
+            const bool ahead = h < last && pass == 0;     // the next head's levels 0 and 1 follow
+            for (int hz = 0; hz < zn; ++hz, lv = lv == 2 ? 0 : lv + 1) {
+                if (hz > 0) {
+                    // this wave's loads of level hz have landed once at most those
+                    // of level hz + 1 (3 instructions for waves 0 and 1, 2 for
+                    // waves 2 and 3, issued later) are outstanding; the barrier
+                    // then makes every wave's part visible and frees the slot of
+                    // level hz - 1 (levels 0 and 1 were waited for before the walk)
+                    if (hz > 1) {
+                        if (hz + 1 < zn || ahead) {
+                            if (wave < 2) wait_vmcnt<3>();
+                            else wait_vmcnt<2>();
+                        } else {
+                            wait_vmcnt<0>();
+                        }
                     }
-                    unsigned lo = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(pv[0], pv[1], 0, false);
-                    lo = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(pv[2], pv[3], (int)lo, true);
-                    unsigned hi = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(pv[4], pv[5], 0, false);
-                    hi = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(pv[6], pv[7], (int)hi, true);
-                    pf[G] = (long)(((unsigned long long)hi << 32) | lo);
+                    __builtin_amdgcn_s_barrier();
                 }
-                const unsigned char *vr = sl + vbase + 4 * hf * RING8_ROWB;
-#pragma unroll
-                for (int tt = 0; tt < 2; ++tt) {
-                    const unsigned char *vt = vr + 64 * tt;
-                    const unsigned a0 = *(const unsigned *)vt, a1 = *(const unsigned *)(vt + 128);
-                    const unsigned b0 = *(const unsigned *)(vt + RING8_ROWB), b1 = *(const unsigned *)(vt + RING8_ROWB + 128);
-                    // group 0: lon columns 0..3 of the block; group 1: columns 2, 3 and 0, 1 of the next
-                    const long v0 = (long)(((unsigned long long)b0 << 32) | a0);
-                    const long v1 = (long)(((unsigned long long)__builtin_amdgcn_alignbyte(b1, b0, 2) << 32) |
-                                           __builtin_amdgcn_alignbyte(a1, a0, 2));
-                    oacc[0][tt] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(v0, pf[0], oacc[0][tt], 0, 0, 0);
-                    oacc[1][tt] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(v1, pf[1], oacc[1][tt], 0, 0, 0);
-                }
-#pragma unroll
-                for (int G = 0; G < 2; ++G)
-                    lacc[G] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(ones, pf[G], lacc[G], 0, 0, 0);
-            }
-        }
-        // weights above 2^TAU (or a non-finite result) need the exact maxima
-        int bad = 0;
-#pragma unroll
-        for (int G = 0; G < 2; ++G) {
-            bad |= !(mx[G] - mref[G] <= tau_raw);
-#pragma unroll
-            for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) bad |= !__builtin_isfinite(oacc[G][tt][i]);
-        }
-        if (!__syncthreads_or(bad) || pass == 1) break;
-        {
-            const unsigned usrow = (unsigned)p.X * tsb;
-            const unsigned urow0 = (unsigned)zlo * ((unsigned)p.Y * usrow) + (unsigned)ylo * usrow;
-            const int kslab = p.Y * p.X * (int)tsb;
-            float me[2] = {-INFINITY, -INFINITY};
-            for (int hz = 0; hz < zn; ++hz) {
+                if (hz + 2 < zn) stage(h, hz + 2, lv == 0 ? 2 : lv - 1);
+                else if (ahead) stage(h + 1, hz + 2 - zn, lv == 0 ? 2 : lv - 1);
+                const unsigned char *sl = ring + lv * RING8_SLOT;
                 const bool okz = (unsigned)(hz - wz) < (unsigned)KZ;
                 const int tbh = tb_lane + hz * BY * XT;
 #pragma unroll
-                for (int hf = 0; hf < 2; ++hf)
+                for (int hf = 0; hf < 2; ++hf) {
+                    f32x4 binit[2];
 #pragma unroll
                     for (int j = 0; j < 2; ++j) {
                         const int a = (okz && oky[hf][j]) ? tbh : TBL;
                         const float *tp = tbl + a + (4 * hf + j) * XT;
-                        f32x4 bi;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) bi[i] = tp[i];
-                        const int hyk = min(4 * hf + j + 2 * (r16 >> 3) + dy, yn - 1);
-#pragma unroll
-                        for (int G = 0; G < 2; ++G) {
-                            int xk = hx0 + (r16 & 7) + GX * (gxa + G);
-                            xk = xk < 0 ? xk + p.X : (xk >= p.X ? xk - p.X : xk);
-                            const unsigned ko = urow0 + (unsigned)hyk * usrow + (unsigned)xk * tsb + 8u * g;
-                            const long kf = (long)__builtin_bit_cast(unsigned long long,
-                                                                   __builtin_amdgcn_raw_buffer_load_b64(krs, ko, hz * kslab, 0));
-                            const f32x4 sc = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(kf, qf[G], bi, 0, 0, 0);
-                            me[G] = max3f(me[G], max3f(sc[0], sc[1], sc[2]), sc[3]);
-                        }
+                        binit[j] = *(const f32x4 *)tp;
                     }
-            }
+                    long pf[2];
 #pragma unroll
-            for (int G = 0; G < 2; ++G) mref[G] = xmax16_32(me[G]);
+                    for (int G = 0; G < 2; ++G) {
+                        float pv[8];
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) {
+                            const long kf = *(const long *)(sl + kaddr[j][G] + 4 * hf * RING8_ROWB);
+                            const f32x4 sc = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(kf, qf[G], binit[j], 0, 0, 0);
+                            mx[G] = max3f(mx[G], max3f(sc[0], sc[1], sc[2]), sc[3]);
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) pv[4 * j + i] = __builtin_amdgcn_exp2f(fmaf(sc[i], c, nmc[G]));
+                        }
+                        const unsigned lo = e4m3x4_inrange(pv[0], pv[1], pv[2], pv[3]), hi = e4m3x4_inrange(pv[4], pv[5], pv[6], pv[7]);
+                        pf[G] = (long)(((unsigned long long)hi << 32) | lo);
+                    }
+                    const unsigned char *vr = sl + 4 * hf * RING8_ROWB;
+#pragma unroll
+                    for (int tt = 0; tt < 2; ++tt) {
+                        const unsigned a0 = *(const unsigned *)(vr + vaddr[0][tt]), a1 = *(const unsigned *)(vr + vaddr[0][1 - tt] + 128);
+                        const unsigned b0 = *(const unsigned *)(vr + vaddr[1][tt]), b1 = *(const unsigned *)(vr + vaddr[1][1 - tt] + 128);
+                        // group 0: lon columns 0..3 of the block; group 1: columns 2, 3 and 0, 1 of the next
+                        const long v0 = (long)(((unsigned long long)b0 << 32) | a0);
+                        const long v1 = (long)(((unsigned long long)__builtin_amdgcn_alignbyte(b1, b0, 2) << 32) |
+                                               __builtin_amdgcn_alignbyte(a1, a0, 2));
+                        oacc[0][tt] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(v0, pf[0], oacc[0][tt], 0, 0, 0);
+                        oacc[1][tt] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(v1, pf[1], oacc[1][tt], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int G = 0; G < 2; ++G)
+                        lacc[G] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(ones, pf[G], lacc[G], 0, 0, 0);
+                }
+            }
+            // weights above 2^TAU (or a non-finite result) need the exact maxima
+            if (h < last) {                           // (in either pass: nothing is held through a second walk)
+                load_tbl(h + 1);
+                load_q(h + 1);
+            }
+            int bad = 0;
+#pragma unroll
+            for (int G = 0; G < 2; ++G) {
+                bad |= !(mx[G] - mref[G] <= tau_raw);
+                bad |= !all_finite(oacc[G][0], oacc[G][1]);
+            }
+            if (!__syncthreads_or(bad) || pass == 1) break;
+            {
+                const __amdgpu_buffer_rsrc_t krs =
+                    __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(k8 + (size_t)h * p.hs), 0, 0x7ffffffe, 0x00020000);
+                int rr = r16;
+                asm volatile("" : "+v"(rr));          // (these addresses are rarely needed: nothing of them ahead of the walk)
+                const unsigned usrow = (unsigned)p.X * tsb;
+                const unsigned urow0 = (unsigned)zlo * ((unsigned)p.Y * usrow) + (unsigned)ylo * usrow;
+                const int kslab = p.Y * p.X * (int)tsb;
+                float me[2] = {-INFINITY, -INFINITY};
+                for (int hz = 0; hz < zn; ++hz) {
+                    const bool okz = (unsigned)(hz - wz) < (unsigned)KZ;
+                    const int tbh = tb_lane + hz * BY * XT;
+#pragma unroll
+                    for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) {
+                            const int a = (okz && oky[hf][j]) ? tbh : TBL;
+                            const float *tp = tbl + a + (4 * hf + j) * XT;
+                            const f32x4 bi = *(const f32x4 *)tp;
+                            const int hyk = min(4 * hf + j + 2 * (rr >> 3) + dy, yn - 1);
+#pragma unroll
+                            for (int G = 0; G < 2; ++G) {
+                                int xk = hx0 + (rr & 7) + GX * (gxa + G);
+                                xk = xk < 0 ? xk + p.X : (xk >= p.X ? xk - p.X : xk);
+                                const unsigned ko = urow0 + (unsigned)hyk * usrow + (unsigned)xk * tsb + 8u * g;
+                                const long kf = (long)__builtin_bit_cast(unsigned long long,
+                                                                       __builtin_amdgcn_raw_buffer_load_b64(krs, ko, hz * kslab, 0));
+                                const f32x4 sc = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(kf, qf[G], bi, 0, 0, 0);
+                                me[G] = max3f(me[G], max3f(sc[0], sc[1], sc[2]), sc[3]);
+                            }
+                        }
+                }
+#pragma unroll
+                for (int G = 0; G < 2; ++G) mref[G] = xmax16_32(me[G]);
+            }
+            stage(h, 0, lv);
+            stage(h, 1, lv == 2 ? 0 : lv + 1);
+            wait_vmcnt<0>();
+            __syncthreads();
         }
-        stage(0, 0);
-        if (zn > 1) stage(1, 1);
-        __syncthreads();
-    }
 
-    // o = s_v (sum p v8) / (sum p); as e4m3 codes at v's scale: (sum p v8) / (sum p)
-    const float sv = p.o8 ? 1.0f : dq_scale(av);
+        if (h < last) {          // (every wave is past the walk: its table may go)
+            if (pass == 1) {
+                stage(h + 1, 0, lv);
+                stage(h + 1, 1, lv == 2 ? 0 : lv + 1);
+            }
+            store_tbl();
+            own_score();
+            wait_vmcnt<0>();
+            __syncthreads();
+            own_bias();
+        }
+        // o = s_v (sum p v8) / (sum p); as e4m3 codes at v's scale: (sum p v8) / (sum p)
+        const float sv = p.o8 ? 1.0f : dq_scale(av);
 #pragma unroll
-    for (int G = 0; G < 2; ++G) {
-        if (!act[G]) continue;
-        const float inv = sv / lacc[G][0];
-        const size_t oo = (size_t)b * p.obs + (size_t)qtok[G] * p.ots + h * 32;
+        for (int G = 0; G < 2; ++G) {
+            if (!act[G]) continue;
+            asm volatile("" : "+v"(qtok[G]));        // (the output's offset is not worth holding through the walk)
+            const float inv = sv / lacc[G][0];
+            const size_t oo = (size_t)b * p.obs + (size_t)qtok[G] * p.ots + h * 32;
 #pragma unroll
-        for (int tt = 0; tt < 2; ++tt) {
-            f32x4 v = oacc[G][tt];
-            if (p.o8) {
-                *(unsigned *)((unsigned char *)p.out + oo + 16 * tt + 4 * g) =
-                    e4m3x4(v[0] * inv, v[1] * inv, v[2] * inv, v[3] * inv);
-            } else {
-                uint2 u;
-                u.x = pack_bf16x2(v[0] * inv, v[1] * inv);
-                u.y = pack_bf16x2(v[2] * inv, v[3] * inv);
-                *(uint2 *)((bf16 *)p.out + oo + 16 * tt + 4 * g) = u;
+            for (int tt = 0; tt < 2; ++tt) {
+                f32x4 v = oacc[G][tt];
+                if (p.o8) {
+                    *(unsigned *)((unsigned char *)p.out + oo + 16 * tt + 4 * g) =
+                        e4m3x4(v[0] * inv, v[1] * inv, v[2] * inv, v[3] * inv);
+                } else {
+                    uint2 u;
+                    u.x = pack_bf16x2(v[0] * inv, v[1] * inv);
+                    u.y = pack_bf16x2(v[2] * inv, v[3] * inv);
+                    *(uint2 *)((bf16 *)p.out + oo + 16 * tt + 4 * g) = u;
+                }
             }
         }
+        if (h == last) break;
     }
 }
 
@@ -1349,7 +1483,7 @@ __global__ __launch_bounds__(256, 2) void nat_tile_fp8_kernel(NatArgs p, int ZWm
 #pragma unroll
         for (int j = 0; j < 2; ++j)
             oky[hf][j] = (unsigned)(4 * hf + 2 * j + (g >> 1) - wy) < (unsigned)KY;
-    const int tb_lane = (zb * BY + yb + (g >> 1)) * XT + 4 * (g & 1) - xrel + 1;
+    const int tb_lane = (zb * BY + yb + (g >> 1)) * XT + 8 * xrel + 4 * (g & 1);
 
     // K fragment (key 16j + r16 = lat row 4hf + 2j + (r16 >> 3), lon column
     // r16 & 7 of the group halo; channels 8g..8g+7): lane base at level 0.
@@ -1398,8 +1532,7 @@ __global__ __launch_bounds__(256, 2) void nat_tile_fp8_kernel(NatArgs p, int ZWm
             for (int j = 0; j < 2; ++j) {
                 const int a = (okz && oky[hf][j]) ? tbh : TBL;
                 const float *tp = tbl + a + (4 * hf + 2 * j) * XT;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) binit[j][i] = tp[i];
+                    binit[j] = *(const f32x4 *)tp;
             }
             f32x4 s[2][2];
             float cm[2];
@@ -1438,10 +1571,7 @@ __global__ __launch_bounds__(256, 2) void nat_tile_fp8_kernel(NatArgs p, int ZWm
                 for (int j = 0; j < 2; ++j)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) pv[4 * j + i] = __builtin_amdgcn_exp2f(fmaf(s[G][j][i], c, nmc[G]));
-                unsigned lo = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(pv[0], pv[1], 0, false);
-                lo = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(pv[2], pv[3], (int)lo, true);
-                unsigned hi = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(pv[4], pv[5], 0, false);
-                hi = (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(pv[6], pv[7], (int)hi, true);
+                const unsigned lo = e4m3x4_inrange(pv[0], pv[1], pv[2], pv[3]), hi = e4m3x4_inrange(pv[4], pv[5], pv[6], pv[7]);
                 pf[G] = (long)(((unsigned long long)hi << 32) | lo);
             }
 #pragma unroll
@@ -1513,6 +1643,20 @@ hipError_t launch_tile_q(const NatArgs &a, hipStream_t stream) {
     return hipGetLastError();
 }
 
+// Heads that a workgroup of the ring kernels walks one after the other: 4 or 2
+// where they divide H and still leave 4096 workgroups (768 or 1024 run at
+// once; fewer than about five rounds of them end with idle CUs), else 1.
+// 8x90x180 tokens, 16 heads, window 5x7x7, us with 1 / 2 / 4 / 8 heads: bf16
+// from token-major q and k 371 / 337 / 330 / 345 (two heads share K's cache
+// lines), from head-major ones 281 / 280 / 282; e4m3, B = 4 1010 / 970 / 960 /
+// 967.  Below the line, with 1 / 2 / 4: 5x45x90, 4 heads 21.5 / 23 / 31 (1152
+// workgroups at 1), e4m3 8x18x20, 16 heads, B = 3 29 / 29.5 / 42.5 (1440).
+int heads_per_workgroup(const NatArgs &a, int ntiles) {
+    for (int n = 4; n > 1; n >>= 1)
+        if (a.H % n == 0 && (long)ntiles * (a.H / n) * a.B >= 4096) return n;
+    return 1;
+}
+
 size_t ring_lds(int Kz, int Ky) {
     const int tblp = (((2 * Kz - 1) * (2 * Ky - 1) * XT + NEG_RUN + 3) & ~3);
     return (size_t)tblp * 4 + 2 * (size_t)RING_SLOT;
@@ -1528,9 +1672,10 @@ hipError_t launch_ring(const NatArgs &a, hipStream_t stream) {
     constexpr int TBLP = tbl_padded<KZ, KY, KX>();
     if (!a.tbl_ready) nat_bias_prep<KZ, KY, KX, QSCALED><<<(a.H * TBLP + 255) / 256, 256, 0, stream>>>(a);
     const int ntiles = ((a.Z + TZ - 1) / TZ) * ((a.Y + TY - 1) / TY) * ((a.X + TX - 1) / TX);
-    const long total = (long)ntiles * a.H * a.B;
+    const int nh = heads_per_workgroup(a, ntiles);
+    const long total = (long)ntiles * (a.H / nh) * a.B;
     const unsigned grid = (unsigned)(((total + 7) >> 3) << 3);
-    nat_ring_kernel<KZ, KY, KX, QSCALED><<<grid, 256, ring_lds(KZ, KY), stream>>>(a, tile_div(a));
+    nat_ring_kernel<KZ, KY, KX, QSCALED><<<grid, 256, ring_lds(KZ, KY), stream>>>(a, tile_div(a, nh), nh);
     return hipGetLastError();
 }
 
@@ -1604,9 +1749,10 @@ hipError_t launch_ring_fp8(const NatArgs &a, hipStream_t stream) {
     constexpr int TBLP = tbl_padded<KZ, KY, KX>();
     nat_bias_prep_fp8<KZ, KY, KX><<<(a.B * a.H * TBLP + 255) / 256, 256, 0, stream>>>(a);
     const int ntiles = ((a.Z + TZ - 1) / TZ) * ((a.Y + TY - 1) / TY) * ((a.X + TX - 1) / TX);
-    const long total = (long)ntiles * a.H * a.B;
+    const int nh = heads_per_workgroup(a, ntiles);
+    const long total = (long)ntiles * (a.H / nh) * a.B;
     const unsigned grid = (unsigned)(((total + 7) >> 3) << 3);
-    nat_ring_fp8_kernel<KZ, KY, KX><<<grid, 256, ring8_lds(KZ, KY), stream>>>(a, tile_div(a));
+    nat_ring_fp8_kernel<KZ, KY, KX><<<grid, 256, ring8_lds(KZ, KY), stream>>>(a, tile_div(a, nh), nh);
     return hipGetLastError();
 }
 
