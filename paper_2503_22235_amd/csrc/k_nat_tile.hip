@@ -44,7 +44,9 @@ constexpr int XW = 16;                    // halo lon extent, padded (>= TX + Kx
 constexpr int XT = 16;                    // bias table row: 8 lon slots for the even, 8 for the odd query of a pair
 constexpr float TAU = 8.0f;               // lazy rescale threshold (log2 units)
 constexpr int LD_BATCH = 4;               // halo items loaded before they are stored
-constexpr int NEG_RUN = 100;              // -inf entries after the bias table (>= 6 XT + 4)
+constexpr int NEG_RUN = 84;               // -inf entries after the bias table (>= 5 XT + 4)
+constexpr int XT9 = 9;                    // row of the table in the tile kernels' LDS: hx - xq_rel + 1
+constexpr int NEG_RUN9 = 64;              // (>= 6 XT9 + 4)
 constexpr int YR_MIN = 10;                // lat rows per level slab a chunk walk may read (2 + 8)
 
 __device__ __forceinline__ void clamp_range(int a0, int tsize, int N, int K, int &lo, int &n) {
@@ -96,6 +98,8 @@ inline TileDiv tile_div(const NatArgs &a, int heads = 1) {
 // the bias table is stored divided by that scale.
 template <int KZ, int KY, int KX>
 constexpr int tbl_padded() { return ((2 * KZ - 1) * (2 * KY - 1) * XT + NEG_RUN + 3) & ~3; }
+template <int KZ, int KY, int KX>
+constexpr int tbl9_padded() { return ((2 * KZ - 1) * (2 * KY - 1) * XT9 + NEG_RUN9 + 3) & ~3; }
 
 // Per-head bias table in the layout the tile kernels read: tbl[iz][iy][x][hx]
 // for the key in lon slot hx of the halo of a query pair and its query x, lon
@@ -103,21 +107,40 @@ constexpr int tbl_padded() { return ((2 * KZ - 1) * (2 * KY - 1) * XT + NEG_RUN 
 // masked (level, lat) rows read.  A lane's four keys are one aligned 16-byte
 // read whichever its query (one row of 9 entries for both queries took four
 // reads that met in the same banks).
-template <int KZ, int KY, int KX, bool QSCALED>
+// ROW9: rows of XT9 entries that serve both queries of a pair (ixt = hx - x + 1),
+// for the tile kernels, whose V halo fills the LDS: with the longer rows one
+// workgroup less fits a CU at 3x5x5 and 5 levels (36.4 -> 39.3 us, 5x45x90).
+template <int KZ, int KY, int KX, bool QSCALED, bool ROW9>
 __global__ void nat_bias_prep(NatArgs p) {
-    constexpr int RX = (KX - 1) / 2, BY = 2 * KY - 1, BZ = 2 * KZ - 1;
-    constexpr int TBL = BZ * BY * XT, TBLP = tbl_padded<KZ, KY, KX>();
+    constexpr int RX = (KX - 1) / 2, BY = 2 * KY - 1, BZ = 2 * KZ - 1, ROW = ROW9 ? XT9 : XT;
+    constexpr int TBL = BZ * BY * ROW, TBLP = ROW9 ? tbl9_padded<KZ, KY, KX>() : tbl_padded<KZ, KY, KX>();
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= p.H * TBLP) return;
     const int h = e / TBLP, i = e - h * TBLP;
     const float bs = QSCALED ? p.bscale : p.bscale / p.qscale;
     float v = -INFINITY;
     if (i < TBL) {
-        const int ixt = i % XT, rest = i / XT;
-        const int dx = (ixt & 7) - (ixt >> 3) - RX;
+        const int ixt = i % ROW, rest = i / ROW;
+        const int dx = (ROW9 ? ixt - 1 : (ixt & 7) - (ixt >> 3)) - RX;
         if (dx >= -RX && dx <= RX) v = p.rpb[((size_t)h * BZ * BY + rest) * (2 * KX - 1) + dx + KX - 1] * bs;
     }
     p.tbl_ws[e] = v;
+}
+
+// A table with rows of XT (a processor's own, or e4m3) into LDS with rows of XT9.
+template <int KZ, int KY, int KX>
+__device__ __forceinline__ void copy_tbl9(float *tbl, const float *src) {
+    constexpr int TBL = (2 * KZ - 1) * (2 * KY - 1) * XT9, TBLP = tbl9_padded<KZ, KY, KX>(), N = (TBLP + 255) / 256;
+    float v[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const int e = min((int)threadIdx.x + 256 * k, TBL - 1), row = e / XT9, ixt = e - row * XT9;
+        v[k] = src[row * XT + max(ixt - 1, 0)];
+        v[k] = ixt > 0 && (int)threadIdx.x + 256 * k < TBL ? v[k] : -INFINITY;
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+        if ((int)threadIdx.x + 256 * k < TBLP) tbl[threadIdx.x + 256 * k] = v[k];
 }
 
 typedef __attribute__((address_space(3))) void lds_void;
@@ -137,12 +160,12 @@ template <int KZ, int KY, int KX, bool QSCALED>
 __global__ __launch_bounds__(256, 2) void nat_tile_kernel(NatArgs p, int ZWmax, int YR, TileDiv dm) {
     constexpr int RX = (KX - 1) / 2;
     constexpr int BY = 2 * KY - 1;
-    constexpr int TBL = (2 * KZ - 1) * BY * XT;    // bias table entries
+    constexpr int TBL = (2 * KZ - 1) * BY * XT9;    // bias table entries
     constexpr int SX = 4 - RX;                      // query tile tx starts at lon 8 tx - SX
     static_assert(2 + KX - 1 <= 8 && 2 + KY - 1 <= 8, "window too large for the 8-wide group halo");
     static_assert(TX == 8 && XW == 16, "halo slab layout");
 
-    constexpr int TBLP = tbl_padded<KZ, KY, KX>();
+    constexpr int TBLP = tbl9_padded<KZ, KY, KX>();
     extern __shared__ __align__(16) unsigned char smem[];
     float *tbl = (float *)smem;                                  // [BZ][BY][XT] + a run of -inf
     unsigned char *Vh = smem + TBLP * 4;                         // [ZWmax * YR] slabs of 1 KB
@@ -209,8 +232,12 @@ __global__ __launch_bounds__(256, 2) void nat_tile_kernel(NatArgs p, int ZWmax, 
     }
     // ---- bias table of this head (prepared by nat_bias_prep) ----
     {
-        const uint4 *src = (const uint4 *)(p.tbl_ws + (size_t)h * TBLP);
-        for (int e = tid; e < TBLP / 4; e += 256) ((uint4 *)tbl)[e] = src[e];
+        if (p.tbl_ready) {
+            copy_tbl9<KZ, KY, KX>(tbl, p.tbl_ws + (size_t)h * tbl_padded<KZ, KY, KX>());
+        } else {
+            const uint4 *src = (const uint4 *)(p.tbl_ws + (size_t)h * TBLP);
+            for (int e = tid; e < TBLP / 4; e += 256) ((uint4 *)tbl)[e] = src[e];
+        }
     }
 
     // ---- per wave: lat group pair (wave & 1), lon groups 2*(wave>>1) + {0,1} ----
@@ -237,7 +264,7 @@ __global__ __launch_bounds__(256, 2) void nat_tile_kernel(NatArgs p, int ZWmax, 
 #pragma unroll
         for (int j = 0; j < 2; ++j)
             oky[hf][j] = (unsigned)(4 * hf + j + 2 * (g >> 1) - wy) < (unsigned)KY;
-    const int tb_lane = (zb * BY + yb + 2 * (g >> 1)) * XT + 8 * xrel + 4 * (g & 1);
+    const int tb_lane = (zb * BY + yb + 2 * (g >> 1)) * XT9 + 4 * (g & 1) - xrel + 1;
 
     // K operand: key 16j + r16 = lat row 4hf + j + 2 (r16 >> 3), lon column
     // r16 & 7 of the group halo, from global memory (byte offsets within level
@@ -285,7 +312,7 @@ __global__ __launch_bounds__(256, 2) void nat_tile_kernel(NatArgs p, int ZWmax, 
     }
     __syncthreads();     // V halo (and table) in LDS
     {
-        const float tcenter = tbl[((KZ - 1) * BY + KY - 1) * XT + RX];   // bias at offset (0, 0, 0)
+        const float tcenter = tbl[((KZ - 1) * BY + KY - 1) * XT9 + 1 + RX];   // bias at offset (0, 0, 0)
 #pragma unroll
         for (int G = 0; G < 2; ++G) mref[G] = QSCALED ? mref[G] + tcenter : (mref[G] + tcenter) * p.qscale;
     }
@@ -319,7 +346,7 @@ __global__ __launch_bounds__(256, 2) void nat_tile_kernel(NatArgs p, int ZWmax, 
             if (hz >= zn) break;                 // uniform
             const bool okz = (unsigned)(hz - wz) < (unsigned)KZ;
             const unsigned char *vz = Vh + vbase + hz * vslab;
-            const int tbh = tb_lane + hz * BY * XT;
+            const int tbh = tb_lane + hz * BY * XT9;
 #pragma unroll
             for (int hf = 0; hf < 2; ++hf) {
                 const int ks = 2 * lv + hf;
@@ -337,8 +364,9 @@ __global__ __launch_bounds__(256, 2) void nat_tile_kernel(NatArgs p, int ZWmax, 
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
                     const int a = (okz && oky[hf][j]) ? tbh : TBL;
-                    const float *tp = tbl + a + (4 * hf + j) * XT;
-                    binit[j] = *(const f32x4 *)tp;
+                    const float *tp = tbl + a + (4 * hf + j) * XT9;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) binit[j][i] = tp[i];
                 }
                 bf16x8 pb[2];
 #pragma unroll
@@ -392,14 +420,16 @@ __global__ __launch_bounds__(256, 2) void nat_tile_kernel(NatArgs p, int ZWmax, 
         float mx[2] = {-INFINITY, -INFINITY};
         for (int hz = 0; hz < zn; ++hz) {
             const bool okz = (unsigned)(hz - wz) < (unsigned)KZ;
-            const int tbh = tb_lane + hz * BY * XT;
+            const int tbh = tb_lane + hz * BY * XT9;
 #pragma unroll
             for (int hf = 0; hf < 2; ++hf) {
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
                     const int a = (okz && oky[hf][j]) ? tbh : TBL;
-                    const float *tp = tbl + a + (4 * hf + j) * XT;
-                    const f32x4 bi = *(const f32x4 *)tp;
+                    const float *tp = tbl + a + (4 * hf + j) * XT9;
+                    f32x4 bi;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) bi[i] = tp[i];
 #pragma unroll
                     for (int G = 0; G < 2; ++G) {
                         const bf16x8 kf = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
@@ -1210,7 +1240,7 @@ __global__ __launch_bounds__(256, 4) void nat_ring_fp8_kernel(NatArgs p, TileDiv
                 stage(h + 1, 0, lv);
                 stage(h + 1, 1, lv == 2 ? 0 : lv + 1);
             }
-            store_tbl();
+                    store_tbl();
             own_score();
             wait_vmcnt<0>();
             __syncthreads();
@@ -1242,75 +1272,88 @@ __global__ __launch_bounds__(256, 4) void nat_ring_fp8_kernel(NatArgs p, TileDiv
     }
 }
 
+// One thread's item of the blocked-V kernels: one 16-byte chunk of a block (4
+// lon positions x 32 channels of a head; PER chunks).  Chunks run fastest, then
+// heads, then blocks of a lat row; a workgroup stays in its row.  A wave's reads
+// are runs of its tokens' rows and its stores whole blocks.  With heads outermost
+// every 128-byte line of two heads was fetched twice, and threads of 64 bytes
+// stored in strides.  bf16, 129600 tokens, 16 heads: 74 -> 44 us (280 MB).
+struct BlockedItem {
+    bool any;
+    unsigned chunk, h, b;
+    int x0;                     // lon of position 0
+    size_t row, block;          // (z Y + y) X of the state; (((h B + b) Z + z) Y + y) nxb + xb
+    __device__ __forceinline__ size_t token(int k, int X) const { return row + (size_t)(x0 + k < X ? x0 + k : x0 + k - X); }
+};
+template <int PER>
+__host__ __device__ inline unsigned blocked_wgs(int H, int xp) { return ((unsigned)(xp >> 2) * (unsigned)H * PER + 255) / 256; }
+// Rows (of B Z Y) per launch: a grid has less than 2^31 threads.
+template <int PER>
+unsigned blocked_rows(int H, int xp) { return std::max(1u, 0x7fffffffu / (256u * blocked_wgs<PER>(H, xp))); }
+template <int PER>
+__device__ __forceinline__ BlockedItem blocked_item(int B, int Z, int Y, int X, int H, int xp, unsigned row0) {
+    const unsigned nxb = (unsigned)xp >> 2, wgs = blocked_wgs<PER>(H, xp), row = blockIdx.x / wgs;
+    const unsigned bzy = row0 + row, zy = bzy % (unsigned)(Z * Y);
+    const unsigned e = (blockIdx.x - row * wgs) * 256 + threadIdx.x;
+    BlockedItem it;
+    it.chunk = e % PER;
+    const unsigned r = e / PER, xb = r / (unsigned)H;
+    it.h = r - xb * (unsigned)H;
+    it.b = bzy / (unsigned)(Z * Y);
+    it.any = xb < nxb;
+    const int x = ((int)(4 * xb) - 4) % X;
+    it.x0 = x < 0 ? x + X : x;
+    it.row = (size_t)zy * (unsigned)X;
+    it.block = (((size_t)it.h * (unsigned)B + it.b) * (unsigned)(Z * Y) + zy) * nxb + xb;
+    return it;
+}
+
 // K (bf16, token-major with strides bs, ts, hs) -> e4m3 at the state's
 // scale amax_k / 448, same strides in bytes; 8 channels per thread.
 __global__ void k8_kernel(const bf16 *__restrict__ k, long bs, long ts, long hs, unsigned char *__restrict__ out,
                           int B, long T, int H, const float *__restrict__ amax, int amax_stride) {
-    const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long total = (long)B * T * H * 4;
-    if (e >= total) return;
+    const unsigned e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= (unsigned)(B * T * H * 4)) return;
     const int c = (int)(e & 3);
-    long r = e >> 2;
-    const int h = (int)(r % H); r /= H;
-    const long t = r % T;
-    const int b = (int)(r / T);
+    unsigned r = e >> 2;
+    const unsigned h = r % (unsigned)H; r /= (unsigned)H;
+    const unsigned t = r % (unsigned)T, b = r / (unsigned)T;
     const size_t off = (size_t)b * bs + (size_t)t * ts + (size_t)h * hs + 8 * c;
     *(uint2 *)(out + off) = bf16x8_to_e4m3(*(const uint4 *)(k + off), q_mul(amax[(size_t)b * amax_stride + 1]));
 }
 
 // V (bf16, token-major) -> e4m3 at the state's scale amax_v / 448 in the
-// blocked layout with byte elements: one thread per (head, state, level,
-// lat, block of 4 positions, 8 channels).
+// blocked layout with byte elements.
 __global__ void v8_blocked_kernel(const bf16 *__restrict__ v, long bs, long ts, long hs, unsigned char *__restrict__ out,
                                   int B, int Z, int Y, int X, int H, int xp, const float *__restrict__ amax,
-                                  int amax_stride) {
-    const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    const int nxb = xp >> 2;
-    const long total = (long)H * B * Z * Y * nxb * 4;
-    if (e >= total) return;
-    const int c = (int)(e & 3);
-    long r = e >> 2;
-    const int xb = (int)(r % nxb); r /= nxb;
-    const long zyb = r;
-    const int y = (int)(r % Y); r /= Y;
-    const int z = (int)(r % Z); r /= Z;
-    const int b = (int)(r % B);
-    const int h = (int)(r / B);
-    const float mul = q_mul(amax[(size_t)b * amax_stride + 2]);
-    uint2 q8[4];
+                                  int amax_stride, unsigned row0) {
+    const BlockedItem it = blocked_item<8>(B, Z, Y, X, H, xp, row0);      // channels 4 chunk .. + 3
+    if (!it.any) return;
+    const float mul = q_mul(amax[(size_t)it.b * amax_stride + 2]);
+    unsigned q8[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        int x = 4 * xb + k - 4;
-        x = ((x % X) + X) % X;
-        q8[k] = bf16x8_to_e4m3(*(const uint4 *)(v + (size_t)b * bs + (((size_t)z * Y + y) * X + x) * ts + (size_t)h * hs + 8 * c), mul);
+        const uint2 u = *(const uint2 *)(v + (size_t)it.b * bs + it.token(k, X) * ts + (size_t)it.h * hs + 4 * it.chunk);
+        q8[k] = e4m3x4(__uint_as_float(u.x << 16) * mul, __uint_as_float(u.x & 0xffff0000u) * mul,
+                       __uint_as_float(u.y << 16) * mul, __uint_as_float(u.y & 0xffff0000u) * mul);
     }
-    // channel 8c + i of the 4 positions -> one dword (byte k = position k)
-    unsigned *dst = (unsigned *)(out + ((size_t)zyb * nxb + xb) * 128 + (8 * c) * 4);
-    const unsigned lo01 = __builtin_amdgcn_perm(q8[1].x, q8[0].x, 0x05010400u);   // p0c0 p1c0 p0c1 p1c1
-    const unsigned lo23 = __builtin_amdgcn_perm(q8[3].x, q8[2].x, 0x05010400u);
-    const unsigned hi01 = __builtin_amdgcn_perm(q8[1].x, q8[0].x, 0x07030602u);   // c2, c3
-    const unsigned hi23 = __builtin_amdgcn_perm(q8[3].x, q8[2].x, 0x07030602u);
-    const unsigned lo01b = __builtin_amdgcn_perm(q8[1].y, q8[0].y, 0x05010400u);
-    const unsigned lo23b = __builtin_amdgcn_perm(q8[3].y, q8[2].y, 0x05010400u);
-    const unsigned hi01b = __builtin_amdgcn_perm(q8[1].y, q8[0].y, 0x07030602u);
-    const unsigned hi23b = __builtin_amdgcn_perm(q8[3].y, q8[2].y, 0x07030602u);
-    dst[0] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);
-    dst[1] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
-    dst[2] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);
-    dst[3] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
-    dst[4] = __builtin_amdgcn_perm(lo23b, lo01b, 0x05040100u);
-    dst[5] = __builtin_amdgcn_perm(lo23b, lo01b, 0x07060302u);
-    dst[6] = __builtin_amdgcn_perm(hi23b, hi01b, 0x05040100u);
-    dst[7] = __builtin_amdgcn_perm(hi23b, hi01b, 0x07060302u);
+    // channel i of the 4 positions -> dword i (byte k = position k)
+    const unsigned lo01 = __builtin_amdgcn_perm(q8[1], q8[0], 0x05010400u);   // p0c0 p1c0 p0c1 p1c1
+    const unsigned lo23 = __builtin_amdgcn_perm(q8[3], q8[2], 0x05010400u);
+    const unsigned hi01 = __builtin_amdgcn_perm(q8[1], q8[0], 0x07030602u);   // c2, c3
+    const unsigned hi23 = __builtin_amdgcn_perm(q8[3], q8[2], 0x07030602u);
+    *(uint4 *)(out + it.block * 128 + 16 * it.chunk) =
+        make_uint4(__builtin_amdgcn_perm(lo23, lo01, 0x05040100u), __builtin_amdgcn_perm(lo23, lo01, 0x07060302u),
+                   __builtin_amdgcn_perm(hi23, hi01, 0x05040100u), __builtin_amdgcn_perm(hi23, hi01, 0x07060302u));
 }
 
 template <int KZ, int KY, int KX>
 __global__ __launch_bounds__(256, 2) void nat_tile_fp8_kernel(NatArgs p, int ZWmax, int YR, TileDiv dm) {
     constexpr int RX = (KX - 1) / 2;
     constexpr int BY = 2 * KY - 1;
-    constexpr int TBL = (2 * KZ - 1) * BY * XT;
+    constexpr int TBL = (2 * KZ - 1) * BY * XT9;
     static_assert(2 + KX - 1 <= 8 && 2 + KY - 1 <= 8, "window too large for the 8-wide group halo");
-    constexpr int TBLP = tbl_padded<KZ, KY, KX>();
+    constexpr int TBLP = tbl9_padded<KZ, KY, KX>();
     extern __shared__ __align__(16) unsigned char smem[];
     float *tbl = (float *)smem;
     unsigned char *Ks = smem + TBLP * 4;                     // [ZWmax*YR lat rows][KRS]
@@ -1353,8 +1396,7 @@ __global__ __launch_bounds__(256, 2) void nat_tile_fp8_kernel(NatArgs p, int ZWm
     const unsigned urow0 = (unsigned)zlo * uslab + (unsigned)ylo * usrow;
 
     {
-        const uint4 *src = (const uint4 *)(p.tbl_ws + ((size_t)b * p.H + h) * TBLP);
-        for (int e = tid; e < TBLP / 4; e += 256) ((uint4 *)tbl)[e] = src[e];
+        copy_tbl9<KZ, KY, KX>(tbl, p.tbl_ws + ((size_t)b * p.H + h) * tbl_padded<KZ, KY, KX>());
     }
     // ---- K halo, token-major e4m3: item = (slot, 16-byte chunk c of 8
     // channels); the 64 items of a halo row go to 64 consecutive threads, so
@@ -1483,7 +1525,7 @@ __global__ __launch_bounds__(256, 2) void nat_tile_fp8_kernel(NatArgs p, int ZWm
 #pragma unroll
         for (int j = 0; j < 2; ++j)
             oky[hf][j] = (unsigned)(4 * hf + 2 * j + (g >> 1) - wy) < (unsigned)KY;
-    const int tb_lane = (zb * BY + yb + (g >> 1)) * XT + 8 * xrel + 4 * (g & 1);
+    const int tb_lane = (zb * BY + yb + (g >> 1)) * XT9 + 4 * (g & 1) - xrel + 1;
 
     // K fragment (key 16j + r16 = lat row 4hf + 2j + (r16 >> 3), lon column
     // r16 & 7 of the group halo; channels 8g..8g+7): lane base at level 0.
@@ -1524,15 +1566,16 @@ __global__ __launch_bounds__(256, 2) void nat_tile_fp8_kernel(NatArgs p, int ZWm
         const unsigned char *kz = Ks + kbase + hz * YR * KRS;
         const unsigned char *vz0 = Vt + vbase + hz * YR * XW;
         const unsigned char *vz1 = vz0 + 16 * VSB;
-        const int tbh = tb_lane + hz * BY * XT;
+        const int tbh = tb_lane + hz * BY * XT9;
 #pragma unroll
         for (int hf = 0; hf < 2; ++hf) {
             f32x4 binit[2];
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int a = (okz && oky[hf][j]) ? tbh : TBL;
-                const float *tp = tbl + a + (4 * hf + 2 * j) * XT;
-                    binit[j] = *(const f32x4 *)tp;
+                const float *tp = tbl + a + (4 * hf + 2 * j) * XT9;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) binit[j][i] = tp[i];
             }
             f32x4 s[2][2];
             float cm[2];
@@ -1622,7 +1665,7 @@ int max_halo(int N, int K, int tsize) {
 }
 
 size_t tile_lds(int Kz, int Ky, int zw, int yr) {
-    const int tblp = (((2 * Kz - 1) * (2 * Ky - 1) * XT + NEG_RUN + 3) & ~3);
+    const int tblp = (((2 * Kz - 1) * (2 * Ky - 1) * XT9 + NEG_RUN9 + 3) & ~3);
     return (size_t)tblp * 4 + (size_t)zw * yr * 1024;     // table + V halo slabs
 }
 
@@ -1634,8 +1677,8 @@ hipError_t launch_tile_q(const NatArgs &a, hipStream_t stream) {
     static const hipError_t attr_err = hipFuncSetAttribute((const void *)nat_tile_kernel<KZ, KY, KX, QSCALED>,
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr_err != hipSuccess) return attr_err;
-    constexpr int TBLP = tbl_padded<KZ, KY, KX>();
-    if (!a.tbl_ready) nat_bias_prep<KZ, KY, KX, QSCALED><<<(a.H * TBLP + 255) / 256, 256, 0, stream>>>(a);
+    constexpr int TBLP = tbl9_padded<KZ, KY, KX>();
+    if (!a.tbl_ready) nat_bias_prep<KZ, KY, KX, QSCALED, true><<<(a.H * TBLP + 255) / 256, 256, 0, stream>>>(a);
     const int ntiles = ((a.Z + TZ - 1) / TZ) * ((a.Y + TY - 1) / TY) * ((a.X + TX - 1) / TX);
     const long total = (long)ntiles * a.H * a.B;
     const unsigned grid = (unsigned)(((total + 7) >> 3) << 3);
@@ -1644,16 +1687,17 @@ hipError_t launch_tile_q(const NatArgs &a, hipStream_t stream) {
 }
 
 // Heads that a workgroup of the ring kernels walks one after the other: 4 or 2
-// where they divide H and still leave 4096 workgroups (768 or 1024 run at
-// once; fewer than about five rounds of them end with idle CUs), else 1.
-// 8x90x180 tokens, 16 heads, window 5x7x7, us with 1 / 2 / 4 / 8 heads: bf16
-// from token-major q and k 371 / 337 / 330 / 345 (two heads share K's cache
-// lines), from head-major ones 281 / 280 / 282; e4m3, B = 4 1010 / 970 / 960 /
-// 967.  Below the line, with 1 / 2 / 4: 5x45x90, 4 heads 21.5 / 23 / 31 (1152
-// workgroups at 1), e4m3 8x18x20, 16 heads, B = 3 29 / 29.5 / 42.5 (1440).
-int heads_per_workgroup(const NatArgs &a, int ntiles) {
+// where they divide H and still leave `least` workgroups, about 5 (bf16, 3 a
+// CU) or 8 (e4m3, 4 a CU) rounds of those that run at once; below, the last
+// round leaves too many CUs idle.  Window 5x7x7, 16 heads, us with 1 / 2 / 4 / 8
+// heads: 8x90x180 bf16 from token-major q and k 371 / 337 / 330 / 345 (two heads
+// share K's cache lines), from head-major ones 281 / 280 / 282; e4m3, B = 4
+// 1010 / 970 / 960 / 967, B = 1 (16928 workgroups at 1) 289 / 277 / 290.  Below
+// the line, with 1 / 2 / 4: 5x45x90, 4 heads, bf16 21.5 / 23 / 31 (1152
+// workgroups at 1), 8x18x20, 16 heads, B = 3, e4m3 29 / 29.5 / 42.5 (1440).
+int heads_per_workgroup(const NatArgs &a, int ntiles, long least) {
     for (int n = 4; n > 1; n >>= 1)
-        if (a.H % n == 0 && (long)ntiles * (a.H / n) * a.B >= 4096) return n;
+        if (a.H % n == 0 && (long)ntiles * (a.H / n) * a.B >= least) return n;
     return 1;
 }
 
@@ -1670,50 +1714,31 @@ hipError_t launch_ring(const NatArgs &a, hipStream_t stream) {
                                                            (int)ring_lds(KZ, KY));
     if (attr_err != hipSuccess) return attr_err;
     constexpr int TBLP = tbl_padded<KZ, KY, KX>();
-    if (!a.tbl_ready) nat_bias_prep<KZ, KY, KX, QSCALED><<<(a.H * TBLP + 255) / 256, 256, 0, stream>>>(a);
+    if (!a.tbl_ready) nat_bias_prep<KZ, KY, KX, QSCALED, false><<<(a.H * TBLP + 255) / 256, 256, 0, stream>>>(a);
     const int ntiles = ((a.Z + TZ - 1) / TZ) * ((a.Y + TY - 1) / TY) * ((a.X + TX - 1) / TX);
-    const int nh = heads_per_workgroup(a, ntiles);
+    const int nh = heads_per_workgroup(a, ntiles, 4096);
     const long total = (long)ntiles * (a.H / nh) * a.B;
     const unsigned grid = (unsigned)(((total + 7) >> 3) << 3);
     nat_ring_kernel<KZ, KY, KX, QSCALED><<<grid, 256, ring_lds(KZ, KY), stream>>>(a, tile_div(a, nh), nh);
     return hipGetLastError();
 }
 
-// v [B][T][H][32] (strides bs, ts, hs) -> the blocked layout: one thread per
-// (head, state, level, lat, block of 4 positions, 8 channels).
+// v [B][T][H][32] (strides bs, ts, hs) -> the blocked layout.
 __global__ void v_blocked_kernel(const bf16 *__restrict__ v, long bs, long ts, long hs, bf16 *__restrict__ out,
-                                 int B, int Z, int Y, int X, int H, int xp) {
-    const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    const int nxb = xp >> 2;
-    const long total = (long)H * B * Z * Y * nxb * 4;
-    if (e >= total) return;
-    const int c = (int)(e & 3);
-    long r = e >> 2;
-    const int xb = (int)(r % nxb); r /= nxb;
-    const long zyb = r;                          // ((h B + b) Z + z) Y + y
-    const int y = (int)(r % Y); r /= Y;
-    const int z = (int)(r % Z); r /= Z;
-    const int b = (int)(r % B);
-    const int h = (int)(r / B);
-    uint4 u[4];
+                                 int B, int Z, int Y, int X, int H, int xp, unsigned row0) {
+    const BlockedItem it = blocked_item<16>(B, Z, Y, X, H, xp, row0);     // channels 2 chunk, + 1
+    if (!it.any) return;
+    unsigned u[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        int x = 4 * xb + k - 4;
-        x = ((x % X) + X) % X;
-        u[k] = *(const uint4 *)(v + (size_t)b * bs + (((size_t)z * Y + y) * X + x) * ts + (size_t)h * hs + 8 * c);
-    }
-    const unsigned w0[4] = {u[0].x, u[0].y, u[0].z, u[0].w}, w1[4] = {u[1].x, u[1].y, u[1].z, u[1].w};
-    const unsigned w2[4] = {u[2].x, u[2].y, u[2].z, u[2].w}, w3[4] = {u[3].x, u[3].y, u[3].z, u[3].w};
-    uint2 *dst = (uint2 *)(out + ((size_t)zyb * nxb + xb) * 128 + (8 * c) * 4);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        dst[2 * k] = make_uint2(__builtin_amdgcn_perm(w1[k], w0[k], 0x05040100u), __builtin_amdgcn_perm(w3[k], w2[k], 0x05040100u));
-        dst[2 * k + 1] = make_uint2(__builtin_amdgcn_perm(w1[k], w0[k], 0x07060302u), __builtin_amdgcn_perm(w3[k], w2[k], 0x07060302u));
-    }
+    for (int k = 0; k < 4; ++k)
+        u[k] = *(const unsigned *)(v + (size_t)it.b * bs + it.token(k, X) * ts + (size_t)it.h * hs + 2 * it.chunk);
+    *(uint4 *)(out + it.block * 128 + 8 * it.chunk) =
+        make_uint4(__builtin_amdgcn_perm(u[1], u[0], 0x05040100u), __builtin_amdgcn_perm(u[3], u[2], 0x05040100u),
+                   __builtin_amdgcn_perm(u[1], u[0], 0x07060302u), __builtin_amdgcn_perm(u[3], u[2], 0x07060302u));
 }
 
 size_t tile_lds_fp8(int Kz, int Ky, int zw, int yr) {
-    const int tblp = (((2 * Kz - 1) * (2 * Ky - 1) * XT + NEG_RUN + 3) & ~3);
+    const int tblp = (((2 * Kz - 1) * (2 * Ky - 1) * XT9 + NEG_RUN9 + 3) & ~3);
     return (size_t)tblp * 4 + (size_t)zw * yr * KRS + 32 * (size_t)vt_row_bytes(zw, yr);
 }
 
@@ -1749,7 +1774,10 @@ hipError_t launch_ring_fp8(const NatArgs &a, hipStream_t stream) {
     constexpr int TBLP = tbl_padded<KZ, KY, KX>();
     nat_bias_prep_fp8<KZ, KY, KX><<<(a.B * a.H * TBLP + 255) / 256, 256, 0, stream>>>(a);
     const int ntiles = ((a.Z + TZ - 1) / TZ) * ((a.Y + TY - 1) / TY) * ((a.X + TX - 1) / TX);
-    const int nh = heads_per_workgroup(a, ntiles);
+    // (q in bf16: scores of any size, and where they send every workgroup on a
+    // second walk the next head's levels were loaded for nothing: standard
+    // normal q and k at 8x90x180 747 us with one head, 764 with 2, 818 with 4)
+    const int nh = a.q8 ? heads_per_workgroup(a, ntiles, 8192) : 1;
     const long total = (long)ntiles * (a.H / nh) * a.B;
     const unsigned grid = (unsigned)(((total + 7) >> 3) << 3);
     nat_ring_fp8_kernel<KZ, KY, KX><<<grid, 256, ring8_lds(KZ, KY), stream>>>(a, tile_div(a, nh), nh);
@@ -1803,7 +1831,7 @@ size_t nat_tile_lds_bytes(const NatArgs &a) {
 template <int KZ, int KY, int KX>
 hipError_t bias_table_only(const NatArgs &a, hipStream_t stream) {
     constexpr int TBLP = tbl_padded<KZ, KY, KX>();
-    nat_bias_prep<KZ, KY, KX, true><<<(a.H * TBLP + 255) / 256, 256, 0, stream>>>(a);
+    nat_bias_prep<KZ, KY, KX, true, false><<<(a.H * TBLP + 255) / 256, 256, 0, stream>>>(a);
     return hipGetLastError();
 }
 
@@ -1822,9 +1850,10 @@ hipError_t launch_kv8(const NatArgs &a, unsigned char *k8, unsigned char *v8, hi
     if (nk > 0x7fffffffL || nv > 0x7fffffffL) return hipErrorInvalidValue;
     if (nk) k8_kernel<<<(unsigned)((nk + 255) / 256), 256, 0, stream>>>((const bf16 *)a.k, a.bs, a.ts, a.hs, k8, a.B, T,
                                                                       a.H, a.amax, a.amax_stride);
-    if (nv) v8_blocked_kernel<<<(unsigned)((nv + 255) / 256), 256, 0, stream>>>((const bf16 *)a.v, a.bs, a.ts, a.hs, v8,
-                                                                              a.B, a.Z, a.Y, a.X, a.H, a.xp, a.amax,
-                                                                              a.amax_stride);
+    const unsigned rows = (unsigned)(a.B * a.Z * a.Y), step = blocked_rows<8>(a.H, a.xp);
+    for (unsigned row0 = 0; nv && row0 < rows; row0 += step)
+        v8_blocked_kernel<<<std::min(step, rows - row0) * blocked_wgs<8>(a.H, a.xp), 256, 0, stream>>>(
+            (const bf16 *)a.v, a.bs, a.ts, a.hs, v8, a.B, a.Z, a.Y, a.X, a.H, a.xp, a.amax, a.amax_stride, row0);
     return hipGetLastError();
 }
 
@@ -1832,8 +1861,10 @@ hipError_t launch_v_blocked(const NatArgs &a, void *out, hipStream_t stream) {
     const long total = (long)a.H * a.B * a.Z * a.Y * (a.xp / 4) * 4;
     if (total == 0) return hipSuccess;
     if ((a.xp & 3) || total > 0x7fffffffL) return hipErrorInvalidValue;
-    v_blocked_kernel<<<(unsigned)((total + 255) / 256), 256, 0, stream>>>((const bf16 *)a.v, a.bs, a.ts, a.hs, (bf16 *)out,
-                                                                        a.B, a.Z, a.Y, a.X, a.H, a.xp);
+    const unsigned rows = (unsigned)(a.B * a.Z * a.Y), step = blocked_rows<16>(a.H, a.xp);
+    for (unsigned row0 = 0; row0 < rows; row0 += step)
+        v_blocked_kernel<<<std::min(step, rows - row0) * blocked_wgs<16>(a.H, a.xp), 256, 0, stream>>>(
+            (const bf16 *)a.v, a.bs, a.ts, a.hs, (bf16 *)out, a.B, a.Z, a.Y, a.X, a.H, a.xp, row0);
     return hipGetLastError();
 }
 
