@@ -852,7 +852,8 @@ constexpr int KRS = XW * 32 + 16;   // K halo bytes per lat row (16-byte pad aga
 // V^T row stride in bytes: >= the halo slots, = 8 mod 128.
 __host__ __device__ inline int vt_row_bytes(int zw, int yr) { return (zw * yr * XW + 119) / 128 * 128 + 8; }
 
-// Per-(state, head) bias table divided by that state's score unit c.
+// Per-(state, head) bias table divided by that state's score unit c (a
+// processor, whose scales are static, prepares one table per head at creation).
 template <int KZ, int KY, int KX>
 __global__ void nat_bias_prep_fp8(NatArgs p) {
     constexpr int RX = (KX - 1) / 2, BY = 2 * KY - 1, BZ = 2 * KZ - 1;
@@ -1003,7 +1004,7 @@ __global__ __launch_bounds__(256, 4) void nat_ring_fp8_kernel(NatArgs p, TileDiv
     constexpr int NT4 = (TBLP / 4 + 255) / 256;
     i32x4 tb[NT4];
     auto load_tbl = [&](int hh) {
-        const char *src = (const char *)(p.tbl_ws + ((size_t)b * p.H + hh) * TBLP);
+        const char *src = (const char *)(p.tbl_ws + (p.tbl_ready ? (size_t)hh : (size_t)b * p.H + hh) * TBLP);
 #pragma unroll
         for (int k = 0; k < NT4; ++k)
             tb[k] = *(const i32x4 *)(src + 16u * (unsigned)min(tid + 256 * k, TBLP / 4 - 1));
@@ -1772,7 +1773,7 @@ hipError_t launch_ring_fp8(const NatArgs &a, hipStream_t stream) {
                                                            (int)ring8_lds(KZ, KY));
     if (attr_err != hipSuccess) return attr_err;
     constexpr int TBLP = tbl_padded<KZ, KY, KX>();
-    nat_bias_prep_fp8<KZ, KY, KX><<<(a.B * a.H * TBLP + 255) / 256, 256, 0, stream>>>(a);
+    if (!a.tbl_ready) nat_bias_prep_fp8<KZ, KY, KX><<<(a.B * a.H * TBLP + 255) / 256, 256, 0, stream>>>(a);
     const int ntiles = ((a.Z + TZ - 1) / TZ) * ((a.Y + TY - 1) / TY) * ((a.X + TX - 1) / TX);
     // (q in bf16: scores of any size, and where they send every workgroup on a
     // second walk the next head's levels were loaded for nothing: standard
@@ -1831,6 +1832,12 @@ size_t nat_tile_lds_bytes(const NatArgs &a) {
 template <int KZ, int KY, int KX>
 hipError_t bias_table_only(const NatArgs &a, hipStream_t stream) {
     constexpr int TBLP = tbl_padded<KZ, KY, KX>();
+    if (a.amax) {                     // e4m3: one table for every state (static scales)
+        NatArgs one = a;
+        one.B = 1;
+        nat_bias_prep_fp8<KZ, KY, KX><<<(a.H * TBLP + 255) / 256, 256, 0, stream>>>(one);
+        return hipGetLastError();
+    }
     nat_bias_prep<KZ, KY, KX, true, false><<<(a.H * TBLP + 255) / 256, 256, 0, stream>>>(a);
     return hipGetLastError();
 }

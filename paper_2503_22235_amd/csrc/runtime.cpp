@@ -284,7 +284,8 @@ static int run_block_fp8(wm_ctx *ctx, const wm_processor *p, int block, int B, f
     na.bscale = 1.0f;
     na.B = B; na.Z = g.Z; na.Y = g.Y; na.X = g.X; na.H = H;
     na.Kz = g.Kz; na.Ky = g.Ky; na.Kx = g.Kx; na.periodic = g.periodic_mask;
-    na.tbl_ws = tbl_ws;
+    na.tbl_ws = w.nat_tbl ? w.nat_tbl : tbl_ws;
+    na.tbl_ready = w.nat_tbl != nullptr;
     na.amax = w.qkv_amax;      // the static (aq, ak, av) of every state
     na.amax_stride = 0;
     na.vt = 1;

@@ -36,8 +36,8 @@ struct BlockWeights {
     const float *qkv_amax = nullptr;
     float qkv_amax_h[3] = {0.f, 0.f, 0.f};
     float h_amax_h = 0.f;
-    // BF16 processors: the tiled attention kernel's bias table of this
-    // block, prepared once at creation (null: prepared per launch)
+    // BF16 and FP8 processors: the tiled attention kernels' bias table of
+    // this block, prepared once at creation (null: prepared per launch)
     float *nat_tbl = nullptr;
 };
 
