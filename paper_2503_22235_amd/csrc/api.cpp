@@ -167,9 +167,7 @@ int nat_forward_into(const wm_grid *g, int B, wm_precision prec, const void *q, 
         unsigned *amax = (unsigned *)((char *)ws + tbl_bytes);
         if ((e = launch_zero_u32(amax, (size_t)AMAX_SHARDS * AMAX_STRIDE, s)) != hipSuccess) return hip_fail(e, "zero");
         const void *src[3] = {q, k, v};
-        for (int i = 0; i < 3; ++i)
-            if ((e = launch_amax_bf16(src[i], (size_t)T * g->C, B, amax + i, 3, s)) != hipSuccess)
-                return hip_fail(e, "amax");
+        if ((e = launch_amax_bf16(src, (size_t)T * g->C, B, amax, s)) != hipSuccess) return hip_fail(e, "amax");
         if ((e = launch_amax_fold(amax, 3 * B, s)) != hipSuccess) return hip_fail(e, "amax fold");
         a.amax = (const float *)amax;
         a.amax_stride = 3;

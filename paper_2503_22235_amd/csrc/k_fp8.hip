@@ -98,11 +98,14 @@ __global__ __launch_bounds__(256) void quant_f32_kernel(const float *__restrict_
     }
 }
 
-// amax over each state's bf16 elements (8 per lane per step).
-__global__ __launch_bounds__(256) void amax_bf16_kernel(const unsigned short *__restrict__ x, size_t per_state,
-                                                        unsigned *__restrict__ amax, int amax_stride) {
-    const int b = blockIdx.y;
-    const unsigned short *xs = x + (size_t)b * per_state;
+// amax over each state's bf16 elements (8 per lane per step) of three tensors:
+// one launch, as a small call is bound by its launches (standalone e4m3
+// attention, 6x10x15 tokens, 4 heads: 38 -> 33 us, without allocation 30 -> 22).
+__global__ __launch_bounds__(256) void amax_bf16_kernel(const unsigned short *__restrict__ x0, const unsigned short *__restrict__ x1,
+                                                        const unsigned short *__restrict__ x2, size_t per_state,
+                                                        unsigned *__restrict__ amax) {
+    const int b = blockIdx.y, which = blockIdx.z;
+    const unsigned short *xs = (which == 0 ? x0 : which == 1 ? x1 : x2) + (size_t)b * per_state;
     float m = 0.f;
     const size_t n8 = per_state / 8;
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += (size_t)gridDim.x * 256) {
@@ -116,7 +119,7 @@ __global__ __launch_bounds__(256) void amax_bf16_kernel(const unsigned short *__
         m = fmaxf(m, fabsf(__uint_as_float((unsigned)xs[i] << 16)));
     m = wave_max(m);
     if ((threadIdx.x & 63) == 0)
-        atomicMax(amax + (blockIdx.x % AMAX_SHARDS) * AMAX_STRIDE + b * amax_stride, __float_as_uint(m));
+        atomicMax(amax + (blockIdx.x % AMAX_SHARDS) * AMAX_STRIDE + 3 * b + which, __float_as_uint(m));
 }
 
 __global__ void zero_u32_kernel(unsigned *p, size_t n) {
@@ -147,14 +150,13 @@ hipError_t launch_layernorm_fp8_static(const StateRows &x, const float *gamma, c
     }
 }
 
-hipError_t launch_amax_bf16(const void *x, size_t per_state, int B, unsigned *amax, int amax_stride,
-                            hipStream_t stream) {
+hipError_t launch_amax_bf16(const void *const x[3], size_t per_state, int B, unsigned *amax, hipStream_t stream) {
     if (B <= 0 || per_state == 0) return hipSuccess;
     size_t bx = (per_state / 8 + 255) / 256;
     if (bx > 1024) bx = 1024;
     if (bx == 0) bx = 1;
-    amax_bf16_kernel<<<dim3((unsigned)bx, (unsigned)B), 256, 0, stream>>>((const unsigned short *)x, per_state, amax,
-                                                                         amax_stride);
+    amax_bf16_kernel<<<dim3((unsigned)bx, (unsigned)B, 3), 256, 0, stream>>>(
+        (const unsigned short *)x[0], (const unsigned short *)x[1], (const unsigned short *)x[2], per_state, amax);
     return hipGetLastError();
 }
 

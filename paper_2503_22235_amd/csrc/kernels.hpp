@@ -156,10 +156,10 @@ inline bool gemm_resid_ln_applies(int N) { return N == 512; }
 // any copy, launch_amax_fold reduces slots [0, n) into copy 0.
 constexpr int AMAX_SHARDS = 64;
 constexpr int AMAX_STRIDE = 512;            // slots per copy (>= 8 per state x 64 states)
-// per-state amax of bf16 data: state b covers elements [b*per_state, (b+1)*per_state);
-// atomicMax into amax[shard*AMAX_STRIDE + b*amax_stride] (fold afterwards)
-hipError_t launch_amax_bf16(const void *x, size_t per_state, int B, unsigned *amax, int amax_stride,
-                            hipStream_t stream);
+// per-state amax of three bf16 tensors: state b covers elements [b*per_state,
+// (b+1)*per_state) of x[i]; atomicMax into amax[shard*AMAX_STRIDE + 3*b + i] (fold
+// afterwards)
+hipError_t launch_amax_bf16(const void *const x[3], size_t per_state, int B, unsigned *amax, hipStream_t stream);
 // dst[i] = ptrs[i] for i < n (n <= 64): a batch's state pointers written by
 // a kernel, in stream order, with no host buffer to keep alive
 struct PtrList {
