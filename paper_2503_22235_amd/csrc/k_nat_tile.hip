@@ -1687,8 +1687,8 @@ hipError_t launch_tile_q(const NatArgs &a, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// Heads that a workgroup of the ring kernels walks one after the other: 4 or 2
-// where they divide H and still leave `least` workgroups, about 5 (bf16, 3 a
+// Heads that a workgroup of the ring kernels walks one after the other: `most`
+// or fewer, where they divide H and still leave `least` workgroups, about 5 (bf16, 3 a
 // CU) or 8 (e4m3, 4 a CU) rounds of those that run at once; below, the last
 // round leaves too many CUs idle.  Window 5x7x7, 16 heads, us with 1 / 2 / 4 / 8
 // heads: 8x90x180 bf16 from token-major q and k 371 / 337 / 330 / 345 (two heads
@@ -1696,8 +1696,8 @@ hipError_t launch_tile_q(const NatArgs &a, hipStream_t stream) {
 // 1010 / 970 / 960 / 967, B = 1 (16928 workgroups at 1) 289 / 277 / 290.  Below
 // the line, with 1 / 2 / 4: 5x45x90, 4 heads, bf16 21.5 / 23 / 31 (1152
 // workgroups at 1), 8x18x20, 16 heads, B = 3, e4m3 29 / 29.5 / 42.5 (1440).
-int heads_per_workgroup(const NatArgs &a, int ntiles, long least) {
-    for (int n = 4; n > 1; n >>= 1)
+int heads_per_workgroup(const NatArgs &a, int ntiles, int most, long least) {
+    for (int n = most; n > 1; n >>= 1)
         if (a.H % n == 0 && (long)ntiles * (a.H / n) * a.B >= least) return n;
     return 1;
 }
@@ -1717,7 +1717,9 @@ hipError_t launch_ring(const NatArgs &a, hipStream_t stream) {
     constexpr int TBLP = tbl_padded<KZ, KY, KX>();
     if (!a.tbl_ready) nat_bias_prep<KZ, KY, KX, QSCALED, false><<<(a.H * TBLP + 255) / 256, 256, 0, stream>>>(a);
     const int ntiles = ((a.Z + TZ - 1) / TZ) * ((a.Y + TY - 1) / TY) * ((a.X + TX - 1) / TX);
-    const int nh = heads_per_workgroup(a, ntiles, 4096);
+    // (head-major rows: 4 heads are no faster than 2, and the halo rows that the
+    // next tiles share have left L2 by then: fetch 1.02 GB against 0.73 per block)
+    const int nh = heads_per_workgroup(a, ntiles, a.ts > 32 ? 4 : 2, 4096);
     const long total = (long)ntiles * (a.H / nh) * a.B;
     const unsigned grid = (unsigned)(((total + 7) >> 3) << 3);
     nat_ring_kernel<KZ, KY, KX, QSCALED><<<grid, 256, ring_lds(KZ, KY), stream>>>(a, tile_div(a, nh), nh);
@@ -1778,7 +1780,7 @@ hipError_t launch_ring_fp8(const NatArgs &a, hipStream_t stream) {
     // (q in bf16: scores of any size, and where they send every workgroup on a
     // second walk the next head's levels were loaded for nothing: standard
     // normal q and k at 8x90x180 747 us with one head, 764 with 2, 818 with 4)
-    const int nh = a.q8 ? heads_per_workgroup(a, ntiles, 8192) : 1;
+    const int nh = a.q8 ? heads_per_workgroup(a, ntiles, 4, 8192) : 1;
     const long total = (long)ntiles * (a.H / nh) * a.B;
     const unsigned grid = (unsigned)(((total + 7) >> 3) << 3);
     nat_ring_fp8_kernel<KZ, KY, KX><<<grid, 256, ring8_lds(KZ, KY), stream>>>(a, tile_div(a, nh), nh);
