@@ -158,29 +158,44 @@ __device__ __forceinline__ Split3 split3(const i32x4 (&raw)[2]) {
     return s;
 }
 
-// A wave's tiles once more with f32 MFMAs, operands straight from global
-// memory: where the partial sums above are not finite (an operand is, or the
-// sum overflows), this gives what float32 arithmetic gives.
+// The sums that are not finite once more with f32 MFMAs, operands straight from
+// global memory: an operand is not finite, or the sum overflows, and this gives
+// what float32 arithmetic gives.  The finite sums of a tile are kept, so that a
+// row's result does not depend on its neighbours.
 template <int TM, int TN>
-__device__ void f32_tiles(const float *A, const float *W, int M, int K, int r0, int n0, int g, int r16, f32x4 (&acc)[TN][TM]) {
-    const float *ar[TM], *wr[TN];
+__device__ void f32_redo(const float *A, const float *W, int M, int K, int r0, int n0, int g, int r16, f32x4 (&acc)[TN][TM]) {
+    const float *ar[TM];
 #pragma unroll
     for (int i = 0; i < TM; ++i) ar[i] = A + (size_t)min(r0 + 16 * i + r16, M - 1) * K + 8 * g;
 #pragma unroll
-    for (int j = 0; j < TN; ++j) wr[j] = W + (size_t)(n0 + 16 * j + r16) * K + 8 * g;
+    for (int j = 0; j < TN; ++j) {
+        bool bad = false;
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int i = 0; i < TM; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // lane group g contracts k = 8 g + s over the 8 steps s
-    for (int k = 0; k < K; k += 32)
-#pragma unroll 1
-        for (int s = 0; s < 8; ++s)
+            for (int c = 0; c < 4; ++c) bad |= !__builtin_isfinite(acc[j][i][c]);
+        if (!__builtin_amdgcn_ballot_w64(bad)) continue;
+        const float *wr = W + (size_t)(n0 + 16 * j + r16) * K + 8 * g;
+        f32x4 t[TM];
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+        for (int i = 0; i < TM; ++i) t[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // lane group g contracts k = 8 g + s over the 8 steps s
+        for (int k = 0; k < K; k += 32)
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
-                    acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(wr[j][k + s], ar[i][k + s], acc[j][i], 0, 0, 0);
+            for (int h = 0; h < 2; ++h) {
+                const f32x4 w = *(const f32x4 *)(wr + k + 4 * h);
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    const f32x4 a = *(const f32x4 *)(ar[i] + k + 4 * h);
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) t[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s], a[s], t[i], 0, 0, 0);
+                }
+            }
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[j][i][c] = __builtin_isfinite(acc[j][i][c]) ? acc[j][i][c] : t[i][c];
+    }
 }
 
 // Epilogue of a V tile of the QKV projection (swapped operands): acc[j][i]
@@ -796,15 +811,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
     stage(std::true_type{}, 0);
     for (int kt = 1; kt < nk; ++kt) stage(std::false_type{}, kt);
     if constexpr (F32) {
-        bool bad = false;
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) bad |= !__builtin_isfinite(acc[j][i][c]);
-        if (__builtin_amdgcn_ballot_w64(bad))
-            f32_tiles<TM, TN>((const float *)A, (const float *)W, M, K, m0 + wm * WM, n0 + wn * WN, g, r16, acc);
+        f32_redo<TM, TN>((const float *)A, (const float *)W, M, K, m0 + wm * WM, n0 + wn * WN, g, r16, acc);
         tile_epilogue_f32<EPI, TM, TN>(ep, M, N, m0 + wm * WM, n0, wn * WN, g, r16, acc);
     } else if constexpr (epi_resid_ln(EPI)) {
         static_assert((2 * WGN * BM + 2 * BN) * 4 <= SLOT && BN <= 2 * NW * 64, "row sums and ln_g, ln_b fit a slot");
