@@ -127,9 +127,13 @@ __device__ __forceinline__ f32x4 mma_fp8(const i32x4 (&wf)[2], const i32x4 (&af)
                 : __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(w, a, FIRST ? z : c, 0, 0, 0, 0, 0, 0);
 }
 
-// Float32 operands on the bf16 matrix cores: x = x1 + x2 + x3 exactly, each
-// part x's remainder rounded to nearest bf16 (8 significant bits; so |x2| <=
-// 2^-9 |x|, |x3| <= 2^-18 |x|).  A product is the sum of the six partial
+// Float32 operands on the bf16 matrix cores: SPLIT_SCALE x = x1 + x2 + x3
+// exactly, each part the remainder rounded to nearest bf16 (8 significant bits;
+// so |x2| <= 2^-9 |x1|, |x3| <= 2^-18 |x1|).  The last bit of x is 2^-149 or
+// more: times 2^24 it is 2^-125, a normal bf16, so no part is lost however small
+// x is (without the factor the parts of x < 2^-110 fell under bf16's smallest
+// values: errors of 2^-22 of x at 2^-112, 2^-8 at 2^-126).  Values of 2^104 and
+// more and sums of 2^80 and more overflow and are done again (f32_finish).  A product is the sum of the six partial
 // products x_i w_j with i + j <= 4, smallest first; the three left out are
 // below 2^-26 of it, with either sign.  The products of bf16 values are exact
 // and the sum takes 6 roundings per 32 k where 16x16x4 f32 MFMAs take 8, at
@@ -139,31 +143,42 @@ __device__ __forceinline__ f32x4 mma_fp8(const i32x4 (&wf)[2], const i32x4 (&af)
 // 5.7e-7 and 1.15e-6 with f32 MFMAs.  M = 129600, N = 1536, K = 512: 2158 ->
 // 1191 us (171 TFLOP/s of products; the f32 MFMA kernel reached 94).  Lane and
 // k layout are those of one 16x16x32 operand (8 consecutive k).
+constexpr float SPLIT_SCALE = 0x1p24f, UNSPLIT = 0x1p-48f;
 struct Split3 {
     i32x4 p[3];
 };
 __device__ __forceinline__ Split3 split3(const i32x4 (&raw)[2]) {
     Split3 s;
+    // remainders by the bf16 dot product, a - part as part * -1 + other * 0 + a: one
+    // instruction where unpacking and subtracting take two (products and differences
+    // are exact; 4e9 random pairs of all exponents gave the bits of the subtraction).
+    // It pays for the scaling: a float32 block at 8x90x180, C = 512, takes 6.10 ms
+    // without the factor, 6.30 with it and subtractions, 6.19 with it and this.
+    // The constants stay in registers.
+    unsigned lo = 0x0000bf80u, hi = 0xbf800000u;
+    asm("" : "+s"(lo), "+s"(hi));
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        float a = __int_as_float(raw[q >> 1][2 * (q & 1)]), b = __int_as_float(raw[q >> 1][2 * (q & 1) + 1]);
+        float a = __int_as_float(raw[q >> 1][2 * (q & 1)]) * SPLIT_SCALE, b = __int_as_float(raw[q >> 1][2 * (q & 1) + 1]) * SPLIT_SCALE;
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
             const unsigned u = pack_bf16x2(a, b);
             s.p[t][q] = (int)u;
-            a -= __uint_as_float(u << 16);
-            b -= __uint_as_float(u & 0xffff0000u);
+            if (t == 2) break;
+            a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, u), __builtin_bit_cast(bf16x2_t, lo), a, false);
+            b = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, u), __builtin_bit_cast(bf16x2_t, hi), b, false);
         }
     }
     return s;
 }
 
-// The sums that are not finite once more with f32 MFMAs, operands straight from
-// global memory: an operand is not finite, or the sum overflows, and this gives
-// what float32 arithmetic gives.  The finite sums of a tile are kept, so that a
-// row's result does not depend on its neighbours.
+// Sums of split products to their own scale; those that are not finite are done
+// again with f32 MFMAs, operands straight from global memory: an operand is not
+// finite, or the scaled sum overflows, and this gives what float32 arithmetic
+// gives.  The finite sums of a tile are kept, so that a row's result does not
+// depend on its neighbours.
 template <int TM, int TN>
-__device__ void f32_redo(const float *A, const float *W, int M, int K, int r0, int n0, int g, int r16, f32x4 (&acc)[TN][TM]) {
+__device__ void f32_finish(const float *A, const float *W, int M, int K, int r0, int n0, int g, int r16, f32x4 (&acc)[TN][TM]) {
     const float *ar[TM];
 #pragma unroll
     for (int i = 0; i < TM; ++i) ar[i] = A + (size_t)min(r0 + 16 * i + r16, M - 1) * K + 8 * g;
@@ -174,7 +189,11 @@ __device__ void f32_redo(const float *A, const float *W, int M, int K, int r0, i
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int c = 0; c < 4; ++c) bad |= !__builtin_isfinite(acc[j][i][c]);
-        if (!__builtin_amdgcn_ballot_w64(bad)) continue;
+        if (!__builtin_amdgcn_ballot_w64(bad)) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) acc[j][i] *= UNSPLIT;
+            continue;
+        }
         const float *wr = W + (size_t)(n0 + 16 * j + r16) * K + 8 * g;
         f32x4 t[TM];
 #pragma unroll
@@ -194,7 +213,7 @@ __device__ void f32_redo(const float *A, const float *W, int M, int K, int r0, i
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc[j][i][c] = __builtin_isfinite(acc[j][i][c]) ? acc[j][i][c] : t[i][c];
+            for (int c = 0; c < 4; ++c) acc[j][i][c] = __builtin_isfinite(acc[j][i][c]) ? acc[j][i][c] * UNSPLIT : t[i][c];
     }
 }
 
@@ -811,7 +830,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
     stage(std::true_type{}, 0);
     for (int kt = 1; kt < nk; ++kt) stage(std::false_type{}, kt);
     if constexpr (F32) {
-        f32_redo<TM, TN>((const float *)A, (const float *)W, M, K, m0 + wm * WM, n0 + wn * WN, g, r16, acc);
+        f32_finish<TM, TN>((const float *)A, (const float *)W, M, K, m0 + wm * WM, n0 + wn * WN, g, r16, acc);
         tile_epilogue_f32<EPI, TM, TN>(ep, M, N, m0 + wm * WM, n0, wn * WN, g, r16, acc);
     } else if constexpr (epi_resid_ln(EPI)) {
         static_assert((2 * WGN * BM + 2 * BN) * 4 <= SLOT && BN <= 2 * NW * 64, "row sums and ln_g, ln_b fit a slot");

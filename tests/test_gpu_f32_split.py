@@ -1,4 +1,5 @@
-"""float32 linear maps on split operands: what a row holds reaches that row only."""
+"""float32 linear maps on split operands: what a row holds reaches that row only,
+and operands of any size keep all their bits."""
 import numpy as np
 import pytest
 
@@ -41,6 +42,38 @@ def test_rows_beside_one_that_is_not_finite(env, M, N, K):
     assert torch.equal(out[keep], clean[keep])
     assert torch.isnan(out[37]).all() and torch.isnan(out[:, 5]).all()
     assert not torch.isfinite(out[3]).any() and not torch.isfinite(out[:, N - 2]).any()
+
+
+@pytest.mark.parametrize("ea,ew", [(-126, 0), (-126, 60), (60, -126), (-112, 0), (0, -118), (-60, -60), (110, 0), (0, 120), (-126, 126), (60, 60)])
+@pytest.mark.parametrize("M,N,K", [(70, 64, 96), (5200, 1024, 160)])
+def test_powers_of_two_commute(env, M, N, K, ea, ew):
+    """Operands in +-[1, 2) times powers of two, so that no float32 operation
+    rounds differently: the result is that of the operands themselves times both
+    powers, bit for bit, down to the smallest normal operands."""
+    wm, torch, ctx = env
+    print("powers of two", M, N, K, ea, ew, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(M)
+
+    def draw(r, c):
+        t = torch.rand((r, c), generator=gen, device="cuda") + 1.0
+        return torch.where(torch.rand((r, c), generator=gen, device="cuda") < 0.5, -t, t)
+
+    a, w, b = draw(M, K), draw(N, K), torch.zeros(N, device="cuda")
+    run = lambda a, w: wm.wm_linear(M, N, K, wm.WM_F32, a, w, b, 0, out := torch.empty((M, N), device="cuda")) or out
+    ref = run(a, w)
+    exact = a.double() @ w.double().T
+    assert (ref.double() - exact).norm() < 2e-6 * exact.norm()
+    pow2 = lambda e: torch.tensor(2.0, dtype=torch.float64).pow(e).item()
+    out = run(a * pow2(ea), w * pow2(ew))
+    # (in float64: the powers of a product may lie beyond float32's range)
+    got = out.double() / pow2(ea) / pow2(ew)
+    rel = (got - exact).norm() / exact.norm()
+    print("  rel_l2", rel.item(), flush=True)
+    assert rel < 2e-6
+    big = max(ea, ew) >= 104 or ea + ew >= 70        # (past the split's range: float32 MFMAs, another order of the sums)
+    small = ea + ew < -110                           # (sums may fall below the smallest normal number)
+    if not big and not small:
+        assert torch.equal(got, ref.double())
 
 
 def test_state_beside_one_that_has_diverged(env):
