@@ -28,6 +28,9 @@ typedef __attribute__((address_space(3))) void lds_void;
 // EPI_RESID and EPI_RESID_LN on states in separate buffers whose token count
 // is not a multiple of 64: the 64 rows of a wave may lie in several states.
 constexpr int EPI_RESID_SPLIT = 6, EPI_RESID_LN_SPLIT = 7;
+// EPI_GELU of bf16 maps whose N is not a multiple of 128 (no processor's): erf
+// by 7.1.28, as these maps have always had it.
+constexpr int EPI_GELU_28 = 8;
 constexpr bool epi_resid(int e) { return e == EPI_RESID || e == EPI_RESID_SPLIT; }
 constexpr bool epi_resid_ln(int e) { return e == EPI_RESID_LN || e == EPI_RESID_LN_SPLIT; }
 inline bool splits(const EpiArgs &ep) { return ep.resid_ptrs && ep.T % 64 != 0; }
@@ -584,6 +587,10 @@ __device__ __forceinline__ void tile_epilogue(const EpiArgs &ep, int M, int N, i
             if constexpr (EPI == EPI_GELU) {
 #pragma unroll
                 for (int c = 0; c < 8; ++c) v[c] = gelu_as4(v[c]);
+            }
+            if constexpr (EPI == EPI_GELU_28) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c) v[c] = gelu_as(v[c]);
             }
             if constexpr (epi_qkv(EPI) || OUT8) {
 #pragma unroll
@@ -1248,9 +1255,16 @@ hipError_t launch_tiles(const void *A, const void *W, int M, int N, int K, EpiKi
         if (!f) return hipErrorInvalidValue;
         return launch_chunks(f, BM, BN, nth, G::lds, row_bytes, A, W, M, N, K, ep, t.tpw, t.rw, stream);
     };
+    typedef LdsGemm<64, 64, 2, 2, 2, 4, FP8 ? T_E4M3 : T_BF16> G64;
+    if constexpr (!FP8)
+        if (epi == EPI_GELU && N % 128 && !ep.perm) {
+            const gemm_fn f = G64::template get<EPI_GELU_28, false>();
+            if (!f) return hipErrorInvalidValue;
+            return launch_chunks(f, 64, 64, 256, G64::lds, row_bytes, A, W, M, N, K, ep, 1, 0, stream);
+        }
     if (t.bm == 256) return run(PpGemm<256, 256, FP8>{}, 256, 256, 512);
     if (t.bm == 128) return run(LdsGemm<128, 128, 2, 2, 2, 2, FP8 ? T_E4M3 : T_BF16>{}, 128, 128, 256);
-    return run(LdsGemm<64, 64, 2, 2, 2, 4, FP8 ? T_E4M3 : T_BF16>{}, 64, 64, 256);
+    return run(G64{}, 64, 64, 256);
 }
 
 // EPI_RESID_LN: the tile spans N = 512; one row block per workgroup (the row
