@@ -1,5 +1,10 @@
-"""Tile choice of the linear maps.  It is read from the host header by a small
-program built here.
+"""Tile choice of the linear maps, and the 256-wide tiles that it sends large
+ones to: one K stage and odd numbers of them, several feature tiles or row
+blocks per workgroup (with a short last group), rows just off a tile, and
+residual rows that straddle states.
+
+The choice is read from the host header by a small program built here, so that
+the sizes below stay on the tiles that they are meant for.
 """
 import ctypes
 import os
@@ -8,7 +13,18 @@ import subprocess
 import numpy as np
 import pytest
 
+import wm_synth as S
+from oracle import wm_oracle as O
+
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2503_22235_amd", "csrc")
+
+# M, N, K stages of 128 bytes, epilogue, feature tiles (N = 512: row blocks) per workgroup
+WIDE = [(59907, 2048, 1, 0, 4), (80131, 1536, 1, 1, 2), (32259, 2048, 2, 1, 4), (64259, 1536, 2, 0, 3),
+        (120067, 1024, 3, 0, 1), (31235, 1536, 5, 2, 3), (20227, 3072, 5, 1, 4), (126211, 512, 5, 2, 2),
+        (58371, 512, 8, 0, 2), (20739, 2048, 8, 2, 3), (41475, 768, 8, 1, 1)]
+SLICE = 2999                                # rows: too few for a 256-wide tile at these sizes
+STATES = S.Grid(Z=5, Y=37, X=31, C=512, heads=16, Kz=3, Ky=5, Kx=5)     # 5735 tokens: 39 (mod 64)
+NSTATES = 3
 
 
 @pytest.fixture(scope="module")
@@ -54,3 +70,85 @@ def test_plans_are_legal(plan):
         assert bm in (64, 128, 256) and 1 <= tpw <= wmax and (bm == 256 or tpw == 1)
         assert bm != 256 or N % 256 == 0
         assert not rw or N == 512
+
+
+def test_sizes_of_the_gpu_tests_are_wide(plan):
+    for M, N, nk, epi, w in WIDE:
+        assert plan(M, N, nk, epi == 2)[:2] == (256, w), (M, N, nk)
+        assert plan(SLICE, N, nk, epi == 2)[0] < 256
+    T, g = STATES.Z * STATES.Y * STATES.X, STATES
+    for stage in (128, 64):                   # e4m3, bf16: MLP2 of the stacked states
+        assert plan(NSTATES * T, g.C, 4 * g.C // stage, 1)[0] == 256
+        assert plan(T, g.C, 4 * g.C // stage, 1)[0] < 256
+    assert T % 64 and NSTATES * T > 64 * 256 >= T     # the fused LayerNorm's 128-row tiles, and its 64-row ones
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    import paper_2503_22235_amd as wm
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    wm.lib()
+    ctx = wm.wm_ctx_create(0)
+    yield wm, torch, ctx
+    torch.cuda.synchronize()
+    ctx.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("M,N,stages,epi,walk", WIDE)
+def test_wide_and_narrow_tiles_agree(env, M, N, stages, epi, walk, fp8):
+    """All rows at once (256-wide tiles) against slices of them (narrow tiles), bit
+    for bit, and some rows against float64 on the same rounded operands (relative
+    L2: bf16 outputs 5e-3, whose rounding is 1.1e-3 rms; the float32 residual
+    update 1e-5, in e4m3 1e-4, as the 128-deep MFMA sums at less than float32)."""
+    wm, torch, ctx = env
+    K = stages * (128 if fp8 else 64)
+    print("wide", M, N, K, "epilogue", epi, "fp8" if fp8 else "bf16", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(M + N)
+    dt = torch.float8_e4m3fn if fp8 else torch.bfloat16
+    a = torch.randn((M, K), generator=gen, device="cuda").to(dt)
+    w = (torch.randn((N, K), generator=gen, device="cuda") / K ** 0.5).to(dt)
+    b = 0.1 * torch.randn(N, generator=gen, device="cuda")
+    x0 = torch.randn((M, N), generator=gen, device="cuda") if epi == 2 else None
+
+    def run(lo, hi):
+        out = x0[lo:hi].clone() if epi == 2 else torch.empty((hi - lo, N), dtype=torch.bfloat16, device="cuda")
+        if fp8:
+            wm.wm_linear_fp8(hi - lo, N, K, a[lo:hi], 1.0, w, 1.0, b, epi, out)
+        else:
+            wm.wm_linear(hi - lo, N, K, wm.WM_BF16, a[lo:hi], w, b, epi, out)
+        return out
+
+    out = run(0, M)
+    for lo in range(0, M, SLICE):
+        hi = min(lo + SLICE, M)
+        assert torch.equal(run(lo, hi), out[lo:hi]), lo
+    rows = torch.cat([torch.arange(3), torch.randint(0, M, (90,)), torch.arange(M - 3, M)]).cuda()
+    ref = a[rows].double().cpu().numpy() @ w.double().cpu().numpy().T + b.double().cpu().numpy()
+    if epi == 2:
+        ref = x0[rows].double().cpu().numpy() + ref
+    elif epi == 1:
+        ref = O.gelu(ref)
+    assert O.rel_l2(out[rows].double().cpu().numpy(), ref) < ((1e-4 if fp8 else 1e-5) if epi == 2 else 5e-3)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec", [1, 2])
+def test_states_straddling_wide_tiles(env, prec):
+    """C = 512 states of 5735 tokens, three in separate buffers (128-row tiles of the
+    fused LayerNorm, 256-wide ones of MLP2; a wave's rows lie in two states):
+    bit-identical to the stacked states and to each state alone (narrow tiles)."""
+    wm, torch, ctx = env
+    g, B = STATES, NSTATES
+    print("straddling wide tiles prec", prec, flush=True)
+    p = wm.wm_processor_create(ctx, g, 1, 4, prec, S.processor_params(g, 1, 1))
+    x = torch.from_numpy(S.latent_state(g, B, 6)).cuda()
+    bufs, alone = ([x[b:b + 1].clone() for b in range(B)] for _ in range(2))
+    wm.wm_processor_step(ctx, p, B, x)
+    wm.wm_processor_step_states(ctx, p, B, torch.tensor([t.data_ptr() for t in bufs], dtype=torch.int64, device="cuda"))
+    for b in range(B):
+        wm.wm_processor_step(ctx, p, 1, alone[b])
+        assert torch.equal(bufs[b], x[b:b + 1]) and torch.equal(alone[b], x[b:b + 1]), b
+    p.close()
