@@ -21,6 +21,7 @@
 // P.V contraction takes its k index in that same order (k-slot 8g + 4j + i
 // <-> key 16j + 4g + i), so the score registers feed the second MFMA
 // without any data movement.
+#include <algorithm>
 #include <cmath>
 
 #include "kernels.hpp"
@@ -78,10 +79,11 @@ struct Vec {
 constexpr int UB = 512;                 // halo units (level, lat, 4 lons) per pass: whole chunks of 8
 constexpr int BIAS_LDS = 8192;          // longest bias table (floats) that is copied to LDS
 
-// A workgroup: four waves, groups of the same levels and lats that follow each
-// other in lon.  The units of their common halo -- 4 lon slots of one (level,
-// lat) -- are listed in LDS, UB at a time, with the offset of their row; so are
-// the lon slots of each wave and the head's bias table.  A key's address is then
+// A workgroup: nw waves (four, or fewer where lon has fewer groups), groups of
+// the same levels and lats that follow each other in lon.  The units of their
+// common halo -- 4 lon slots of one (level, lat) -- are listed in LDS, UB at a
+// time, with the offset of their row; so are the lon slots of each wave and the
+// head's bias table.  A key's address is then
 // one addition and a chunk has no divisions or wrap-arounds.  What bounds it:
 // the f32 MFMAs (32 of 32 cycles per chunk) and as many cycles of other
 // instructions beside them.  K is loaded one chunk ahead.  A lane takes V
@@ -93,16 +95,17 @@ constexpr int BIAS_LDS = 8192;          // longest bias table (floats) that is c
 //   FAR: rows beyond 32-bit byte offsets, or too many lon slots for the table:
 //   row and slot hold tokens and the address is computed in 64 bits.
 template <typename T, bool FAR>
-__global__ __launch_bounds__(256, 4) void nat_generic_kernel(NatArgs p, int ngq, int per, int nslot, bool bias_lds) {
+__global__ __launch_bounds__(256, 4) void nat_generic_kernel(NatArgs p, long first, long count, int ngq, int nw, int nslot, bool bias_lds) {
     __shared__ i32x4 unit[UB + 8];                 // row offset, slots on the level and lat axes, first lon slot
-    extern __shared__ __align__(16) float dyn[];                 // [4][nslot] lon offsets (not FAR), then 4 + table + 8 biases
+    extern __shared__ __align__(16) float dyn[];                 // [nw][nslot] lon offsets (not FAR), then 4 + table + 8 biases
     const int ngz = (p.Z + GZ - 1) / GZ, ngy = (p.Y + GY - 1) / GY, ngx = (p.X + GX - 1) / GX;
-    const int L = blockIdx.x;
-    long t = (long)(L & 7) * per + (L >> 3);       // XCD-aware: neighbours share an L2
-    if (t >= (long)ngq * ngy * ngz * p.H * p.B) return;
+    const int L = blockIdx.x, nth = 64 * nw;
+    long t = (long)(L & 7) * (gridDim.x >> 3) + (L >> 3);      // XCD-aware: neighbours share an L2
+    if (t >= count) return;
+    t += first;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, g = lane >> 4, r16 = lane & 15;
-    const int gxw = 4 * (int)(t % ngq) + wave; t /= ngq;
+    const int gxw = nw * (int)(t % ngq) + wave; t /= ngq;
     const int gy = (int)(t % ngy); t /= ngy;
     const int gz = (int)(t % ngz); t /= ngz;
     const int h = (int)(t % p.H); t /= p.H;
@@ -134,13 +137,13 @@ __global__ __launch_bounds__(256, 4) void nat_generic_kernel(NatArgs p, int ngq,
     const T8 qf = *(const T8 *)(qb + qtok * p.ts + 8 * g);    // channels 8g .. of this lane's query
 
     unsigned *lons = (unsigned *)dyn + wave * nslot;
-    float *bias_s = dyn + (FAR ? 0 : 4 * nslot) + 4;
+    float *bias_s = dyn + (FAR ? 0 : nw * nslot) + 4;
     // lon of slot s (a slot past the halo: slot 0's, a key of the halo; its score is masked)
     auto lon = [&](int s) { return coord(ax, s < ax.n ? s : 0); };
     if constexpr (!FAR)
         for (int e = lane; e < nslot; e += 64) lons[e] = (unsigned)lon(e) * tsb;
     if (bias_lds)
-        for (int e = (int)threadIdx.x - 4; e < tbl + 8; e += 256)
+        for (int e = (int)threadIdx.x - 4; e < tbl + 8; e += nth)
             bias_s[e] = e >= 0 && e < tbl ? rpb[e] * p.bscale : 0.f;
     auto load_k = [&](unsigned off, int slot) {
         if constexpr (FAR) return *(const T8 *)(kb + (long)((int)off + lon(slot)) * p.ts + 8 * g);
@@ -155,7 +158,7 @@ __global__ __launch_bounds__(256, 4) void nat_generic_kernel(NatArgs p, int ngq,
     for (int ub = 0; ub < nunit; ub += UB) {
         const int nu = min(UB, nunit - ub), nchunk = (nu + 7) >> 3;
         if (ub > 0) __syncthreads();
-        for (int e = threadIdx.x; e < 8 * nchunk; e += 256) {
+        for (int e = threadIdx.x; e < 8 * nchunk; e += nth) {
             const int u = min(ub + e, nunit - 1), row = u / nx4;
             const int sz = row / ay.n, sy = row - sz * ay.n;
             const unsigned tok = (unsigned)(coord(az, sz) * p.Y + coord(ay, sy)) * (unsigned)p.X;
@@ -314,18 +317,25 @@ hipError_t launch_nat(const NatArgs &a, bool bf16in, hipStream_t stream) {
 
 hipError_t launch_nat_generic(const NatArgs &a, bool bf16in, hipStream_t stream) {
     if (a.vt || a.q8 || a.o8) return hipErrorInvalidValue;     // reads token-major bf16/f32 q, k, v only
-    const int ngq = ((a.X + GX - 1) / GX + 3) / 4;      // workgroups of four lon groups
+    // Workgroups of up to four lon groups, as even as they come: a wave without a
+    // group would walk a halo for nothing (float32, 8 heads, window 3x5x1, us, four
+    // waves always / these: 8x512x1 tokens 61.4 / 20.0, 8x512x2 61.6 / 20.3).
+    const int ngx = (a.X + GX - 1) / GX, ngq = (ngx + 3) / 4, nw = (ngx + ngq - 1) / ngq;
     const long total = (long)((a.Z + GZ - 1) / GZ) * ((a.Y + GY - 1) / GY) * ngq * a.H * a.B;
     if (total == 0) return hipSuccess;
-    const int per = (int)((total + 7) / 8);
-    const unsigned grid = (unsigned)per * 8u;
     const int nslot = (GX + a.Kx - 1 + 3) & ~3;
     const long tbl = (long)(2 * a.Kz - 1) * (2 * a.Ky - 1) * (2 * a.Kx - 1);
     const size_t span = (size_t)a.Z * a.Y * a.X * (size_t)a.ts * (bf16in ? 2 : 4);
     const bool far = span >= (1ull << 32) || nslot > 1024;
     const bool bias_lds = tbl <= BIAS_LDS;
-    const size_t lds = (far ? 0 : 16 * (size_t)nslot) + (bias_lds ? 4 * (size_t)(tbl + 12) : 0);
-    auto go = [&](auto kernel) { kernel<<<grid, 256, lds, stream>>>(a, ngq, per, nslot, bias_lds); };
+    const size_t lds = (far ? 0 : 4 * (size_t)nw * nslot) + (bias_lds ? 4 * (size_t)(tbl + 12) : 0);
+    const long most = 0x7fffffff / (64 * nw) & ~7;      // workgroups per launch: a grid has less than 2^31 threads
+    auto go = [&](auto kernel) {
+        for (long first = 0; first < total; first += most) {
+            const long count = std::min(most, total - first);
+            kernel<<<(unsigned)((count + 7) & ~7L), 64 * nw, lds, stream>>>(a, first, count, ngq, nw, nslot, bias_lds);
+        }
+    };
     if (bf16in) far ? go(nat_generic_kernel<bf16, true>) : go(nat_generic_kernel<bf16, false>);
     else far ? go(nat_generic_kernel<float, true>) : go(nat_generic_kernel<float, false>);
     return hipGetLastError();
