@@ -34,6 +34,7 @@
 #include <cmath>
 
 #include "kernels.hpp"
+#include "nat_plan.hpp"
 
 namespace wm {
 namespace {
@@ -474,7 +475,7 @@ __global__ __launch_bounds__(256, 2) void nat_tile_kernel(NatArgs p, int ZWmax, 
 // q ^ kswz(R, c), so the 16 lanes of a fragment read hit distinct banks.
 // Arithmetic, key order and softmax reference are those of nat_tile_kernel.
 //
-// A workgroup walks nh heads (heads_per_workgroup) over the same tile: the
+// A workgroup walks nh heads (nat_heads) over the same tile: the
 // addresses are worked out once, the levels follow each other without a gap
 // and the table, the queries and their own keys of the next head load while
 // the last one's output is written.  Tiles go lon, level, lat: the two level
@@ -1687,21 +1688,6 @@ hipError_t launch_tile_q(const NatArgs &a, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// Heads that a workgroup of the ring kernels walks one after the other: `most`
-// or fewer, where they divide H and still leave `least` workgroups, about 5 (bf16, 3 a
-// CU) or 8 (e4m3, 4 a CU) rounds of those that run at once; below, the last
-// round leaves too many CUs idle.  Window 5x7x7, 16 heads, us with 1 / 2 / 4 / 8
-// heads: 8x90x180 bf16 from token-major q and k 371 / 337 / 330 / 345 (two heads
-// share K's cache lines), from head-major ones 281 / 280 / 282; e4m3, B = 4
-// 1010 / 970 / 960 / 967, B = 1 (16928 workgroups at 1) 289 / 277 / 290.  Below
-// the line, with 1 / 2 / 4: 5x45x90, 4 heads, bf16 21.5 / 23 / 31 (1152
-// workgroups at 1), 8x18x20, 16 heads, B = 3, e4m3 29 / 29.5 / 42.5 (1440).
-int heads_per_workgroup(const NatArgs &a, int ntiles, int most, long least) {
-    for (int n = most; n > 1; n >>= 1)
-        if (a.H % n == 0 && (long)ntiles * (a.H / n) * a.B >= least) return n;
-    return 1;
-}
-
 size_t ring_lds(int Kz, int Ky) {
     const int tblp = (((2 * Kz - 1) * (2 * Ky - 1) * XT + NEG_RUN + 3) & ~3);
     return (size_t)tblp * 4 + 2 * (size_t)RING_SLOT;
@@ -1717,9 +1703,7 @@ hipError_t launch_ring(const NatArgs &a, hipStream_t stream) {
     constexpr int TBLP = tbl_padded<KZ, KY, KX>();
     if (!a.tbl_ready) nat_bias_prep<KZ, KY, KX, QSCALED, false><<<(a.H * TBLP + 255) / 256, 256, 0, stream>>>(a);
     const int ntiles = ((a.Z + TZ - 1) / TZ) * ((a.Y + TY - 1) / TY) * ((a.X + TX - 1) / TX);
-    // (head-major rows: 4 heads are no faster than 2, and the halo rows that the
-    // next tiles share have left L2 by then: fetch 1.02 GB against 0.73 per block)
-    const int nh = heads_per_workgroup(a, ntiles, a.ts > 32 ? 4 : 2, 4096);
+    const int nh = nat_heads((long)ntiles * a.B, a.H, a.Kz, a.ts > 32 ? NAT_TOKEN_MAJOR : NAT_HEAD_MAJOR);
     const long total = (long)ntiles * (a.H / nh) * a.B;
     const unsigned grid = (unsigned)(((total + 7) >> 3) << 3);
     nat_ring_kernel<KZ, KY, KX, QSCALED><<<grid, 256, ring_lds(KZ, KY), stream>>>(a, tile_div(a, nh), nh);
@@ -1780,7 +1764,7 @@ hipError_t launch_ring_fp8(const NatArgs &a, hipStream_t stream) {
     // (q in bf16: scores of any size, and where they send every workgroup on a
     // second walk the next head's levels were loaded for nothing: standard
     // normal q and k at 8x90x180 747 us with one head, 764 with 2, 818 with 4)
-    const int nh = a.q8 ? heads_per_workgroup(a, ntiles, 4, 8192) : 1;
+    const int nh = a.q8 ? nat_heads((long)ntiles * a.B, a.H, a.Kz, NAT_E4M3) : 1;
     const long total = (long)ntiles * (a.H / nh) * a.B;
     const unsigned grid = (unsigned)(((total + 7) >> 3) << 3);
     nat_ring_fp8_kernel<KZ, KY, KX><<<grid, 256, ring8_lds(KZ, KY), stream>>>(a, tile_div(a, nh), nh);
