@@ -95,19 +95,6 @@ __device__ __forceinline__ u32x4 pack8_bf16(const float *v) {
     return u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
 }
 
-// Wait until at most min(later, D - 2) stages of PER load instructions each
-// are still in flight (later: stages issued after the one waited for).
-template <int PER, int D>
-__device__ __forceinline__ void wait_stages(int later) {
-    if constexpr (D >= 5)
-        if (later >= 3) return wait_vmcnt<3 * PER>();
-    if constexpr (D >= 4)
-        if (later >= 2) return wait_vmcnt<2 * PER>();
-    if constexpr (D >= 3)
-        if (later >= 1) return wait_vmcnt<PER>();
-    wait_vmcnt<0>();
-}
-
 // One MFMA k-step: acc of the tile of W rows wf by activation rows af, from
 // zero if FIRST.  SWAP: the activation tile is the MFMA "A" operand, so a lane
 // holds four consecutive tokens of one output feature (the blocked V layout).
@@ -699,9 +686,9 @@ __device__ __forceinline__ void tile_epilogue_f32(const EpiArgs &ep, int M, int 
 
 // The narrow tiles: WGM x WGN waves compute one BM x BN tile, OCC workgroups
 // share a CU, and the activation and weight tiles of each K stage stream
-// through a ring of D slots, D - 1 stages ahead of the MFMAs.
+// through two slots, one stage ahead of the MFMAs.
 enum OperandType : int { T_BF16 = 0, T_E4M3 = 1, T_F32 = 2 };
-template <int BM, int BN, int D, int WGM, int WGN, int OCC, int EPI, int TY, bool PERM>
+template <int BM, int BN, int WGM, int WGN, int OCC, int EPI, int TY, bool PERM>
 __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const void *__restrict__ A, const void *__restrict__ W,
                                                          int M, int N, int K, EpiArgs ep, int, int) {
 #if defined(__HIP_DEVICE_COMPILE__)   // LDS-address-space builtins exist only in the device pass
@@ -759,7 +746,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
         for (int i = 0; i < LPB; ++i)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lds_void *)(dst + BM * BKB + 1024 * (wave + NW * i)), 16, vob[i], lk, 0, 0);
         lk += BKB;
-        lslot = lslot == D - 1 ? 0 : lslot + 1;
+        lslot ^= 1;
     };
 
     // fragment chunks of a row: as in gemm_pp_kernel
@@ -771,7 +758,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
         woff[o] = BM * BKB + (wn * WN + r16) * BKB + (pc << 4);
     }
 
-    for (int s0 = 0; s0 < D - 1 && s0 < nk; ++s0) load();
+    load();
 
     // SWAP (the V tiles of a QKV projection with ep.vt set): swapped MFMA
     // operands and the blocked-layout epilogue.
@@ -781,16 +768,13 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_lds_kernel(const voi
     int slot = 0;
     auto stage = [&](auto first_tag, int kt) {
         constexpr bool FIRST = decltype(first_tag)::value;
-        // This wave's loads of stage kt have landed once at most the loads of
-        // the later stages already issued are outstanding (loads return in
-        // order); the barrier then makes all waves' parts of stage kt visible
-        // and frees the slot read in stage kt - 1.  (A bare s_barrier:
-        // __syncthreads() would also drain the loads still in flight.)
-        wait_stages<LPA + LPB, D>(nk - 1 - kt);
+        // This wave's loads of stage kt have landed; the barrier then makes all
+        // waves' parts of it visible and frees the slot read in stage kt - 1.
+        wait_vmcnt<0>();
         __builtin_amdgcn_s_barrier();
-        if (kt + D - 1 < nk) load();
+        if (kt + 1 < nk) load();
         const unsigned char *sl = smem + slot * SLOT;
-        slot = slot == D - 1 ? 0 : slot + 1;
+        slot ^= 1;
         // (typed reads: see gemm_pp_kernel)
         i32x4 a[TM][2], w[TN][2];
 #pragma unroll
@@ -1157,13 +1141,13 @@ inline gemm_fn with_lds(K kernel) {
                ? (gemm_fn)kernel : nullptr;
 }
 
-template <int BM, int BN, int D, int WGM, int WGN, int OCC, int TY>
+template <int BM, int BN, int WGM, int WGN, int OCC, int TY>
 struct LdsGemm {
-    static constexpr size_t lds = (size_t)D * (BM + BN) * 128;
+    static constexpr size_t lds = (size_t)2 * (BM + BN) * 128;
     static_assert(lds * OCC <= 160 * 1024, "LDS per CU");
     template <int EPI, bool PERM>
     static gemm_fn get() {
-        static const gemm_fn f = with_lds<lds>(gemm_lds_kernel<BM, BN, D, WGM, WGN, OCC, EPI, TY, PERM>);
+        static const gemm_fn f = with_lds<lds>(gemm_lds_kernel<BM, BN, WGM, WGN, OCC, EPI, TY, PERM>);
         return f;
     }
 };
@@ -1177,14 +1161,6 @@ struct PpGemm {
         return f;
     }
 };
-
-template <int BM, int BN, int D, int WGM, int WGN, int OCC, bool FP8>
-hipError_t launch_lds(const void *A, const void *W, int M, int N, int K, EpiKind epi, const EpiArgs &ep, hipStream_t stream) {
-    typedef LdsGemm<BM, BN, D, WGM, WGN, OCC, FP8> G;
-    const gemm_fn f = pick<G>(epi, ep);
-    if (!f) return hipErrorInvalidValue;
-    return launch_chunks(f, BM, BN, 64 * WGM * WGN, G::lds, (size_t)K * (FP8 ? 1 : 2), A, W, M, N, K, ep, 1, 0, stream);
-}
 
 template <bool FP8>
 hipError_t launch_tiles(const void *A, const void *W, int M, int N, int K, EpiKind epi, const EpiArgs &ep, hipStream_t stream) {
@@ -1200,7 +1176,7 @@ hipError_t launch_tiles(const void *A, const void *W, int M, int N, int K, EpiKi
         if (!f) return hipErrorInvalidValue;
         return launch_chunks(f, BM, BN, nth, G::lds, row_bytes, A, W, M, N, K, ep, t.tpw, t.rw, stream);
     };
-    typedef LdsGemm<64, 64, 2, 2, 2, 4, FP8 ? T_E4M3 : T_BF16> G64;
+    typedef LdsGemm<64, 64, 2, 2, 4, FP8 ? T_E4M3 : T_BF16> G64;
     if constexpr (!FP8)
         if (epi == EPI_GELU && N % 128 && !ep.perm) {
             const gemm_fn f = G64::template get<EPI_GELU_28, false>();
@@ -1208,7 +1184,7 @@ hipError_t launch_tiles(const void *A, const void *W, int M, int N, int K, EpiKi
             return launch_chunks(f, 64, 64, 256, G64::lds, row_bytes, A, W, M, N, K, ep, 1, 0, stream);
         }
     if (t.bm == 256) return run(PpGemm<256, 256, FP8>{}, 256, 256, 512);
-    if (t.bm == 128) return run(LdsGemm<128, 128, 2, 2, 2, 2, FP8 ? T_E4M3 : T_BF16>{}, 128, 128, 256);
+    if (t.bm == 128) return run(LdsGemm<128, 128, 2, 2, 2, FP8 ? T_E4M3 : T_BF16>{}, 128, 128, 256);
     return run(G64{}, 64, 64, 256);
 }
 
@@ -1225,7 +1201,7 @@ hipError_t launch_resid_ln(const void *A, const void *W, int M, int N, int K, co
         if (!f) return hipErrorInvalidValue;
         return launch_chunks(f, BM, 512, 512, G::lds, (size_t)K * (FP8 ? 1 : 2), A, W, M, N, K, ep, 1, 1, stream);
     };
-    if (M <= 64 * 256) return run(LdsGemm<64, 512, 2, 2, 4, 1, FP8 ? T_E4M3 : T_BF16>{}, 64);
+    if (M <= 64 * 256) return run(LdsGemm<64, 512, 2, 4, 1, FP8 ? T_E4M3 : T_BF16>{}, 64);
     return run(PpGemm<128, 512, FP8>{}, 128);
 }
 
@@ -1240,8 +1216,8 @@ inline hipError_t launch_f32(const void *A, const void *W, int M, int N, int K, 
         return launch_chunks(f, B, B, 256, G::lds, (size_t)K * 4, A, W, M, N, K, ep, 1, 0, stream);
     };
     const bool n128 = N % 128 == 0 && (!epi_qkv(epi) || ep.C % 128 == 0);
-    if (n128 && (long)((M + 127) / 128) * (N / 128) > 300) return run(LdsGemm<128, 128, 2, 2, 2, 2, T_F32>{}, 128);
-    return run(LdsGemm<64, 64, 2, 2, 2, 4, T_F32>{}, 64);
+    if (n128 && (long)((M + 127) / 128) * (N / 128) > 300) return run(LdsGemm<128, 128, 2, 2, 2, T_F32>{}, 128);
+    return run(LdsGemm<64, 64, 2, 2, 4, T_F32>{}, 64);
 }
 
 }  // namespace glds

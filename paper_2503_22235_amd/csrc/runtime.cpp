@@ -22,8 +22,8 @@ size_t block_workspace_bytes(const wm_processor *p, int B) {
     const size_t M = (size_t)B * p->g.Z * p->g.Y * p->g.X;
     const size_t C = p->g.C, F = C * p->mlp;
     if (p->prec == WM_FP8_E4M3) {
-        // LN codes | q8 k8 v8, then GELU codes | o8 | bias tables
-        return al256(M * C) + fp8_big_bytes(p, B) + al256(M * C) + (size_t)B * p->g.heads * NAT_TBL_WS_FLOATS * 4;
+        // LN codes | q8 k8 v8, then GELU codes | o8
+        return al256(M * C) + fp8_big_bytes(p, B) + al256(M * C);
     }
     const size_t esz = p->prec == WM_BF16 ? 2 : 4;
     const size_t big = (3 * C > F ? 3 * C : F);
@@ -34,12 +34,7 @@ size_t block_workspace_bytes(const wm_processor *p, int B) {
         const size_t qkv = 2 * M * C * 2 + (size_t)B * p->g.Z * p->g.Y * v_blocked_xp(p->g.X) * C * 2;
         bigb = std::max(bigb, al256(qkv));
     }
-    return act + bigb + (size_t)p->g.heads * NAT_TBL_WS_FLOATS * 4;
-}
-
-// Bytes from the start of the block workspace to the bias-table scratch.
-static size_t block_tbl_offset(const wm_processor *p, int B) {
-    return block_workspace_bytes(p, B) - (size_t)p->g.heads * NAT_TBL_WS_FLOATS * 4;
+    return act + bigb;
 }
 
 int reserve_block_workspace(wm_ctx *ctx, const wm_processor *p, int B) {
@@ -99,7 +94,6 @@ int run_block(wm_ctx *ctx, const wm_processor *p, int block, int B, float *x, fl
     const size_t esz = bf ? 2 : 4;
     char *act = (char *)ctx->ws;
     char *big = act + (((size_t)M * C * esz + 255) & ~(size_t)255);
-    float *tbl_ws = (float *)((char *)ctx->ws + block_tbl_offset(p, B));
     hipError_t e;
 
     // Attention arguments first: bf16 blocks whose grid the tiled kernel
@@ -120,8 +114,8 @@ int run_block(wm_ctx *ctx, const wm_processor *p, int block, int B, float *x, fl
     na.bscale = 1.0f;
     na.B = B; na.Z = g.Z; na.Y = g.Y; na.X = g.X; na.H = H;
     na.Kz = g.Kz; na.Ky = g.Ky; na.Kx = g.Kx; na.periodic = g.periodic_mask;
-    na.tbl_ws = w.nat_tbl ? w.nat_tbl : tbl_ws;
-    na.tbl_ready = w.nat_tbl != nullptr;
+    na.tbl_ws = w.nat_tbl;     // (null: a window that the tiled kernels do not cover)
+    na.tbl_ready = 1;
     if (bf) {
         na.vt = 1;
         na.xp = v_blocked_xp(g.X);
@@ -236,7 +230,6 @@ static int run_block_fp8(wm_ctx *ctx, const wm_processor *p, int block, int B, f
     unsigned char *q8 = big, *k8 = big + (size_t)M * C, *v8 = big + al256(2 * (size_t)M * C);
     unsigned char *h8 = big;                                 // after the attention
     unsigned char *o8 = big + fp8_big_bytes(p, B);
-    float *tbl_ws = (float *)(o8 + al256((size_t)M * C));
     hipError_t e;
     int rc;
 #define WM_TIMED(kind, call, what)                                  \
@@ -284,8 +277,8 @@ static int run_block_fp8(wm_ctx *ctx, const wm_processor *p, int block, int B, f
     na.bscale = 1.0f;
     na.B = B; na.Z = g.Z; na.Y = g.Y; na.X = g.X; na.H = H;
     na.Kz = g.Kz; na.Ky = g.Ky; na.Kx = g.Kx; na.periodic = g.periodic_mask;
-    na.tbl_ws = w.nat_tbl ? w.nat_tbl : tbl_ws;
-    na.tbl_ready = w.nat_tbl != nullptr;
+    na.tbl_ws = w.nat_tbl;
+    na.tbl_ready = 1;
     na.amax = w.qkv_amax;      // the static (aq, ak, av) of every state
     na.amax_stride = 0;
     na.vt = 1;

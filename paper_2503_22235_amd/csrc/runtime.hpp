@@ -37,7 +37,7 @@ struct BlockWeights {
     float qkv_amax_h[3] = {0.f, 0.f, 0.f};
     float h_amax_h = 0.f;
     // BF16 and FP8 processors: the tiled attention kernels' bias table of
-    // this block, prepared once at creation (null: prepared per launch)
+    // this block, prepared once at creation (null: a window they do not cover)
     float *nat_tbl = nullptr;
 };
 
