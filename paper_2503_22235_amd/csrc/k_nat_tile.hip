@@ -1775,7 +1775,7 @@ template <int KZ, int KY, int KX>
 hipError_t launch_tile(const NatArgs &a, hipStream_t stream) {
     if (a.amax && a.vt) return launch_ring_fp8<KZ, KY, KX>(a, stream);
     if (a.q8 || a.o8) return hipErrorInvalidValue;   // e4m3 q / o: the level-ring kernel only
-    if (a.amax) return launch_tile_fp8<KZ, KY, KX>(a, stream);
+    if (a.amax) return a.tbl_ready ? hipErrorInvalidValue : launch_tile_fp8<KZ, KY, KX>(a, stream);   // (prepares B x H tables itself)
     if (a.vt) {
         if (a.qscale == 1.0f) return launch_ring<KZ, KY, KX, true>(a, stream);
         return launch_ring<KZ, KY, KX, false>(a, stream);
