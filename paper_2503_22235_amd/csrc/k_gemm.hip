@@ -229,7 +229,14 @@ hipError_t launch_gemm(const void *A, const void *W, int M, int N, int K, bool a
     if (!a_bf16 && (unsigned long long)N * K * 4 < (1ull << 31)) return launch_gemm_f32(A, W, M, N, K, epi, ep, stream);
     // permuted W rows and the blocked V layout are the LDS kernels' only
     if (ep.perm || ep.vt || ep.out8 || epi == EPI_RESID_LN) return hipErrorInvalidValue;
-    if (a_bf16) return launch_cfg<bf16, 128, 64>(A, W, M, N, K, epi, ep, stream);
+    // 128 x 128 tiles where N allows them: ms with 128 x 64 / 128 x 128, M = 3000,
+    // bf16 (N, K) = (2^20, 1024) 43 / 20, (65536, 16384) 43 / 18, float32
+    // (2^19, 1024) 48 / 32; M = 1 1.75 / 0.79, 1.72 / 0.73, 1.99 / 1.39
+    if (a_bf16) {
+        if (N % 128 == 0) return launch_cfg<bf16, 128, 128>(A, W, M, N, K, epi, ep, stream);
+        return launch_cfg<bf16, 128, 64>(A, W, M, N, K, epi, ep, stream);
+    }
+    if (N % 128 == 0) return launch_cfg<float, 128, 128>(A, W, M, N, K, epi, ep, stream);
     return launch_cfg<float, 128, 64>(A, W, M, N, K, epi, ep, stream);
 }
 

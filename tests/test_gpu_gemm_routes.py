@@ -36,3 +36,49 @@ def test_gelu_of_64_wide_maps(env, M, N, K):
     ends = [torch.from_numpy(ref + s * d).bfloat16().double().numpy() for s in (-1, 1)]
     got = out.double().cpu().numpy()
     assert ((ends[0] <= got) & (got <= ends[1])).all()
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("extra", [0, 64])
+def test_weights_of_2_gib(env, extra, bf16):
+    """Weights past 32-bit offsets, with 128- and 64-wide tiles: sampled features of
+    every row against float64 (relative L2: bf16 outputs 5e-3, whose rounding is
+    1.1e-3 rms; float32 2 (sqrt(K / 4) + 1) 2^-24, a rounding per four products)."""
+    wm, torch = env
+    K, M = 1024, 131
+    N = (1 << (20 if bf16 else 19)) + extra
+    print("2 GiB of weights", N, "bf16" if bf16 else "f32", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    dt = torch.bfloat16 if bf16 else torch.float32
+    w = torch.randn((N, K), generator=gen, device="cuda", dtype=dt)
+    a = torch.randn((M, K), generator=gen, device="cuda", dtype=dt)
+    b = torch.randn(N, generator=gen, device="cuda")
+    out = torch.empty((M, N), dtype=dt, device="cuda")
+    wm.wm_linear(M, N, K, wm.WM_BF16 if bf16 else wm.WM_F32, a, w, b, 0, out)
+    cols = torch.cat([torch.arange(70), torch.randint(0, N, (300,)), torch.arange(N - 70, N)]).cuda()
+    ref = (a.double() @ w[cols].double().T + b[cols].double()).cpu().numpy()
+    err = O.rel_l2(out[:, cols].double().cpu().numpy(), ref)
+    print("  rel_l2", err, flush=True)
+    assert err < (5e-3 if bf16 else 2 * (np.sqrt(K / 4) + 1) * 2.0 ** -24)
+
+
+def test_weights_of_2_gib_keep_the_wide_tile(env):
+    """N a multiple of 128 runs on 128-wide tiles, in half the time of 64-wide ones."""
+    wm, torch = env
+    K, M, times = 1024, 700, []
+    for N in (1 << 20, (1 << 20) + 64):
+        print("2 GiB of weights, time", N, flush=True)
+        w = torch.randn((N, K), device="cuda", dtype=torch.bfloat16)
+        a = torch.randn((M, K), device="cuda", dtype=torch.bfloat16)
+        b, out = torch.zeros(N, device="cuda"), torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+        best = float("inf")
+        for _ in range(4):
+            t = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            t[0].record()
+            wm.wm_linear(M, N, K, wm.WM_BF16, a, w, b, 0, out)
+            t[1].record()
+            torch.cuda.synchronize()
+            best = min(best, t[0].elapsed_time(t[1]))
+        times.append(best)
+    print("  ms", times, flush=True)
+    assert times[0] < 0.75 * times[1]
