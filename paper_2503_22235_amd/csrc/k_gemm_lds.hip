@@ -167,12 +167,19 @@ __device__ __forceinline__ Split3 split3(const i32x4 (&raw)[2]) {
 // again with f32 MFMAs, operands straight from global memory: an operand is not
 // finite, or the scaled sum overflows, and this gives what float32 arithmetic
 // gives.  The finite sums of a tile are kept, so that a row's result does not
-// depend on its neighbours.
+// depend on its neighbours.  A NaN in a row of A makes all its sums NaN: where one
+// is among the first 32 (in a row that a LayerNorm or a map wrote all are), no
+// products are needed, so that a state which has diverged costs little more than
+// another (a float32 block at 8x90x180, C = 512: 6.1 to 6.5 ms, all NaN 18.1 with
+// the products and 5.8 without).  Values and sums past the split's range cost
+// both routes: M = 129600, N = 1536, K = 512 of 1e32 4.2 ms, 1.4 in range.
 template <int TM, int TN>
 __device__ void f32_finish(const float *A, const float *W, int M, int K, int r0, int n0, int g, int r16, f32x4 (&acc)[TN][TM]) {
     const float *ar[TM];
 #pragma unroll
     for (int i = 0; i < TM; ++i) ar[i] = A + (size_t)min(r0 + 16 * i + r16, M - 1) * K + 8 * g;
+    unsigned anan = 0;                                     // bit i: row 16 i + r16 has a NaN
+    bool scanned = false;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
         bool bad = false;
@@ -186,25 +193,45 @@ __device__ void f32_finish(const float *A, const float *W, int M, int K, int r0,
             continue;
         }
         const float *wr = W + (size_t)(n0 + 16 * j + r16) * K + 8 * g;
-        f32x4 t[TM];
+        if (!scanned) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i) t[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-        // lane group g contracts k = 8 g + s over the 8 steps s
-        for (int k = 0; k < K; k += 32)
+            for (int i = 0; i < TM; ++i) {
+                const f32x4 lo = *(const f32x4 *)ar[i], hi = *(const f32x4 *)(ar[i] + 4);
+                bool nan = false;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const f32x4 w = *(const f32x4 *)(wr + k + 4 * h);
-#pragma unroll
-                for (int i = 0; i < TM; ++i) {
-                    const f32x4 a = *(const f32x4 *)(ar[i] + k + 4 * h);
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) t[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s], a[s], t[i], 0, 0, 0);
-                }
+                for (int c = 0; c < 4; ++c) nan |= __builtin_isnan(lo[c]) || __builtin_isnan(hi[c]);
+                const unsigned long long m = __builtin_amdgcn_ballot_w64(nan) >> r16;      // the row's lanes: every 16th
+                anan |= (m & 0x0001000100010001ull ? 1u : 0u) << i;
             }
+            scanned = true;
+        }
+        bool todo = false;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc[j][i][c] = __builtin_isfinite(acc[j][i][c]) ? acc[j][i][c] * UNSPLIT : t[i][c];
+            for (int c = 0; c < 4; ++c) todo |= !__builtin_isfinite(acc[j][i][c]) && !(anan >> i & 1u);
+        f32x4 t[TM];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) t[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (__builtin_amdgcn_ballot_w64(todo))
+            // lane group g contracts k = 8 g + s over the 8 steps s
+            for (int k = 0; k < K; k += 32)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const f32x4 w = *(const f32x4 *)(wr + k + 4 * h);
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+                        const f32x4 a = *(const f32x4 *)(ar[i] + k + 4 * h);
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) t[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s], a[s], t[i], 0, 0, 0);
+                    }
+                }
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                acc[j][i][c] = __builtin_isfinite(acc[j][i][c]) ? acc[j][i][c] * UNSPLIT
+                                                                : (anan >> i & 1u ? __builtin_nanf("") : t[i][c]);
     }
 }
 

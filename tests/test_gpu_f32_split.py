@@ -92,3 +92,53 @@ def test_state_beside_one_that_has_diverged(env):
     assert torch.equal(x[1:], alone)
     assert not torch.isfinite(x[0]).all()
     p.close()
+
+
+def test_nan_rows_and_features(env):
+    """Every row of a state or every feature of w NaN, and NaN rows beside an
+    infinity and an overflow: what float32 arithmetic gives."""
+    wm, torch, ctx = env
+    M, N, K = 200, 192, 160
+    print("nan rows", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    b = torch.zeros(N, device="cuda")
+    run = lambda a, w: wm.wm_linear(M, N, K, wm.WM_F32, a, w, b, 0, out := torch.empty((M, N), device="cuda")) or out
+    a, w = torch.rand((M, K), generator=gen, device="cuda") + 0.5, torch.rand((N, K), generator=gen, device="cuda") + 0.5
+    clean = run(a, w)
+    assert torch.isnan(run(torch.full_like(a, float("nan")), w)).all()
+    assert torch.isnan(run(a, torch.full_like(w, float("nan")))).all()
+    a2, w2 = a.clone(), w.clone()
+    a2[::2, 3] = float("nan")               # every other row
+    a2[1, 7], a2[65, 9] = float("inf"), -float("inf")
+    a2[3] = 3e38
+    w2[5, 150], w2[130, 0] = float("nan"), float("nan")
+    out = run(a2, w2)
+    assert torch.isnan(out[::2]).all() and torch.isnan(out[:, [5, 130]]).all()
+    rest = torch.ones(N, dtype=torch.bool, device="cuda")
+    rest[[5, 130]] = False
+    assert (out[1, rest] == float("inf")).all() and (out[65, rest] == -float("inf")).all() and (out[3, rest] == float("inf")).all()
+    rows = [r for r in range(1, M, 2) if r not in (1, 3, 65)]
+    assert torch.equal(out[rows][:, rest], clean[rows][:, rest])
+
+
+def test_diverged_state_costs_little_more(env):
+    """A float32 map of NaN rows takes less than 1.5 times a finite one's time
+    (three times where every sum was done again)."""
+    wm, torch, ctx = env
+    M, N, K = 64800, 512, 512
+    print("diverged, time", flush=True)
+    w, b, out = torch.randn((N, K), device="cuda"), torch.zeros(N, device="cuda"), torch.empty((M, N), device="cuda")
+    times = []
+    for a in (torch.randn((M, K), device="cuda"), torch.full((M, K), float("nan"), device="cuda")):
+        best = float("inf")
+        for _ in range(5):
+            t = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            t[0].record()
+            for _ in range(3):
+                wm.wm_linear(M, N, K, wm.WM_F32, a, w, b, 0, out)
+            t[1].record()
+            torch.cuda.synchronize()
+            best = min(best, t[0].elapsed_time(t[1]))
+        times.append(best)
+    print("  ms", times, flush=True)
+    assert times[1] < 1.5 * times[0]
