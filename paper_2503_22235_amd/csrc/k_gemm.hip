@@ -1,5 +1,6 @@
-// Launcher of the linear maps, and the MFMA GEMM for weights of 2 GiB and
-// more, beyond the 32-bit buffer offsets of the LDS-ring kernels.
+// Launcher of the linear maps, and the MFMA GEMM for what the LDS-ring kernels
+// do not take: weights of 2 GiB and more (32-bit buffer offsets), and float32 or
+// 64-wide maps whose operands are not 16-byte aligned (direct loads to LDS).
 //
 //   D[m][n] = sum_k A[m][k] * W[n][k]
 //
@@ -225,8 +226,9 @@ hipError_t launch_gemm(const void *A, const void *W, int M, int N, int K, bool a
                        const EpiArgs &ep, hipStream_t stream) {
     if (M <= 0) return hipSuccess;
     if (N % 64 || K % (a_bf16 ? 64 : 32)) return hipErrorInvalidValue;
-    if (a_bf16 && gemm_lds_applies(M, N, K)) return launch_gemm_lds(A, W, M, N, K, epi, ep, stream);
-    if (!a_bf16 && (unsigned long long)N * K * 4 < (1ull << 31)) return launch_gemm_f32(A, W, M, N, K, epi, ep, stream);
+    const bool aligned = (((uintptr_t)A | (uintptr_t)W) & 15) == 0;
+    if (a_bf16 && gemm_lds_applies(M, N, K) && (aligned || N % 128 == 0)) return launch_gemm_lds(A, W, M, N, K, epi, ep, stream);
+    if (!a_bf16 && aligned && (unsigned long long)N * K * 4 < (1ull << 31)) return launch_gemm_f32(A, W, M, N, K, epi, ep, stream);
     // permuted W rows and the blocked V layout are the LDS kernels' only
     if (ep.perm || ep.vt || ep.out8 || epi == EPI_RESID_LN) return hipErrorInvalidValue;
     // 128 x 128 tiles where N allows them: ms with 128 x 64 / 128 x 128, M = 3000,

@@ -82,3 +82,33 @@ def test_weights_of_2_gib_keep_the_wide_tile(env):
         times.append(best)
     print("  ms", times, flush=True)
     assert times[0] < 0.75 * times[1]
+
+
+@pytest.mark.parametrize("bf16,N", [(False, 192), (False, 128), (True, 192)])
+@pytest.mark.parametrize("which", ["a", "w", "bias and out"])
+def test_operands_at_odd_elements(env, which, bf16, N):
+    """Tensors that start one element into a buffer: the direct loads to LDS are
+    for 16-byte aligned operands (other kernel, other order of the sums: relative
+    L2 as in test_weights_of_2_gib)."""
+    wm, torch = env
+    M, K = 77, 128
+    print("odd elements", which, N, "bf16" if bf16 else "f32", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    dt = torch.bfloat16 if bf16 else torch.float32
+
+    def place(t, odd):
+        if not odd:
+            return t.contiguous()
+        buf = torch.empty(t.numel() + 8, dtype=t.dtype, device="cuda")
+        v = buf[1:1 + t.numel()].view(t.shape)
+        v.copy_(t)
+        return v
+
+    a = place(torch.randn((M, K), generator=gen, device="cuda").to(dt), which == "a")
+    w = place(torch.randn((N, K), generator=gen, device="cuda").to(dt), which == "w")
+    odd = which == "bias and out" and not bf16
+    b = place(torch.randn(N, generator=gen, device="cuda"), odd)
+    out = place(torch.zeros((M, N), dtype=dt, device="cuda"), odd)
+    wm.wm_linear(M, N, K, wm.WM_BF16 if bf16 else wm.WM_F32, a, w, b, 0, out)
+    ref = (a.double() @ w.double().T + b.double()).cpu().numpy()
+    assert O.rel_l2(out.double().cpu().numpy(), ref) < (5e-3 if bf16 else 2 * (np.sqrt(K / 4) + 1) * 2.0 ** -24)
