@@ -1,9 +1,9 @@
-// MFMA GEMM (bf16 or e4m3 operands, float32 accumulation) fed by an LDS
-// ring that direct buffer->LDS loads fill.
+// MFMA GEMM (bf16 or e4m3 operands, or float32 ones split into bf16 parts;
+// float32 accumulation) fed by an LDS ring that direct buffer->LDS loads fill.
 //
 //   D[m][n] = sum_k A[m][k] * W[n][k]      (A: tokens x K, W: [out][in])
 //
-// K advances in stages of 128 bytes per row (64 bf16 or 128 e4m3 values),
+// K advances in stages of 128 bytes per row (64 bf16, 128 e4m3 or 32 float32 values),
 // written straight from global memory into LDS by buffer_load_dwordx4 ... lds
 // (no register staging).  Rows of A past M come back as zeros from the buffer
 // range check, which handles the ragged last token tile.  16-byte chunks of an
@@ -124,16 +124,17 @@ __device__ __forceinline__ f32x4 mma_fp8(const i32x4 (&wf)[2], const i32x4 (&af)
 // more: times 2^24 it is 2^-125, a normal bf16, so no part is lost however small
 // x is (without the factor the parts of x < 2^-110 fell under bf16's smallest
 // values: errors of 2^-22 of x at 2^-112, 2^-8 at 2^-126).  Values of 2^104 and
-// more and sums of 2^80 and more overflow and are done again (f32_finish).  A product is the sum of the six partial
-// products x_i w_j with i + j <= 4, smallest first; the three left out are
-// below 2^-26 of it, with either sign.  The products of bf16 values are exact
-// and the sum takes 6 roundings per 32 k where 16x16x4 f32 MFMAs take 8, at
-// six bf16 MFMAs of 16 cycles instead of eight of 32.  Measured (N(0,1) rows,
-// N(0,0.02) weights) the relative error against float64 is 1.54e-7, 3.36e-7,
-// 4.9e-7 and 1.00e-6 at K = 128, 512, 1024 and 4096, against 2.04e-7, 4.06e-7,
-// 5.7e-7 and 1.15e-6 with f32 MFMAs.  M = 129600, N = 1536, K = 512: 2158 ->
-// 1191 us (171 TFLOP/s of products; the f32 MFMA kernel reached 94).  Lane and
-// k layout are those of one 16x16x32 operand (8 consecutive k).
+// more and sums of 2^80 and more overflow and are done again (f32_finish).
+// A product is the sum of the six partial products x_i w_j with i + j <= 4,
+// smallest first; the three left out are below 2^-26 of it, with either sign.
+// The products of bf16 values are exact and the sum takes 6 roundings per 32 k
+// where 16x16x4 f32 MFMAs take 8, at six bf16 MFMAs of 16 cycles instead of eight
+// of 32.  Measured (N(0,1) rows, N(0,0.02) weights) the relative error against
+// float64 is 1.54e-7, 3.36e-7, 4.9e-7 and 1.00e-6 at K = 128, 512, 1024 and 4096,
+// against 2.04e-7, 4.06e-7, 5.7e-7 and 1.15e-6 with f32 MFMAs.  M = 129600,
+// N = 1536, K = 512: 2141 us with those, 1165 so (1110 without the factor); K =
+// 2048, N = 512: 2714, 1461 (1382).  Lane and k layout are those of one 16x16x32
+// operand (8 consecutive k).
 constexpr float SPLIT_SCALE = 0x1p24f, UNSPLIT = 0x1p-48f;
 struct Split3 {
     i32x4 p[3];

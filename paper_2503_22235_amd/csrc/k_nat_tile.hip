@@ -168,7 +168,7 @@ __global__ __launch_bounds__(256, 2) void nat_tile_kernel(NatArgs p, int ZWmax, 
 
     constexpr int TBLP = tbl9_padded<KZ, KY, KX>();
     extern __shared__ __align__(16) unsigned char smem[];
-    float *tbl = (float *)smem;                                  // [BZ][BY][XT] + a run of -inf
+    float *tbl = (float *)smem;                                  // [BZ][BY][XT9] + a run of -inf
     unsigned char *Vh = smem + TBLP * 4;                         // [ZWmax * YR] slabs of 1 KB
 
     // ---- tile of this workgroup (XCD-aware order over (b, h, tile)) ----
@@ -1242,7 +1242,7 @@ __global__ __launch_bounds__(256, 4) void nat_ring_fp8_kernel(NatArgs p, TileDiv
                 stage(h + 1, 0, lv);
                 stage(h + 1, 1, lv == 2 ? 0 : lv + 1);
             }
-                    store_tbl();
+            store_tbl();
             own_score();
             wait_vmcnt<0>();
             __syncthreads();
@@ -1577,7 +1577,7 @@ __global__ __launch_bounds__(256, 2) void nat_tile_fp8_kernel(NatArgs p, int ZWm
                 const int a = (okz && oky[hf][j]) ? tbh : TBL;
                 const float *tp = tbl + a + (4 * hf + 2 * j) * XT9;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) binit[j][i] = tp[i];
+                for (int i = 0; i < 4; ++i) binit[j][i] = tp[i];
             }
             f32x4 s[2][2];
             float cm[2];

@@ -131,12 +131,11 @@ __host__ __device__ inline int perm_row(int o) {
 }
 // A: [M][K], W: [N][K], both bf16 (a_bf16) or float32.  Output element
 // type follows the operands (bf16 or float) except EPI_RESID (float32).
-// Requires N % 128 == 0 (N % 64 for small N) and K % 64 == 0 (bf16) /
-// K % 32 == 0 (float32).
+// Requires N % 64 == 0 and K % 64 == 0 (bf16) / K % 32 == 0 (float32).
 hipError_t launch_gemm(const void *A, const void *W, int M, int N, int K, bool a_bf16,
                        EpiKind epi, const EpiArgs &ep, hipStream_t stream);
 
-// The LDS-ring bf16 kernel (taken by launch_gemm when it applies).
+// The LDS-ring bf16 kernels (taken by launch_gemm where they apply).
 bool gemm_lds_applies(int M, int N, int K);
 hipError_t launch_gemm_lds(const void *A, const void *W, int M, int N, int K, EpiKind epi,
                            const EpiArgs &ep, hipStream_t stream);
@@ -198,8 +197,8 @@ struct NatArgs {
     const float *amax;
     int amax_stride;
     // v is in the blocked layout of v_blocked_offset (vt = 1) with xp padded
-    // lon positions per row: bf16 elements with q pre-scaled (qscale = 1),
-    // or (amax set) e4m3 bytes from launch_kv8 with k in e4m3 as well
+    // lon positions per row: bf16 elements, or (amax set) e4m3 bytes from
+    // launch_kv8 with k in e4m3 as well
     int vt;
     int xp;
     // e4m3 level-ring kernel (amax and vt set): q8 set, q holds e4m3 codes
