@@ -16,7 +16,7 @@ enum NatRows : int { NAT_HEAD_MAJOR = 0, NAT_TOKEN_MAJOR = 1, NAT_E4M3 = 2 };
 //       4232   78 /  83 /  93     16928 (16 heads) 398 / 371 / 364     33856 713 / 671 / 698
 //   bf16 from head-major ones (the blocks): nothing is shared, and the halo rows
 //   that the next tiles share have left L2 by the next head (1.02 GB fetched with 4
-//   heads, 0.73 with 2, 0.58 with 1, per block of 129600 tokens).  A walk of 5 to 8
+//   heads, 0.73 with 2, 0.47 with 1, per block of 129600 tokens).  A walk of 5 to 8
 //   levels covers what a workgroup does around it; one of 3 to 5 gains by two heads
 //       8832  140 / 144 / 150     12512  209 / 213 / 218     16928 282 / 282 / 284
 //     3x5x5:  9216  111 / 106 / 107     16928  204 / 195 / 197     36864 440 / 413 / 401
