@@ -152,3 +152,31 @@ def test_states_straddling_wide_tiles(env, prec):
         wm.wm_processor_step(ctx, p, 1, alone[b])
         assert torch.equal(bufs[b], x[b:b + 1]) and torch.equal(alone[b], x[b:b + 1]), b
     p.close()
+
+
+# a model of width 128: MLP1 has one (e4m3) or two (bf16) K stages, and two states
+# send it to 256-wide tiles that walk row blocks
+NARROW = S.Grid(Z=8, Y=90, X=180, C=128, heads=4, Kz=3, Ky=3, Kx=3)
+
+
+def test_narrow_model_changes_tiles(plan):
+    T, C = NARROW.Z * NARROW.Y * NARROW.X, NARROW.C
+    for stage in (128, 64):
+        assert plan(T, 4 * C, C // stage, 0)[0] == 128 and plan(2 * T, 4 * C, C // stage, 0) == (256, 2, 1)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec", [1, 2])
+def test_narrow_model_alone_and_in_a_batch(env, prec):
+    """The same bits for a state alone (128-wide tiles) and beside another."""
+    wm, torch, ctx = env
+    print("narrow model prec", prec, flush=True)
+    p = wm.wm_processor_create(ctx, NARROW, 1, 4, prec, S.processor_params(NARROW, 1, 1))
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    x = torch.randn((2, NARROW.Z, NARROW.Y, NARROW.X, NARROW.C), generator=gen, device="cuda")
+    alone = [x[b:b + 1].clone() for b in range(2)]
+    wm.wm_processor_step(ctx, p, 2, x)
+    for b in range(2):
+        wm.wm_processor_step(ctx, p, 1, alone[b])
+        assert torch.equal(alone[b], x[b:b + 1]), b
+    p.close()
